@@ -294,7 +294,7 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
             }
         }
         F.kmap_end = (int)P.kpair.size();
-        F.asm_begin = (int)P.asm_rc.size();
+        F.asm_begin = (int)P.asm_dst.size();
         {
             const int nen = 1 << d, ndl = nen * d;
             for (int q = F.kmap_begin; q < F.kmap_end; ++q) {
@@ -303,8 +303,9 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
                     for (int l = 0; l < d; ++l) {
                         int r = kp.row_node * d + k, col = kp.col_node * d + l;
                         if (r < col) continue;
-                        if (r >= 32768 || col >= 32768) throw std::runtime_error("front too large for the gather list");
-                        P.asm_rc.push_back((r << 16) | col);
+                        const int64_t dst = (int64_t)col * F.m - (int64_t)col * (col - 1) / 2 + r - col;
+                        if (dst > INT32_MAX) throw std::runtime_error("front too large for the gather list");
+                        P.asm_dst.push_back((int32_t)dst);
                         for (int t = 0; t < nen; ++t) {
                             int src = -1;
                             if (t < kp.c_count) {
@@ -318,7 +319,7 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
                     }
             }
         }
-        F.asm_end = (int)P.asm_rc.size();
+        F.asm_end = (int)P.asm_dst.size();
         // storage
         F.L_off = Loff;
         Loff += (int64_t)F.m * F.p;
@@ -375,7 +376,7 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
         P.lds_path = mm <= 256 && (mm * (mm + 1) / 2 + mm * d * d) * 8 <= kLdsFrontBytes;
     }
     if (P.lds_path) {
-        int64_t off = 0;
+        int64_t off = 2;  // (element 0 stays zero: read in place of entries a child does not have)
         for (int s = 0; s < ns; ++s) {
             FrontHost& F = P.fronts[s];
             const int64_t mu = F.m - F.p;
@@ -383,6 +384,29 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
             off += mu * mu + mu * kMaxNrhs;  // room for either update-matrix format
         }
         P.U_stack = std::max<int64_t>(off, 1);
+        // right-hand-side columns of the widest solve (2D: the d^2 columns of the
+        // condensation beside the Newton residual) and what they take in LDS: two
+        // buffers of a 16-pivot block's rows beside the panel; in the backward
+        // substitution the front's rows and one partial sum per wave
+        const int64_t rhs_cols = d * d + (d == 2 ? 1 : 0), block_rhs = 2 * 16 * rhs_cols;
+        auto packed_panel = [](const FrontHost& X) { return (int64_t)X.p * X.m - (int64_t)X.p * (X.p - 1) / 2; };
+        for (int s = 0; s < ns; ++s) {
+            FrontHost& F = P.fronts[s];
+            F.inv_off = (int64_t)P.inv.size();
+            if (F.parent < 0) continue;
+            const FrontHost& A = P.fronts[F.parent];
+            const int mc = F.m - F.p;
+            const int32_t* rel = &P.relind[F.relind_off];
+            P.inv.resize(P.inv.size() + A.m, -1);
+            int npiv = 0;
+            for (int q = 0; q < mc; ++q) {
+                const int col = q * mc - q * (q - 1) / 2 - q;
+                if (col > 32767) throw std::runtime_error("front too large for the inverse row map");
+                P.inv[F.inv_off + rel[q]] = (col << 16) | q;
+                npiv += rel[q] < A.p ? 1 : 0;
+            }
+            F.npre = npiv * mc - npiv * (npiv - 1) / 2;
+        }
         int maxh = 0;
         for (int s = 0; s < ns; ++s) {
             FrontHost& F = P.fronts[s];
@@ -395,8 +419,8 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
             }
             if (F.wave) {
                 maxh = std::max(maxh, F.height);
-                // packed front, rhs rows, original diagonal (m <= 64) within the 256 spare
-                P.wave_slice = std::max<int64_t>(P.wave_slice, (int64_t)F.m * (F.m + 1) / 2 + (int64_t)F.m * d * d + 256);
+                P.wave_slice = std::max<int64_t>(P.wave_slice, packed_panel(F) + block_rhs);
+                P.bs_slice = std::max<int64_t>(P.bs_slice, rhs_cols * (F.m + F.p));
             }
         }
         for (int h = 0; h <= maxh; ++h) {
@@ -406,6 +430,83 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
         }
         P.wave_hbeg.push_back((int32_t)P.wave_list.size());
         P.wave_slice = (P.wave_slice + 31) / 32 * 32;
+        // Update matrices that stay in LDS.  A plan of wave fronts only (up to 8 x 8)
+        // keeps all of them, shared by the waves, where they fit.  Otherwise every
+        // maximal subtree whose panels and inner update matrices fit a quarter of
+        // the budget becomes one task of one wave (three fronts of two leaves and
+        // their separator from 16 x 16 on), as long as that leaves a task per wave.
+        auto u_elems = [&](const FrontHost& X) {
+            const int64_t mu = X.m - X.p;
+            return mu * (mu + 1) / 2 + mu * rhs_cols;
+        };
+        std::vector<int64_t> inner(ns, 0);  // LDS of a subtree's inner update matrices
+        std::vector<char> fused(ns, 0);
+        int64_t all_u = 0;
+        bool all_wave = true;
+        for (const FrontHost& F : P.fronts) {
+            all_wave = all_wave && F.wave;
+            all_u += u_elems(F);
+        }
+        const int64_t slices = kSolveWaves * P.wave_slice;
+        P.ul_base = slices;
+        if (all_wave && slices + all_u <= kWaveElemsMax) {
+            int64_t at = 0;
+            for (FrontHost& F : P.fronts)
+                if (F.parent >= 0) {
+                    F.u_lds = (int)at;
+                    at += u_elems(F);
+                }
+            P.wave_elems = slices + at;
+        } else {
+            const int64_t budget = kWaveElemsMax / kSolveWaves - P.wave_slice;
+            for (int s = 0; s < ns; ++s) {
+                const FrontHost& F = P.fronts[s];
+                fused[s] = F.wave;
+                for (int q = F.child_begin; q < F.child_end; ++q) {
+                    const int ch = P.children[q];
+                    fused[s] = fused[s] && fused[ch];
+                    inner[s] += inner[ch] + u_elems(P.fronts[ch]);
+                }
+                fused[s] = fused[s] && inner[s] <= budget;
+            }
+            int ntask = 0;
+            for (int s = 0; s < ns; ++s)
+                ntask += fused[s] && (P.fronts[s].parent < 0 || !fused[P.fronts[s].parent]);
+            if (ntask < kSolveWaves) std::fill(fused.begin(), fused.end(), 0);
+            std::vector<int64_t> at(ns, 0);
+            for (int s = 0; s < ns; ++s) {
+                FrontHost& F = P.fronts[s];
+                if (!fused[s] || F.parent < 0 || !fused[F.parent]) continue;
+                int root = F.parent;  // of the subtree the front is in
+                while (P.fronts[root].parent >= 0 && fused[P.fronts[root].parent]) root = P.fronts[root].parent;
+                F.u_lds = (int)at[root];
+                at[root] += u_elems(F);
+                P.ul_stride = std::max(P.ul_stride, at[root]);
+            }
+            P.ul_stride = (P.ul_stride + 31) / 32 * 32;
+            P.wave_elems = slices + kSolveWaves * P.ul_stride;
+        }
+        // tasks: the subtrees first (a contiguous range of the postorder each), then
+        // the other wave fronts by height
+        P.task_beg.push_back(0);
+        std::vector<int> nsub(ns, 1);
+        for (int s = 0; s < ns; ++s)
+            for (int q = P.fronts[s].child_begin; q < P.fronts[s].child_end; ++q) nsub[s] += nsub[P.children[q]];
+        for (int s = 0; s < ns; ++s)
+            if (fused[s] && (P.fronts[s].parent < 0 || !fused[P.fronts[s].parent])) {
+                P.task.push_back(s - nsub[s] + 1);
+                P.task.push_back(s);
+            }
+        if (!P.task.empty()) P.task_beg.push_back((int32_t)P.task.size() / 2);
+        for (int h = 0; h <= maxh; ++h) {
+            const size_t before = P.task.size();
+            for (int s = 0; s < ns; ++s)
+                if (P.fronts[s].wave && !fused[s] && P.fronts[s].height == h) {
+                    P.task.push_back(s);
+                    P.task.push_back(s);
+                }
+            if (P.task.size() > before) P.task_beg.push_back((int32_t)P.task.size() / 2);
+        }
         // workgroup fronts by height (children first).  Fronts of one height are
         // independent; with equal p and child counts they pass the same barriers,
         // so up to kStepFronts of them can share a step (each on a group of at
@@ -453,6 +554,15 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
                     grp.pop_back();
                 }
                 for (int k = 0; k < kStepFronts; ++k) P.wg_steps.push_back(k < (int)grp.size() ? grp[k] : -1);
+                // (the kernel runs a step's fronts on one or two thread groups)
+                const int ng = std::min<int>((int)grp.size(), kStepGroups), nw = kSolveWaves / ng;
+                int64_t need = 0;
+                for (int f : grp) {
+                    need = std::max(need, packed_panel(P.fronts[f]) + block_rhs);
+                    P.bs_slice = std::max<int64_t>(
+                        P.bs_slice, (rhs_cols * (P.fronts[f].m + nw * (int64_t)P.fronts[f].p) + nw - 1) / nw);
+                }
+                P.wg_elems = std::max(P.wg_elems, ng * need);
             }
         }
     }

@@ -29,6 +29,9 @@ struct FrontHost {
     int kmap_begin = 0, kmap_end = 0;    // into kpair[]
     int asm_begin = 0, asm_end = 0;      // into asm_rc[] (lower-triangle targets of original entries)
     int64_t ea_off = 0;                  // into ea_dst[]: this front's packed update entries -> packed parent offsets
+    int64_t inv_off = 0;                 // into inv[]: the parent's rows -> this front's update rows
+    int u_lds = -1;                      // wave phase: offset of the update matrix among those kept in LDS, or -1
+    int npre = 0;                        // update entries (a prefix) whose target is a pivot column of the parent
     int wave = 0;                        // 1: small front (m <= 64, subtree small) processed by one wave
     int height = 0;                      // 0 for leaves, 1 + max over children
 };
@@ -54,23 +57,36 @@ struct PlanHost {
     std::vector<int32_t> rows, relind, children;
     std::vector<KPair> kpair;
     std::vector<KContrib> kcontrib;
-    // flat gather list of the original entries: target (row << 16 | col) in the
-    // front and up to 2^d element-matrix sources (flat index into the element
-    // matrices [elem][2^d d][2^d d], -1 = none), asm_src[t * 2^d + q]
-    std::vector<int32_t> asm_rc, asm_src;
+    // flat gather list of the original entries: offset in the packed front
+    // (cpk(col, m) + row - col) and up to 2^d element-matrix sources (flat index
+    // into the element matrices [elem][2^d d][2^d d], -1 = none),
+    // asm_src[t * 2^d + q]
+    std::vector<int32_t> asm_dst, asm_src;
     // extend-add map: for every entry t of a front's packed update matrix
     // (column-major lower, (m-p)(m-p+1)/2 entries) the offset of its target in
     // the parent's packed front, cpk(C, m_par) + R - C
     std::vector<int32_t> ea_dst;
+    // inverse row maps (LDS plans): for every row of a front and each child, -1 or
+    // the child's update row i in the low half and its packed column offset
+    // cpk(i, m_child - p_child) - i in the high half
+    std::vector<int32_t> inv;
     // fronts processed wave-per-front before the workgroup fronts, grouped by
     // height (all fronts of one height are independent)
     std::vector<int32_t> wave_list, wave_hbeg;
+    // the wave phase's tasks, (first front, last front) pairs of contiguous fronts
+    // in level order: a whole subtree whose inner update matrices stay in the
+    // wave's LDS, or one front
+    std::vector<int32_t> task, task_beg;
+    int64_t ul_base = 0, ul_stride = 0;  // where the waves' LDS update matrices start, elements per wave (0: shared)
     // the other (workgroup) fronts in processing order, kStepFronts entries per
     // step (-1 padded): one front on the whole workgroup, or 2 or 4 independent
     // fronts (equal height, pivot and child counts) side by side on equal parts
     // of it
     std::vector<int32_t> wg_steps;
-    int64_t wave_slice = 0;    // doubles of one wave's LDS slice (packed front + rhs rows)
+    int64_t wave_slice = 0;    // elements of one wave's LDS slice (panel + rhs of the block rows)
+    int64_t wave_elems = 0;    // LDS elements of the wave phase (slices + update matrices)
+    int64_t wg_elems = 0;      // LDS elements of the largest workgroup step (panels + block-row rhs)
+    int64_t bs_slice = 0;      // FP64 scratch per wave of the backward substitution
     bool lds_path = false;     // every front fits the LDS front buffer
     int64_t L_size = 0;        // doubles of L + D + y storage
     int64_t U_stack = 0;       // doubles of the update-matrix stack
@@ -84,6 +100,10 @@ struct PlanHost {
 constexpr int64_t kLdsFrontBytes = 148 * 1024;
 constexpr int kWaveFrontMaxM = 64;
 constexpr int kStepFronts = 4;  // fronts per workgroup-front step at most
+constexpr int kSolveWaves = 4;  // waves of the solver's workgroup
+// LDS elements a wave phase may take (FP64: 74 KB, which leaves two workgroups per CU)
+constexpr int64_t kWaveElemsMax = 9472;
+constexpr int kStepGroups = 2;  // thread groups that share a step's fronts
 
 // Builds the plan; throws std::runtime_error on unsupported (d, n).
 // structural parameters of a plan (the autotuner's plan-level knobs)

@@ -18,20 +18,10 @@
 #include "solver_dev.h"
 
 namespace fehmm {
-// the solver compiled with 256-thread (four-wave) and 512-thread (eight-wave) workgroups
-namespace nt256 {
 hipError_t launch_rve_solve(const SolveArgs& a, int nslots, size_t dyn_bytes, bool fp32, hipStream_t stream);
 hipError_t launch_rve_assembly(const SolveArgs& a, int nslots, hipStream_t stream);
 hipError_t prepare_rve_solve();
 int lds_static_bytes();
-}
-namespace nt512 {
-hipError_t launch_rve_solve(const SolveArgs& a, int nslots, size_t dyn_bytes, bool fp32, hipStream_t stream);
-hipError_t launch_rve_assembly(const SolveArgs& a, int nslots, hipStream_t stream);
-hipError_t prepare_rve_solve();
-int lds_static_bytes();
-}
-constexpr int NWAVE_ = 4;  // waves per workgroup of the default solver
 }
 
 using namespace fehmm;
@@ -68,7 +58,10 @@ struct PlanEntry {
     int32_t* d_children = nullptr;
     KPair* d_kpair = nullptr;
     KContrib* d_kcontrib = nullptr;
-    int32_t* d_asm_rc = nullptr;
+    int32_t* d_asm_dst = nullptr;
+    int32_t* d_inv = nullptr;
+    DevChild* d_childrec = nullptr;
+    int32_t *d_task = nullptr, *d_task_beg = nullptr;
     int32_t* d_asm_src = nullptr;
     int32_t* d_ea_dst = nullptr;
     int32_t* d_wave_list = nullptr;
@@ -76,9 +69,7 @@ struct PlanEntry {
     int32_t* d_wg_steps = nullptr;
     int refs = 0;
     int device = -1;
-    int64_t lds_bytes = 0;            // FP64 fronts: dynamic LDS bytes
-    int64_t front_elems[2] = {0, 0};  // LDS front region (elements of FP64 / FP32)
-    int64_t rl_elems = 0;             // rhs rows following it
+    int64_t lds_need[2] = {0, 0};     // LDS plans: dynamic LDS bytes with FP64 / FP32 factors
 };
 
 std::mutex g_mu;
@@ -102,12 +93,6 @@ int tuned_slots(int d, int n) {
     return it != g_tuning.end() ? it->second.slots : 0;
 }
 
-int tuned_threads(int d, int n) {
-    std::lock_guard<std::mutex> lk(g_mu);
-    auto it = g_tuning.find(std::make_pair(d, n));
-    return it != g_tuning.end() ? it->second.threads : 0;
-}
-
 template <typename T>
 int upload(const std::vector<T>& v, T** out) {
     size_t bytes = std::max<size_t>(v.size(), 1) * sizeof(T);
@@ -119,7 +104,8 @@ int upload(const std::vector<T>& v, T** out) {
 void free_plan_dev(PlanEntry& e) {
     (void)hipFree(e.d_fronts); (void)hipFree(e.d_rows); (void)hipFree(e.d_relind);
     (void)hipFree(e.d_children); (void)hipFree(e.d_kpair); (void)hipFree(e.d_kcontrib);
-    (void)hipFree(e.d_asm_rc); (void)hipFree(e.d_asm_src); (void)hipFree(e.d_ea_dst);
+    (void)hipFree(e.d_asm_dst); (void)hipFree(e.d_inv); (void)hipFree(e.d_childrec); (void)hipFree(e.d_task); (void)hipFree(e.d_task_beg);
+    (void)hipFree(e.d_asm_src); (void)hipFree(e.d_ea_dst);
     (void)hipFree(e.d_wave_list); (void)hipFree(e.d_wave_hbeg); (void)hipFree(e.d_wg_steps);
     e.d_fronts = nullptr;
 }
@@ -154,12 +140,18 @@ int plan_device(PlanEntry* e) {
     for (size_t s = 0; s < fr.size(); ++s) {
         const FrontHost& f = P.fronts[s];
         fr[s] = DevFront{f.m, f.p, f.parent, f.child_begin, f.child_end, f.kmap_begin, f.kmap_end, f.asm_begin,
-                         f.asm_end, f.wave, f.rows_off, f.relind_off, f.L_off, f.D_off, f.y_off, f.U_off, f.ea_off};
+                         f.asm_end, f.u_lds, f.rows_off, f.relind_off, f.L_off, f.D_off, f.y_off, f.U_off, f.ea_off};
+    }
+    std::vector<DevChild> cr(P.children.size());
+    for (size_t q = 0; q < cr.size(); ++q) {
+        const FrontHost& f = P.fronts[P.children[q]];
+        cr[q] = DevChild{f.m - f.p, f.npre, f.u_lds, 0, f.ea_off, f.inv_off, f.U_off};
     }
     int st;
-    if ((st = upload(fr, &e->d_fronts)) || (st = upload(P.rows, &e->d_rows)) || (st = upload(P.relind, &e->d_relind)) ||
+    if ((st = upload(fr, &e->d_fronts)) || (st = upload(P.inv, &e->d_inv)) || (st = upload(cr, &e->d_childrec)) ||
+        (st = upload(P.task, &e->d_task)) || (st = upload(P.task_beg, &e->d_task_beg)) || (st = upload(P.rows, &e->d_rows)) || (st = upload(P.relind, &e->d_relind)) ||
         (st = upload(P.children, &e->d_children)) || (st = upload(P.kpair, &e->d_kpair)) ||
-        (st = upload(P.kcontrib, &e->d_kcontrib)) || (st = upload(P.asm_rc, &e->d_asm_rc)) ||
+        (st = upload(P.kcontrib, &e->d_kcontrib)) || (st = upload(P.asm_dst, &e->d_asm_dst)) ||
         (st = upload(P.asm_src, &e->d_asm_src)) || (st = upload(P.ea_dst, &e->d_ea_dst)) ||
         (st = upload(P.wave_list, &e->d_wave_list)) || (st = upload(P.wave_hbeg, &e->d_wave_hbeg)) ||
         (st = upload(P.wg_steps, &e->d_wg_steps))) {
@@ -168,27 +160,23 @@ int plan_device(PlanEntry* e) {
     }
     e->dev = DevPlan{P.d, P.n, P.nnode, P.nelem, (int32_t)P.fronts.size(), 0,
                      e->d_fronts, e->d_rows, e->d_relind, e->d_children, e->d_kpair, e->d_kcontrib,
-                     e->d_asm_rc, e->d_asm_src, e->d_ea_dst, e->d_wave_list, e->d_wave_hbeg,
+                     e->d_asm_dst, e->d_asm_src, e->d_ea_dst, e->d_inv, e->d_childrec, e->d_wave_list, e->d_wave_hbeg,
                      (int32_t)P.wave_hbeg.size() - 1, (int32_t)P.wave_slice, e->d_wg_steps,
-                     (int32_t)(P.wg_steps.size() / kStepFronts)};
+                     (int32_t)(P.wg_steps.size() / kStepFronts), e->d_task, e->d_task_beg,
+                     std::max<int32_t>((int32_t)P.task_beg.size() - 1, 0), (int32_t)P.ul_base, (int32_t)P.ul_stride, 0};
     if (P.wave_hbeg.empty()) e->dev.nwave_h = 0;
     e->dev.bc = P.bc;
-    // whole fronts in LDS when the largest packed front plus its rhs rows fit;
-    // the front region also hosts the FP64 scratch of the triangular solves
-    // (m d^2 + 3 m doubles)
-    const int64_t mm = P.max_m;
-    int64_t scratch = 0;
-    for (const FrontHost& fr : P.fronts) scratch = std::max<int64_t>(scratch, (int64_t)fr.m * (P.d * P.d + 3));
-    e->front_elems[0] = std::max<int64_t>(mm * (mm + 1) / 2, scratch);
-    e->front_elems[1] = std::max<int64_t>(mm * (mm + 1) / 2, 2 * scratch);
-    // rhs rows (d^2 + 1 in 2D: the Newton residual beside the condensation's
-    // columns, see rve_solve_kernel), then the original diagonal
-    e->rl_elems = mm * (P.d * P.d + (P.d == 2 ? 2 : 1));
-    const int64_t need = std::max<int64_t>(e->front_elems[0] + e->rl_elems, NWAVE_ * P.wave_slice) *
-                         (int64_t)sizeof(double);
-    e->lds_bytes = need;
-    // (one thread per front row in the pivot sweep: m <= 256; the plan decides)
-    e->dev.lds_ok = (P.lds_path && need + nt256::lds_static_bytes() + 1024 <= kLdsBytesMax) ? 1 : 0;
+    // dynamic LDS of a plan whose panels live there: the wave phase's slices, the
+    // workgroup steps' panels, the FP64 scratch of the backward substitution and
+    // (FP32 factors) the FP64 rows of the refinement's forward substitution
+    const int64_t rhs_cols = P.d * P.d + (P.d == 2 ? 1 : 0);
+    for (int k = 0; k < 2; ++k) {
+        const int64_t es = k == 0 ? 8 : 4;
+        e->lds_need[k] = std::max({es * std::max<int64_t>(P.wave_elems, P.wg_elems),
+                                   8 * kSolveWaves * P.bs_slice, 8 * (int64_t)P.max_m * rhs_cols});
+    }
+    // (one thread per front row: m <= 256; the plan decides)
+    e->dev.lds_ok = (P.lds_path && e->lds_need[0] + lds_static_bytes() + 1024 <= kLdsBytesMax) ? 1 : 0;
     return RVE_OK;
 }
 
@@ -218,13 +206,8 @@ struct rve_batch_s {
     int d = 0;
     int64_t B = 0;
     int nslots = 0;
-    int64_t lds_front[2] = {0, 0};  // front region of the dynamic LDS (FP64 / FP32 elements)
-    int64_t wave_slice = 0;         // elements per wave slice
-    size_t dyn_bytes[2] = {0, 0};
-    // per precision: launch the eight-wave solver (2D LDS plans whose fronts leave
-    // room for one four-wave workgroup per CU only) with its dynamic LDS size
-    bool wide[2] = {false, false};
-    size_t dyn_bytes_wide[2] = {0, 0};
+    int64_t bs_slice = 0;           // FP64 scratch per wave of the backward substitution
+    size_t dyn_bytes[2] = {0, 0};   // dynamic LDS with FP64 / FP32 factors
     SlotLayout lay{};
     std::vector<int64_t> state_off;
     // device
@@ -388,8 +371,7 @@ static void free_batch(rve_batch_s* b) {
 static int ensure_prepared() {
     static bool prepared = false;
     if (!prepared) {
-        hipError_t pe = nt256::prepare_rve_solve();
-        if (pe == hipSuccess) pe = nt512::prepare_rve_solve();
+        hipError_t pe = prepare_rve_solve();
         if (pe != hipSuccess) return fail(RVE_EHIP, std::string("rve kernels: ") + hipGetErrorString(pe));
         prepared = true;
     }
@@ -460,35 +442,19 @@ int rve_batch_create(const rve_mesh* meshes, int64_t B, rve_batch* out) {
         Ust = std::max(Ust, p->host.U_stack);
         Usc = std::max(Usc, p->host.U_scratch);
     }
-    for (PlanEntry* p : plans)
+    for (PlanEntry* p : plans) {
         if (p->dev.lds_ok) {
-            for (int k = 0; k < 2; ++k) b->lds_front[k] = std::max(b->lds_front[k], p->front_elems[k]);
-            b->wave_slice = std::max(b->wave_slice, p->host.wave_slice);
-        }
-    {
-        int64_t rl = 0;
-        for (PlanEntry* p : plans)
-            if (p->dev.lds_ok) rl = std::max(rl, p->rl_elems);
-        bool glb = false;
-        for (PlanEntry* p : plans) glb = glb || !p->dev.lds_ok;
-        const int threads = tuned_threads(d, meshes[0]->n);
-        for (int k = 0; k < 2; ++k) {
-            const int64_t es = k == 0 ? 8 : 4;
-            int64_t elems = std::max(b->lds_front[k] + rl, NWAVE_ * b->wave_slice);
-            int64_t bytes = elems * es;
+            for (int k = 0; k < 2; ++k) b->dyn_bytes[k] = std::max<size_t>(b->dyn_bytes[k], (size_t)p->lds_need[k]);
+            b->bs_slice = std::max(b->bs_slice, p->host.bs_slice);
+        } else {
             // global fronts: staged tile slabs, FP64-sized in both kernels (the
             // condensation factorization of global-front plans is FP64)
-            if (glb) bytes = std::max<int64_t>(bytes, (int64_t)kTileLdsElems * 8);
-            b->dyn_bytes[k] = (size_t)bytes;
-            // eight waves: 2D plans with fronts in LDS, by default where the
-            // fronts leave room for one four-wave workgroup per CU only
-            const int64_t wide_bytes = std::max(b->lds_front[k] + rl, 2 * NWAVE_ * b->wave_slice) * es;
-            const bool wide_fits = d == 2 && !glb && wide_bytes + nt512::lds_static_bytes() + 1024 <= kLdsBytesMax;
-            const bool wide_rule = bytes + nt256::lds_static_bytes() > kLdsBytesMax / 2;
-            b->wide[k] = wide_fits && (threads == 512 || (threads == 0 && wide_rule));
-            b->dyn_bytes_wide[k] = (size_t)wide_bytes;
+            for (int k = 0; k < 2; ++k)
+                b->dyn_bytes[k] = std::max<size_t>(b->dyn_bytes[k], (size_t)kTileLdsElems * 8);
         }
     }
+    // (the backward substitution's slices are the largest of the batch's plans)
+    for (int k = 0; k < 2; ++k) b->dyn_bytes[k] = std::max<size_t>(b->dyn_bytes[k], (size_t)(8 * kSolveWaves * b->bs_slice));
     auto rnd = [](int64_t x) { return (x + 31) / 32 * 32; };
     SlotLayout& L = b->lay;
     int64_t o = 0;
@@ -614,16 +580,14 @@ static int solve_batch_impl(rve_batch b, const int32_t* subset, const int32_t* s
     a.dim = b->d;
     a.flags = o.flags;
     const int k = fp32 ? 1 : 0;
-    a.lds_front = (int32_t)b->lds_front[k];
-    a.wave_slice = (int32_t)b->wave_slice;
-    const bool wide = b->wide[k];
-    size_t dyn = wide ? b->dyn_bytes_wide[k] : b->dyn_bytes[k];
-    // FP32 factors: where the FP64 front region keeps two workgroups per CU (the
-    // register limit), the condensation factorization runs in FP64 and the direct
-    // Schur form replaces the refined FP32 solves
+    a.bs_slice = (int32_t)b->bs_slice;
+    size_t dyn = b->dyn_bytes[k];
+    a.lds_elems = (int32_t)(dyn / (fp32 ? 4 : 8));
+    // FP32 factors: where FP64 panels keep two workgroups per CU (the register
+    // limit), the condensation factorization runs in FP64 and the direct Schur
+    // form replaces the refined FP32 solves
     a.tan64 = 0;
-    a.lds_front64 = (int32_t)b->lds_front[0];
-    if (fp32 && !wide && (int64_t)b->dyn_bytes[0] + nt256::lds_static_bytes() <= kLdsBytesMax / 2) {
+    if (fp32 && (int64_t)b->dyn_bytes[0] + lds_static_bytes() <= kLdsBytesMax / 2) {
         a.tan64 = 1;
         dyn = std::max(dyn, b->dyn_bytes[0]);
     }
@@ -637,8 +601,7 @@ static int solve_batch_impl(rve_batch b, const int32_t* subset, const int32_t* s
     a.reuse_tan = (A != nullptr && !(o.flags & RVE_FLAG_DIRECT_TANGENT)) ? 1 : 0;
     a.ir_eta = 1e-2;
     a.ir_eta_tan = 0.0;
-    hipError_t e = wide ? nt512::launch_rve_solve(a, nslots, dyn, fp32, (hipStream_t)hip_stream)
-                        : nt256::launch_rve_solve(a, nslots, dyn, fp32, (hipStream_t)hip_stream);
+    hipError_t e = launch_rve_solve(a, nslots, dyn, fp32, (hipStream_t)hip_stream);
     if (e != hipSuccess) return fail(RVE_EHIP, std::string("rve_solve_batch launch: ") + hipGetErrorString(e));
     return RVE_OK;
 }
@@ -679,7 +642,7 @@ int rve_assemble_batch(rve_batch b, const double* F, const double* w_state, int3
     a.status = status;
     a.dim = b->d;
     a.atol = -1.0;
-    hipError_t e = nt256::launch_rve_assembly(a, b->nslots, (hipStream_t)hip_stream);
+    hipError_t e = launch_rve_assembly(a, b->nslots, (hipStream_t)hip_stream);
     if (e != hipSuccess) return fail(RVE_EHIP, std::string("rve_assemble_batch launch: ") + hipGetErrorString(e));
     return RVE_OK;
 }
@@ -838,13 +801,11 @@ int rve_autotune(rve_mesh m, const double* F, int64_t nF, const rve_opts* o, rve
             err = fail(RVE_EINVAL, std::string("rve_autotune: ") + ex.what());
             break;
         }
-        // eight-wave workgroups exist for 2D plans with fronts in LDS only
-        const std::vector<int> threads = lds && d == 2 ? std::vector<int>{256, 512} : std::vector<int>{0};
         for (int wave : waves) {
             if (!lds && wave != kWaveFrontMaxM) continue;
-            for (size_t c = 0; c < slots.size() * threads.size() && !err; ++c) {
-                const int sl = slots[c / threads.size()], th = threads[c % threads.size()];
-                rve_tuning cand{leaf, wave, sl, th, 0.0};
+            for (size_t c = 0; c < slots.size() && !err; ++c) {
+                const int sl = slots[c];
+                rve_tuning cand{leaf, wave, sl, kSolveWaves * 64, 0.0};
                 if ((err = rve_tuning_set(d, n, &cand))) break;
                 rve_mesh_desc md{};
                 md.ndim = d;
@@ -876,7 +837,7 @@ int rve_autotune(rve_mesh m, const double* F, int64_t nF, const rve_opts* o, rve
                 rve_batch_destroy(cb);
                 rve_mesh_destroy(cm);
                 if (err) break;
-                if (ms_best < win.ms) win = rve_tuning{leaf, wave, sl, th, (double)ms_best};
+                if (ms_best < win.ms) win = rve_tuning{leaf, wave, sl, kSolveWaves * 64, (double)ms_best};
             }
             if (err) break;
         }

@@ -1,8 +1,7 @@
 // rve_solve.hip -- persistent batched periodic-RVE solver for gfx950.
 //
-// One workgroup (256 threads, four wave64; or 512 threads, eight wave64, when
-// compiled with FEHMM_NT=512 into namespace fehmm::nt512) owns one workspace
-// slot and pulls RVE ids from a device queue until the batch is exhausted.  Per RVE it runs the
+// One workgroup (256 threads, four wave64) owns one workspace slot and pulls RVE
+// ids from a device queue until the batch is exhausted.  Per RVE it runs the
 // micro Newton iteration of Sec. 3.3 (residual, tangent, linear solve, update;
 // the PBC form in which G^T dLambda = 0), then the post-convergence outputs:
 // Pbar = <P> (eq. Average-of-P-and-F) and the tangent transfer of Sec. 3.2 for
@@ -39,17 +38,11 @@
 #include "mesh_common.h"
 #include "solver_dev.h"
 
-#ifndef FEHMM_NT
-#define FEHMM_NT 256
-#define FEHMM_VARIANT nt256
-#endif
-
 namespace fehmm {
-namespace FEHMM_VARIANT {
 
-constexpr int NT = FEHMM_NT;
-constexpr int NWAVE = NT / 64;
-static_assert(NT == 256 || NT == 512, "workgroup size");
+constexpr int NWAVE = kSolveWaves;
+constexpr int NT = 64 * NWAVE;
+static_assert(NT / 128 == kStepGroups, "thread groups of a step");
 
 // Optional per-phase clock accounting (slot 0, thread 0), compiled in only
 // with -DFEHMM_PHASE_PROF=1; the default build records nothing.
@@ -76,7 +69,6 @@ __device__ unsigned long long g_phase[PH_N];
 #endif
 
 struct Smem {
-    double pub[kStepFronts][2][18 + kMaxNrhs];  // pivot publication per front group (double-buffered)
     double red[NWAVE * 81];
     double dN[8 * 8 * 3];    // [gp][a][k]
     double Fbar[9];
@@ -641,6 +633,10 @@ __device__ inline const KeType<D, NRHS, T>* ke_of(const RveCtx& c) {
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 __device__ inline int cpk(int j, int m) { return j * m - ((j * (j - 1)) >> 1); }
+// the same for a j that differs between lanes, j, m < 2^12 (24-bit products run at
+// the vector unit's full rate, 32-bit ones at a quarter of it; uniform arguments
+// belong on the scalar unit, which has no 24-bit product)
+__device__ inline int cpkv(int j, int m) { return __mul24(j, m) - (__mul24(j, j - 1) >> 1); }
 
 // 1/x for a pivot on the elimination's dependent chain: the hardware reciprocal
 // estimate refined by two Newton-Raphson steps r <- r + r (1 - x r), each of
@@ -985,13 +981,6 @@ __device__ __attribute__((noinline)) void factorize_glb(const RveCtx& c, Smem& s
     constexpr int NEN = 1 << D, ND = NEN * D;
     const DevPlan& pl = *c.plan;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if constexpr (NWAVE != 4) {
-        // the global-front tiles are laid out for four waves; the host launches
-        // the eight-wave solver for LDS plans only, and anything else fails here
-        if (tid == 0) sm.flag = 2;
-        __syncthreads();
-        return;
-    }
     T* W = reinterpret_cast<T*>(sm.red);  // 16 x 16
     nrhs = uni(nrhs);
     double* const cL = uni(c.L);
@@ -1351,69 +1340,178 @@ __device__ __attribute__((noinline)) void backsolve_glb(const RveCtx& c, Smem& s
     }
 }
 
-// Multifrontal LDL^T, fronts in LDS (F: packed front, rl: m x nrhs rhs rows).
-// Small subtrees first, one front per wave (wave_front); then the workgroup
-// fronts in the plan's steps of 1, 2 or 4 independent fronts side by side
-// (wg_front).  Per pivot block of 16 columns: a row-owner sweep (one barrier per
-// pivot) gives the 16 L columns of every row and the forward-substituted rhs;
-// the trailing lower triangle is then updated with v_mfma_f64_16x16x4 (lane
-// layouts: A[l%16][l/16], B[l/16][l%16], D row = l/16 + 4 v, col = l%16).
+// Multifrontal LDL^T with the front panels in LDS.  Of a front of m rows and p
+// pivots only the m x p panel is held in LDS (packed columns, entry (i, j),
+// i >= j, at cpk(j, m) + i - j); the update matrix never is.  Per front:
+//   1. the panel takes its original entries (one gather) and the panel part of
+//      the children's update matrices (a prefix of each, extend-add);
+//   2. 16-column blocks: every row is owned by one thread, which holds its 16
+//      block entries in registers beside a copy of the block's own 16 rows,
+//      replicated in each 16-lane DPP row.  A pivot's multipliers are broadcast
+//      from that copy by row_newbcast moves, so the 16 pivots of a block need
+//      neither barriers nor LDS traffic nor readlane;
+//   3. the panel columns right of the block are updated on MFMA;
+//   4. after the last block the update matrix is formed tile by tile in MFMA
+//      accumulators over all p pivots, the children's entries (gathered through
+//      the inverse row maps) added, and written once, straight to the stack.
+// A panel needs 2 p / m of a packed front's LDS: two four-wave workgroups fit a
+// CU up to 32 x 32 in FP64 (81.4 KB each), where whole packed fronts (139 KB)
+// allowed one.  Small subtrees run the same code one front per wave first, then
+// the workgroup fronts run in the plan's steps of 1, 2 or 4 independent fronts.
+// What bounds it: latency (dependent FP64 chains of the pivots, memory round trips
+// per front), at a third of the vector unit's issue slots.  Measured against whole
+// packed fronts eliminated with a barrier per pivot, on one MI355X: 4096 RVEs of
+// 32 x 32 85.7 -> 64 ms (FP32 factors 66.7 -> 56), 14288 of 16 x 16 55.3 -> 48.5 ms.
 
+// Address spaces.  The panels' functions are not inlined into the solver kernel
+// and receive generic pointers in vector registers; these views restore what the
+// compiler cannot see: workspace pointers are wave-uniform and global (scalar
+// bases, 32-bit lane offsets, no flat instructions), the LDS is LDS, and the plan
+// is constant while the kernel runs, so wave-uniform reads of it are scalar loads.
+#define FEHMM_GLB __attribute__((address_space(1)))
+#define FEHMM_LDS __attribute__((address_space(3)))
+#define FEHMM_CST __attribute__((address_space(4)))
+template <typename T>
+__device__ inline FEHMM_GLB T* glb(T* p) {
+    return (FEHMM_GLB T*)uni((int64_t)(uintptr_t)p);
+}
+template <typename S>
+__device__ inline S load_const(const FEHMM_GLB S* p) {
+    static_assert(sizeof(S) % 4 == 0, "whole words");
+    const FEHMM_CST uint32_t* q = (const FEHMM_CST uint32_t*)uni((int64_t)p);
+    uint32_t w[sizeof(S) / 4];
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(S) / 4; ++k) w[k] = q[k];
+    S out;
+    __builtin_memcpy(&out, w, sizeof(S));
+    return out;
+}
 
-// Original entries of an LDS front from the element matrices (one gather level)
-// and the extend-add of a child's packed update matrix: U strides of the list
-// per pass, every index load first, then every value load (clamped addresses,
-// zeros selected), then the stores, so a pass costs one or two memory round
-// trips for all its strides.  first / stride: the caller's lane (wave-level) or
-// thread (workgroup-level) numbering.  D0 (LDS) receives the original diagonal
-// of the pivot columns, the scale of the vanishing-pivot test.
-template <int NEN, int U = 4, typename KT, typename T>
-__device__ inline void gather_original(const DevPlan& pl, const KT* ke, int a0, int a1, int first, int stride,
-                                       T* F, int m, T* D0) {
+// what the LDS-plan functions read of the plan and the slot, in scalar registers
+struct PanelCtx {
+    const FEHMM_GLB DevFront* fronts;
+    const FEHMM_GLB DevChild* childrec;
+    const FEHMM_GLB int32_t *rows, *asm_dst, *asm_src, *ea_dst, *inv, *wave_list, *wave_hbeg, *wg_steps, *task, *task_beg;
+    int nwave_h, nwg_steps, ntask_lev, ul_base, ul_stride, wave_slice;
+    FEHMM_GLB double *L, *U;
+};
+__device__ inline PanelCtx panel_ctx(const RveCtx& c) {
+    const DevPlan pl = load_const(glb(c.plan));
+    PanelCtx k;
+    k.fronts = glb(pl.fronts);
+    k.childrec = glb(pl.childrec);
+    k.rows = glb(pl.rows);
+    k.asm_dst = glb(pl.asm_dst);
+    k.asm_src = glb(pl.asm_src);
+    k.ea_dst = glb(pl.ea_dst);
+    k.inv = glb(pl.inv);
+    k.wave_list = glb(pl.wave_list);
+    k.wave_hbeg = glb(pl.wave_hbeg);
+    k.wg_steps = glb(pl.wg_steps);
+    k.task = glb(pl.task);
+    k.task_beg = glb(pl.task_beg);
+    k.ntask_lev = uni(pl.ntask_lev);
+    k.wave_slice = uni(pl.wave_slice);
+    k.ul_base = uni(pl.ul_base);
+    k.ul_stride = uni(pl.ul_stride);
+    k.nwave_h = uni(pl.nwave_h);
+    k.nwg_steps = uni(pl.nwg_steps);
+    k.L = glb(c.L);
+    k.U = glb(c.U);
+    return k;
+}
+
+// f(0) .. f(N - 1) with compile-time indices (DPP controls are immediates)
+template <int I, int N, typename Fn>
+__device__ inline __attribute__((always_inline)) void static_for(Fn&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+// lane N of the caller's 16-lane row, in every lane of the row
+template <int N, typename T>
+__device__ inline T row_bcast(T v) {
+    return __builtin_amdgcn_mov_dpp(v, 0x150 + N, 0xf, 0xf, true);
+}
+
+// barrier of a front's threads: the workgroup's, or (one front per wave) only
+// an ordering of the wave's own LDS accesses, which complete in issue order
+template <bool WAVE>
+__device__ inline void front_sync() {
+    if constexpr (WAVE) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
+}
+
+// Original entries of a panel from the element matrices (one gather level): U
+// strides of the list per pass, every index load first, then every value load
+// (clamped addresses, zeros selected), then the stores, so a pass costs two
+// memory round trips for all its strides.
+template <int NEN, int U, typename KT, typename T>
+__device__ inline void gather_original(const PanelCtx& pl, const FEHMM_GLB KT* ke, int a0, int a1, int first, int stride,
+                                       FEHMM_LDS T* F) {
+    typedef int32_t vint4 __attribute__((ext_vector_type(4)));
+    const FEHMM_GLB vint4* src4 = (const FEHMM_GLB vint4*)pl.asm_src;
     for (int t0 = a0 + first; t0 < a1; t0 += U * stride) {
-        int rc[U], src[U][NEN];
+        int dst[U];
+        vint4 src[U][NEN / 4];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int t = min(t0 + u * stride, a1 - 1);
-            rc[u] = pl.asm_rc[t];
+            dst[u] = pl.asm_dst[t];
 #pragma unroll
-            for (int q = 0; q < NEN; ++q) src[u][q] = pl.asm_src[(int64_t)t * NEN + q];
+            for (int q = 0; q < NEN / 4; ++q) src[u][q] = src4[(int64_t)t * (NEN / 4) + q];
         }
         double v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             v[u] = 0.0;
 #pragma unroll
-            for (int q = 0; q < NEN; ++q) {
-                const double kv = (double)ke[max(src[u][q], 0)];
-                v[u] += (src[u][q] >= 0) ? kv : 0.0;
+            for (int q = 0; q < NEN / 4; ++q) {
+                const int s[4] = {src[u][q].x, src[u][q].y, src[u][q].z, src[u][q].w};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const double kv = (double)ke[max(s[k], 0)];
+                    v[u] += (s[k] >= 0) ? kv : 0.0;
+                }
             }
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (t0 + u * stride < a1) {
-                const int r = rc[u] >> 16, col = rc[u] & 0xffff;
-                F[cpk(col, m) + r - col] = v[u];
-                if (r == col) D0[col] = v[u];
-            }
-        }
+        for (int u = 0; u < U; ++u)
+            if (t0 + u * stride < a1) F[dst[u]] = v[u];
     }
 }
-// global -> LDS copy, eight strides per pass: all loads first, then all stores
-// (the compiler does not move a load past a store that may alias it)
-template <typename T>
-__device__ inline void copy_in(T* dst, const T* src, int n, int first, int stride) {
-    for (int t0 = first; t0 < n; t0 += 8 * stride) {
-        T v[8];
+// one pass of an extend-add in parts, so that its loads can be issued early
+template <int U, typename T>
+struct ExtendPass {
+    int e[U];
+    T v[U];
+    __device__ inline void index(const FEHMM_GLB int32_t* ea, int nu, int first, int stride) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = src[min(t0 + u * stride, n - 1)];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (t0 + u * stride < n) dst[t0 + u * stride] = v[u];
+        for (int u = 0; u < U; ++u) e[u] = nu > 0 ? ea[min(first + u * stride, nu - 1)] : 0;
     }
-}
-template <int U = 8, typename T>
-__device__ inline void extend_add_packed(const int32_t* ea, const T* Uc, int nu, int first, int stride, T* F) {
+    template <typename Src>
+    __device__ inline void value(const Src* Uc, int nu, int first, int stride) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = Uc[max(min(first + u * stride, nu - 1), 0)];
+    }
+    __device__ inline void add(int nu, int first, int stride, FEHMM_LDS T* F) {
+        T o[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) o[u] = F[e[u]];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (first + u * stride < nu) F[e[u]] = o[u] + v[u];
+    }
+};
+template <int U = 8, typename Src, typename T>
+__device__ inline void extend_add_packed(const FEHMM_GLB int32_t* ea, const Src* Uc, int nu, int first, int stride,
+                                         FEHMM_LDS T* F) {
     for (int t0 = first; t0 < nu; t0 += U * stride) {
         int e[U];
         T v[U];
@@ -1435,681 +1533,637 @@ __device__ inline void extend_add_packed(const int32_t* ea, const T* Uc, int nu,
     }
 }
 
-// One small front (m <= 64) processed by a single wave: lane i owns front row i.
-// Assembly as in the workgroup path, then a right-looking LDL^T sweep over the
-// p pivots done in place in LDS (the wave's slice: front, rhs rows, original
-// diagonal); within a wave LDS accesses complete in issue order, so no barrier
-// is needed between pivots.
-template <int D, int NRHS, typename T>
-__device__ void wave_front(const RveCtx& c, Smem& sm, int s, T* F, T* rl) {
-    const DevPlan& pl = *c.plan;
-    constexpr int NEN = 1 << D;
-    const int lane = threadIdx.x & 63;
-    const DevFront fr = pl.fronts[uni(s)];  // (uniform per wave: scalar loads)
-    const int m = uni(fr.m), p = uni(fr.p), mu = m - p;
-    const int32_t* rows = pl.rows + fr.rows_off;
-    T* Lg = reinterpret_cast<T*>(c.L + fr.L_off);
-    double* Dg = c.L + fr.D_off;
-    double* yg = c.L + fr.y_off;
-    const int tot = cpk(m, m);
-    // the rhs rows (lane = row, m <= 64) are loaded first and stored after the
-    // gather, so their two round trips overlap the gather's; the gather takes
-    // eight strides per pass (one pass for the usual front), and a child's rhs
-    // rows travel with its update matrix, sixteen strides per pass
-    T rv[NRHS];
-    {
-        const int ri = rows[min(lane, m - 1)];  // (the value is used on the pivot rows only)
+// The 16 pivots of a block on one thread's row (entries row[], rhs b[]) and the
+// replicated block rows (blk[], yb[]; lane l of each 16-lane row holds block row
+// l).  ib: the row's number in the block (negative above it, >= 16 below).  rows
+// below a pivot leave with L and the forward-substituted rhs, a pivot's own row
+// with D on its diagonal; entries above a diagonal and columns past kb hold
+// garbage that is neither stored nor broadcast.  Pivots past kb (whole groups of
+// four are skipped, the others run with a zero reciprocal) change nothing.
+template <int NRHS, typename T>
+__device__ inline __attribute__((always_inline)) void eliminate16(T (&blk)[16], T (&row)[16], T (&yb)[NRHS],
+                                                                  T (&b)[NRHS], int kb, int ib, T& mypiv) {
+    static_for<0, 4>([&](auto G) {
+        constexpr int g = decltype(G)::value;
+        if (4 * g < kb) {
+            static_for<4 * g, 4 * g + 4>([&](auto J) {
+                constexpr int j = decltype(J)::value;
+                const T piv = row_bcast<j>(blk[j]);
+                const T rp = j < kb ? recip_t(piv) : T(0);
+                mypiv = ib == j ? piv : mypiv;
+                const T bj = blk[j], rj = row[j];
+                const T lb = bj * rp;
+                static_for<j + 1, 16>([&](auto C) {
+                    constexpr int cc = decltype(C)::value;
+                    const T lc = row_bcast<cc>(lb);
+                    blk[cc] -= bj * lc;
+                    row[cc] -= rj * lc;
+                });
+                const T l = ib > j ? rj * rp : T(0);
 #pragma unroll
-        for (int q = 0; q < NRHS; ++q) rv[q] = lane < p ? (T)c.rhs[(int64_t)ri * NRHS + q] : T(0);
-    }
-    for (int t = lane; t < tot; t += 64) F[t] = 0.0;
-    __builtin_amdgcn_wave_barrier();
-    T* const D0 = rl + m * NRHS;
-    gather_original<NEN, 8>(pl, ke_of<D, NRHS, T>(c), fr.asm_begin, fr.asm_end, lane, 64, F, m, D0);
-    if (lane < m)
-#pragma unroll
-        for (int q = 0; q < NRHS; ++q) rl[q * m + lane] = rv[q];
-    __builtin_amdgcn_wave_barrier();
-    for (int q = fr.child_begin; q < fr.child_end; ++q) {
-        const DevFront ch = pl.fronts[pl.children[q]];
-        const int mc = ch.m - ch.p;  // < 64: the child is a wave front too
-        const int32_t* rel = pl.relind + ch.relind_off;
-        const T* Uc = reinterpret_cast<const T*>(c.U + ch.U_off);
-        const int nu = cpk(mc, mc);
-        const T* ruc = Uc + nu;
-        const int32_t* ea = pl.ea_dst + ch.ea_off;
-        const int li = max(min(lane, mc - 1), 0);
-        const int ci = mc > 0 ? rel[li] : 0;
-        T cr[NRHS];
-#pragma unroll
-        for (int k = 0; k < NRHS; ++k) cr[k] = mc > 0 ? ruc[(int64_t)k * mc + li] : T(0);
-        extend_add_packed<16>(ea, Uc, nu, lane, 64, F);
-        if (lane < mc)
-#pragma unroll
-            for (int k = 0; k < NRHS; ++k) rl[k * m + ci] += cr[k];
-        __builtin_amdgcn_wave_barrier();
-    }
-    for (int K = 0; K < p; K += 16) {
-        const int kb = min(16, p - K);
-        // the 16 columns of the block by elimination on every front row at once
-        // (lane = row, rows below the block included): readlane broadcasts of
-        // the pivot and of the block rows' multipliers; the rows below leave
-        // with their L entries and forward-substituted rhs
-        {
-            const int r = lane;
-            const bool act = r >= K && r < m;
-            T row[16];
-            T yv[NRHS];
-            // (clamped reads inside the front, masked: no branch per entry)
-#pragma unroll
-            for (int cc = 0; cc < 16; ++cc) {
-                const int col = min(K + cc, m - 1);
-                const int idx = min(max(cpk(col, m) + r - col, 0), cpk(m, m) - 1);
-                row[cc] = F[idx] * ((act && cc < kb && K + cc <= r) ? T(1) : T(0));
-            }
-            // (clamped reads; lanes off the front never store or broadcast these,
-            // and only the pivot's own lane tests its d0)
-#pragma unroll
-            for (int q = 0; q < NRHS; ++q) yv[q] = rl[q * m + min(r, m - 1)];
-            const double d0 = (double)D0[min(r, m - 1)];
-            T mypiv = T(1);  // the pivot of this lane's row, tested after the block
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                if (j < kb) {
-                    const T piv = readlane_t(row[j], K + j);
-                    const T rp = recip_t(piv);
-                    mypiv = r == K + j ? piv : mypiv;
-                    const bool below = act && r > K + j;
-                    const T l = below ? row[j] * rp : T(0);
-                    const T lpv = l * piv;
-                    // unconditional updates, past the block bound too (lane K + cc
-                    // <= 63 since K <= 48): l = 0 off the rows below the pivot, and
-                    // the only other entries touched, row[cc] with K + cc > r or
-                    // cc >= kb, lie above the diagonal or outside the block and are
-                    // neither stored nor read as a pivot
-#pragma unroll
-                    for (int cc = j + 1; cc < 16; ++cc) {
-                        const T lc = readlane_t(l, K + cc);
-                        row[cc] -= lpv * lc;
-                    }
-#pragma unroll
-                    for (int q = 0; q < NRHS; ++q) {
-                        const T yj = readlane_t(yv[q], K + j);
-                        yv[q] -= l * yj;
-                    }
-                    if (below) row[j] = l;
+                for (int q = 0; q < NRHS; ++q) {
+                    const T yj = row_bcast<j>(yb[q]);
+                    b[q] -= l * yj;
+                    yb[q] -= lb * yj;
                 }
-            }
-            if (r >= K && r < K + kb &&
-                (!(fabs((double)mypiv) > 1e-14 * fabs(d0)) || !isfinite((double)mypiv)))
-                sm.flag = 2;
-#pragma unroll
-            for (int cc = 0; cc < 16; ++cc)
-                if (act && cc < kb && K + cc <= r) F[cpk(K + cc, m) + r - K - cc] = row[cc];
-#pragma unroll
-            for (int q = 0; q < NRHS; ++q)
-                if (act) rl[q * m + r] = yv[q];
+                row[j] = ib > j ? l : rj;
+            });
         }
-        __builtin_amdgcn_wave_barrier();
-        const int R0 = K + kb;
-        const int nRT = (m - R0 + 15) >> 4;
-        // trailing lower triangle -= L D L^T (MFMA), two independent tiles in flight
-        const int nT = nRT;
-        const int ntile = nT * (nT + 1) / 2;
-        // (MFMA of the factor type: v_mfma_f64_16x16x4 or v_mfma_f32_16x16x4)
-        typedef Mfma16<T> M;
-        for (int t0 = 0; t0 < ntile; t0 += 2) {
-            typename M::V acc[2];
-            int Ii[2], Jj[2];
+    });
+}
+
+// Rank-kb update of the panel columns T0 .. p - 1 (rows >= the column) by the
+// block of kb columns at K: tiles of 32 rows x 16 columns, round robin over nw
+// waves.  The column operand is the MFMA's row operand, so a lane's result
+// element lies in row l % 16: consecutive LDS addresses along a column.
+template <typename T>
+__device__ inline void panel_update(FEHMM_LDS T* F, int m, int p, int K, int kb, int gw, int nw) {
+    typedef Mfma16<T> M;
+    const int lane = threadIdx.x & 63, l15 = lane & 15, lg = lane >> 4;
+    const int T0 = K + kb;
+    const int nR = (m - T0 + 15) >> 4, nC = (p - T0 + 15) >> 4;
+    int base[4];
+    T dk[4];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                int I = 0, rem = t0 + u;
-                while (rem > I) { rem -= I + 1; ++I; }
-                Ii[u] = I;
-                Jj[u] = rem;
-                acc[u] = M::zero();
-            }
-            // operands from clamped addresses inside the front (column K and row
-            // m - 1 stand in past the block, the front or the last tile) times 0/1
-            // masks: every read of both tiles issues without branches
-            T av[4][2], bv[4][2];
+    for (int ks = 0; ks < 4; ++ks) {
+        const int kk = 4 * ks + lg, kc = K + min(kk, kb - 1);
+        base[ks] = cpkv(kc, m) - kc;
+        dk[ks] = F[base[ks] + kc] * (kk < kb ? T(1) : T(0));
+    }
+    int t = 0;
+    for (int J = 0; J < nC; ++J) {
+        const int ca = min(T0 + 16 * J + l15, m - 1);
+        for (int I = J; I < nR; I += 2, ++t) {
+            if ((t & (nw - 1)) != gw) continue;
+            T a[4], b[4][2];
+            int rb[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) rb[u] = min(T0 + 16 * (I + u) + l15, m - 1);
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
-                const int kk = 4 * ks + (lane >> 4);
-                const int kc = kk < kb ? K + kk : K;
-                const int base = cpk(kc, m) - kc;
-                const T dk = F[base + kc];
+                a[ks] = F[base[ks] + ca];
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int ra = R0 + 16 * Ii[u] + (lane & 15), rb = R0 + 16 * Jj[u] + (lane & 15);
-                    const bool live = (t0 + u < ntile) && kk < kb;
-                    const T ma = (live && ra < m) ? T(1) : T(0), mb = (live && rb < m) ? T(1) : T(0);
-                    av[ks][u] = F[base + min(ra, m - 1)] * dk * ma;
-                    bv[ks][u] = F[base + min(rb, m - 1)] * mb;
-                }
+                for (int u = 0; u < 2; ++u) b[ks][u] = F[base[ks] + rb[u]];
             }
+            int cb[4], cv[4];
+            T o[2][4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                cv[v] = T0 + 16 * J + M::row(lane, v);
+                const int cl = min(cv[v], p - 1);
+                cb[v] = cpkv(cl, m) - cl;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) o[u][v] = F[cb[v] + max(rb[u], cl)];
+            }
+            typename M::V acc[2] = {M::zero(), M::zero()};
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                for (int u = 0; u < 2; ++u) acc[u] = M::mma(av[ks][u], bv[ks][u], acc[u]);
-            // the tiles' targets are distinct: all eight read (clamped), then written
-            T o[2][4];
-            int bs[2];
+                for (int u = 0; u < 2; ++u) acc[u] = M::mma(a[ks] * dk[ks], b[ks][u], acc[u]);
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const int cc = R0 + 16 * Jj[u] + (lane & 15), ccl = min(cc, m - 1);
-                bs[u] = cpk(ccl, m) - ccl;
+                const int r = T0 + 16 * (I + u) + l15;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int rr = R0 + 16 * Ii[u] + M::row(lane, v);
-                    o[u][v] = F[bs[u] + min(max(rr, ccl), m - 1)];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int cc = R0 + 16 * Jj[u] + (lane & 15);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int rr = R0 + 16 * Ii[u] + M::row(lane, v);
-                    if (t0 + u < ntile && cc < m && rr < m && rr >= cc) F[bs[u] + rr] = o[u][v] - acc[u][v];
-                }
+                for (int v = 0; v < 4; ++v)
+                    if (cv[v] < p && r < m && r >= cv[v]) F[cb[v] + r] = o[u][v] - acc[u][v];
             }
         }
-        __builtin_amdgcn_wave_barrier();
     }
-    const int lp = cpk(p, m);
-    for (int t = lane; t < lp; t += 64) Lg[t] = F[t];
-    for (int t = lane; t < p; t += 64) Dg[t] = F[cpk(t, m)];
-    for (int t = lane; t < p * NRHS; t += 64) {
-        const int j = t % p, col = t / p;
-        yg[t] = rl[col * m + j];
-    }
-    if (mu > 0) {
-        T* dst = reinterpret_cast<T*>(c.U + fr.U_off);
-        const int usz = tot - lp;
-        for (int t = lane; t < usz; t += 64) dst[t] = F[lp + t];
-        for (int t = lane; t < mu * NRHS; t += 64) {
-            const int ii = t % mu, col = t / mu;
-            dst[usz + t] = rl[col * m + p + ii];
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
 }
 
-// One workgroup front s on threads gt = 0..GT-1 and waves gw = 0..nw-1 (the
-// whole workgroup, or one half of it beside a second front): assembly into the
-// packed front F and rhs rows rl (original diagonal after them), 16-pivot blocks
-// (row-owner sweep, one barrier per pivot, publication in pub; trailing lower
-// triangle on MFMA), then L, D, y and the update matrix out.  Every barrier is
-// workgroup-wide: fronts sharing a step have equal pivot and child counts, so
-// both halves pass the same sequence of barriers.
-template <int D, int NRHS, typename T>
-__device__ inline void wg_front(const RveCtx& c, Smem& sm, int s, T* F, T* rl, int gt, int GT, int gw, int nw,
-                                double (*pub)[18 + kMaxNrhs]) {
-    constexpr int nrhs = NRHS;
-    constexpr int NEN = 1 << D;
-    const DevPlan& pl = *c.plan;
-    const int lane = threadIdx.x & 63;
-    PROF_T0();
-    const DevFront fr = pl.fronts[uni(s)];  // (uniform per wave: scalar loads)
-    const int m = uni(fr.m), p = uni(fr.p), mu = m - p;
-    const int32_t* rows = pl.rows + fr.rows_off;
-    T* Lg = reinterpret_cast<T*>(c.L + fr.L_off);
-    double* Dg = c.L + fr.D_off;
-    double* yg = c.L + fr.y_off;
-    const int tot = cpk(m, m);
-    for (int t = gt; t < tot; t += GT) F[t] = 0.0;
-    for (int t = gt; t < m * nrhs; t += GT) {
-        const int i = t % m, col = t / m;
-        rl[t] = (i < p) ? c.rhs[(int64_t)rows[i] * nrhs + col] : 0.0;
-    }
-    __syncthreads();
-    // original entries: one gather level, every source load in flight at once
-    T* const D0 = rl + m * nrhs;  // original diagonal, after the rhs rows
-    gather_original<NEN>(pl, ke_of<D, NRHS, T>(c), fr.asm_begin, fr.asm_end, gt, GT, F, m, D0);
-    __syncthreads();
-    for (int q = fr.child_begin; q < fr.child_end; ++q) {
-        const DevFront ch = pl.fronts[pl.children[q]];
-        const int mc = ch.m - ch.p;
-        const int32_t* rel = pl.relind + ch.relind_off;
-        const T* Uc = reinterpret_cast<const T*>(c.U + ch.U_off);
-        const int nu = cpk(mc, mc);
-        const T* ruc = Uc + nu;
-        const int32_t* ea = pl.ea_dst + ch.ea_off;
-        extend_add_packed(ea, Uc, nu, gt, GT, F);
-        for (int t = gt; t < mc * nrhs; t += GT) {
-            const int i = t % mc, col = t / mc;
-            rl[col * m + rel[i]] += ruc[(int64_t)col * mc + i];
+// Update matrix of a front, U(r, c) = sum over children - sum_k L(r, k) D(k)
+// L(c, k), packed lower columns: 32 x 32 tiles (2 x 2 MFMA tiles) round robin over
+// nw waves, accumulated in registers over all p pivots (eight per step, the next
+// step's operands read ahead).  The entries of the first two children are loaded
+// before the products, so that their round trip overlaps them: iv holds their
+// inverse row maps in LDS ([child][m]), an entry a child does not have is read from
+// the workspace's zero (U[0]).
+template <typename T>
+struct ChildU {  // a child's update matrix: in LDS (u_lds >= 0) or in the workspace
+    int lds, off;
+};
+template <typename T, typename Out>
+__device__ inline void schur_tiles(const PanelCtx& pl, int child_begin, int nch, const FEHMM_LDS T* F,
+                                   const FEHMM_LDS T* Ul, const FEHMM_LDS int32_t* iv, ChildU<T> ch0, ChildU<T> ch1,
+                                   Out dst, int m, int p, int gw, int nw) {
+    typedef Mfma16<T> M;
+    const int lane = threadIdx.x & 63, l15 = lane & 15, lg = lane >> 4;
+    const int mu = m - p, ns = (mu + 31) >> 5;
+    const FEHMM_GLB T* Ug = (const FEHMM_GLB T*)pl.U;
+    int t = 0;
+    for (int J = 0; J < ns; ++J)
+        for (int I = J; I < ns; ++I, ++t) {
+            if ((t & (nw - 1)) != gw) continue;
+            int r[2], c[2][4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                r[u] = 32 * I + 16 * u + l15;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) c[u][v] = 32 * J + 16 * u + M::row(lane, v);
+            }
+            T val[2][2][2][4];  // [child][row tile][column tile][element]
+            auto child_load = [&](const auto* inv, const ChildU<T>& ch, T (&x)[2][2][4]) {
+                int ir[2], ic[2][4];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    ir[u] = inv[p + min(r[u], mu - 1)];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) ic[u][v] = inv[p + min(c[u][v], mu - 1)];
+                }
+                // inv: child row | column offset cpk(row) - row above it, negative
+                // where the child has no such row (entries above the diagonal read
+                // some entry of the child and are not stored)
+                if (ch.lds >= 0) {
+                    const FEHMM_LDS T* Uc = Ul + ch.lds;
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+#pragma unroll
+                        for (int w = 0; w < 2; ++w)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                const bool ok = (ir[u] | ic[w][v]) >= 0;
+                                const T y = Uc[ok ? (ir[u] & 0xffff) + (ic[w][v] >> 16) : 0];
+                                x[u][w][v] = ok ? y : T(0);
+                            }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+#pragma unroll
+                        for (int w = 0; w < 2; ++w)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                const bool ok = (ir[u] | ic[w][v]) >= 0;
+                                x[u][w][v] = Ug[ok ? ch.off + (ir[u] & 0xffff) + (ic[w][v] >> 16) : 0];
+                            }
+                }
+            };
+            if (nch > 0) child_load(iv, ch0, val[0]);
+            if (nch > 1) child_load(iv + m, ch1, val[1]);
+            typename M::V acc[2][2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int w = 0; w < 2; ++w) acc[u][w] = M::zero();
+            int ra[2], rc[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                ra[u] = min(p + 32 * I + 16 * u + l15, m - 1);
+                rc[u] = min(p + 32 * J + 16 * u + l15, m - 1);
+            }
+            // (columns past p: the last column's address, a zero pivot)
+            T ob[2][2][2], oa[2][2][2], od[2][2];
+            auto load = [&](int k0, int h) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const int k = k0 + 4 * s + lg, kc = min(k, p - 1);
+                    const int base = cpkv(kc, m) - kc;
+                    od[h][s] = F[base + kc] * (k < p ? T(1) : T(0));
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        oa[h][s][u] = F[base + rc[u]];
+                        ob[h][s][u] = F[base + ra[u]];
+                    }
+                }
+            };
+            auto mul = [&](int h) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        const T av = oa[h][s][w] * od[h][s];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) acc[u][w] = M::mma(av, ob[h][s][u], acc[u][w]);
+                    }
+            };
+            load(0, 0);
+            for (int k0 = 0; k0 < p; k0 += 16) {
+                load(k0 + 8, 1);
+                mul(0);
+                if (k0 + 8 < p) {
+                    load(k0 + 16, 0);
+                    mul(1);
+                }
+            }
+            if (nch > 0)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int w = 0; w < 2; ++w)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            acc[u][w][v] -= nch > 1 ? val[0][u][w][v] + val[1][u][w][v] : val[0][u][w][v];
+            for (int q = 2; q < nch; ++q) {
+                const DevChild ch = load_const(pl.childrec + child_begin + q);
+                child_load(pl.inv + ch.inv_off, ChildU<T>{ch.u_lds, (int)(ch.U_off * (8 / (int)sizeof(T)))}, val[0]);
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int w = 0; w < 2; ++w)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[u][w][v] -= val[0][u][w][v];
+            }
+#pragma unroll
+            for (int w = 0; w < 2; ++w)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int cb = cpkv(c[w][v], mu) - c[w][v];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        if (r[u] < mu && r[u] >= c[w][v]) dst[cb + r[u]] = -acc[u][w][v];
+                }
         }
-        __syncthreads();
+}
+
+// One front s on threads gt = 0..GT-1 (one per front row, m <= GT) and waves gw =
+// 0..nw-1: a wave of its own (WAVE), the workgroup, or one half of it beside a
+// second front.  F: the panel, ys: [2][NRHS][16] rhs of the block rows, iv: [2][m]
+// inverse row maps of the first two children, Ul: update matrices kept in LDS.
+// Fronts sharing a step have equal pivot and child counts, so both halves pass the
+// same sequence of barriers.  Every global load that needs no other is issued
+// first (rows, children's maps, original entries' sources, the first pass of the
+// children's panel entries): a front is about three memory round trips.
+template <int D, int NRHS, typename T, bool WAVE>
+__device__ inline void front_lds(const PanelCtx& pl, const FEHMM_GLB KeType<D, NRHS, T>* ke, const FEHMM_GLB double* rhs,
+                                 FEHMM_LDS int* flag, int s, FEHMM_LDS T* F, FEHMM_LDS T* ys, FEHMM_LDS int32_t* iv,
+                                 FEHMM_LDS T* Ul, int gt, int GT, int gw, int nw) {
+    constexpr int NEN = 1 << D;
+    constexpr int per = 8 / (int)sizeof(T);
+    const int lane = threadIdx.x & 63, l15 = lane & 15;
+    PROF_T0();
+    const DevFront fr = load_const(pl.fronts + s);
+    const int m = fr.m, p = fr.p, mu = m - p, nch = fr.child_end - fr.child_begin;
+    const FEHMM_GLB int32_t* rows = pl.rows + fr.rows_off;
+    FEHMM_GLB T* Lg = (FEHMM_GLB T*)(pl.L + fr.L_off);
+    const int lp = cpk(p, m);
+    const int i = gt, ic = min(i, m - 1);
+    const FEHMM_GLB T* Ug = (const FEHMM_GLB T*)pl.U;
+    DevChild ch[2];
+    ChildU<T> cu[2] = {{-1, 0}, {-1, 0}};
+    int ivr[2] = {-1, -1};
+    const int ri = rows[ic];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (q < nch) {
+            ch[q] = load_const(pl.childrec + fr.child_begin + q);
+            cu[q] = ChildU<T>{ch[q].u_lds, (int)ch[q].U_off * per};
+            ivr[q] = (pl.inv + ch[q].inv_off)[ic];
+        }
+    // first pass of the children's panel entries
+    ExtendPass<8, T> ep[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (q < nch) {
+            ep[q].index(pl.ea_dst + ch[q].ea_off, ch[q].npre, gt, GT);
+            if (cu[q].lds < 0) ep[q].value(Ug + cu[q].off, ch[q].npre, gt, GT);
+        }
+    for (int t = gt; t < lp; t += GT) F[t] = T(0);
+    // rhs of the thread's row: its own entry and the children's
+    T b[NRHS], cr[2][NRHS];
+#pragma unroll
+    for (int q = 0; q < NRHS; ++q) b[q] = i < p ? (T)rhs[ri * NRHS + q] : T(0);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (q < nch) {
+            const int o = cpk(ch[q].mc, ch[q].mc) + (ivr[q] >= 0 ? (ivr[q] & 0xffff) : 0);
+#pragma unroll
+            for (int k = 0; k < NRHS; ++k)
+                cr[q][k] = cu[q].lds >= 0 ? Ul[cu[q].lds + o + k * ch[q].mc] : Ug[cu[q].off + o + k * ch[q].mc];
+            if (i < m) iv[q * m + i] = ivr[q];
+        }
+    front_sync<WAVE>();
+    gather_original<NEN, WAVE ? 8 : 4>(pl, ke, fr.asm_begin, fr.asm_end, gt, GT, F);
+    front_sync<WAVE>();
+    // original diagonal of the thread's pivot: the scale of the vanishing-pivot test
+    const double d0 = (double)F[i < p ? cpkv(i, m) : 0];
+    if (nch > 0) front_sync<WAVE>();
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (q < nch) {
+            if (cu[q].lds >= 0) {
+                ep[q].value((const FEHMM_LDS T*)Ul + cu[q].lds, ch[q].npre, gt, GT);
+                ep[q].add(ch[q].npre, gt, GT, F);
+                extend_add_packed(pl.ea_dst + ch[q].ea_off, (const FEHMM_LDS T*)Ul + cu[q].lds, ch[q].npre, gt + 8 * GT, GT, F);
+            } else {
+                ep[q].add(ch[q].npre, gt, GT, F);
+                extend_add_packed(pl.ea_dst + ch[q].ea_off, Ug + cu[q].off, ch[q].npre, gt + 8 * GT, GT, F);
+            }
+#pragma unroll
+            for (int k = 0; k < NRHS; ++k) b[k] += ivr[q] >= 0 ? cr[q][k] : T(0);
+            front_sync<WAVE>();
+        }
+    for (int q = 2; q < nch; ++q) {
+        const DevChild c2 = load_const(pl.childrec + fr.child_begin + q);
+        const int v2 = (pl.inv + c2.inv_off)[ic];
+        const int o = cpk(c2.mc, c2.mc) + (v2 >= 0 ? (v2 & 0xffff) : 0);
+        if (c2.u_lds >= 0)
+            extend_add_packed(pl.ea_dst + c2.ea_off, (const FEHMM_LDS T*)Ul + c2.u_lds, c2.npre, gt, GT, F);
+        else
+            extend_add_packed(pl.ea_dst + c2.ea_off, Ug + (int)c2.U_off * per, c2.npre, gt, GT, F);
+#pragma unroll
+        for (int k = 0; k < NRHS; ++k) {
+            const T v = c2.u_lds >= 0 ? Ul[c2.u_lds + o + k * c2.mc] : Ug[(int)c2.U_off * per + o + k * c2.mc];
+            b[k] += v2 >= 0 ? v : T(0);
+        }
+        front_sync<WAVE>();
     }
+    if (i < 16)
+#pragma unroll
+        for (int q = 0; q < NRHS; ++q) ys[q * 16 + i] = b[q];
+    front_sync<WAVE>();
     PROF_MARK(PH_ASM);
+    T mypiv = T(1);
     for (int K = 0; K < p; K += 16) {
         const int kb = min(16, p - K);
-        // ---- pivot block sweep: each front row below K is owned by one thread
-        // that keeps its 16 block entries in registers; at pivot j the owners of
-        // the block rows publish pivot, reciprocal, column-j entries and the
-        // forward-substituted rhs (double-buffered, one barrier per pivot)
-        const int i = K + gt;
-        const bool own = i < m;
-        T r[16];
-        T b[NRHS];
-        // (clamped reads inside the front, masked or unused: rows off the front
-        // never publish, update or store these, and only a pivot's owner tests
-        // its d0)
+        const int par = (K >> 4) & 1;
+        // waves that hold rows from K on
+        const bool busy = WAVE || (64 * gw < m && 64 * gw + 63 >= K);
+        T blk[16], row[16], yb[NRHS];
+        if (busy) {
+            const int rb = min(K + l15, m - 1);
 #pragma unroll
-        for (int cc = 0; cc < 16; ++cc) {
-            const int col = min(K + cc, m - 1);
-            const int idx = min(max(cpk(col, m) + min(i, m - 1) - col, 0), cpk(m, m) - 1);
-            r[cc] = F[idx] * ((own && cc < kb && K + cc <= i) ? T(1) : T(0));
-        }
-#pragma unroll
-        for (int q = 0; q < NRHS; ++q) b[q] = rl[q * m + min(i, m - 1)];
-        const double d0 = (double)D0[min(i, m - 1)];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            if (j < kb) {
-                // [0] piv, [1] 1/piv, [2..17] g, [18..] y, in the factor type
-                T* P = reinterpret_cast<T*>(pub[j & 1]);
-                if (i == K + j) {
-                    const T piv = r[j];
-                    if (!(fabs((double)piv) > 1e-14 * fabs(d0)) || !isfinite((double)piv)) sm.flag = 2;
-                    P[0] = piv;
-                    P[1] = recip_t(piv);
-#pragma unroll
-                    for (int q = 0; q < NRHS; ++q) P[18 + q] = b[q];
-                } else if (i > K + j && i < K + kb) {
-                    P[2 + i - K] = r[j];
-                }
-                __syncthreads();
-                if (own && i > K + j) {
-                    const T l = r[j] * P[1];
-                    // every P entry is read (all within the buffer; entries past the
-                    // block are stale) and the multiplier selected, so the reads
-                    // need no branch of their own: r[cc] above the row's diagonal
-                    // (K + cc > i) is neither stored nor read, so only the block
-                    // bound masks the update
-#pragma unroll
-                    for (int cc = j + 1; cc < 16; ++cc) {
-                        const T lc = cc < kb ? l : T(0);
-                        r[cc] -= lc * P[2 + cc];
-                    }
-                    r[j] = l;
-#pragma unroll
-                    for (int q = 0; q < NRHS; ++q) b[q] -= l * P[18 + q];
-                }
+            for (int cc = 0; cc < 16; ++cc) {
+                const int col = min(K + cc, p - 1), base = cpk(col, m) - col;
+                blk[cc] = F[base + rb];
+                row[cc] = F[base + max(ic, K)];
             }
+#pragma unroll
+            for (int q = 0; q < NRHS; ++q) yb[q] = ys[(par * NRHS + q) * 16 + l15];
         }
-        if (own) {
+        // (the owners of the block rows overwrite what every wave reads here)
+        front_sync<WAVE>();
+        if (busy) {
+            T piv = T(1);
+            eliminate16<NRHS, T>(blk, row, yb, b, kb, i - K, piv);
+            if (i >= K && i < K + kb) mypiv = piv;
+            const bool act = i >= K && i < m;
 #pragma unroll
             for (int cc = 0; cc < 16; ++cc)
-                if (cc < kb && K + cc <= i) F[cpk(K + cc, m) + i - K - cc] = r[cc];
+                if (act && cc < kb && K + cc <= i) F[cpk(K + cc, m) + i - K - cc] = row[cc];
+            if (i >= K + 16 && i < K + 32)
 #pragma unroll
-            for (int q = 0; q < NRHS; ++q) rl[q * m + i] = b[q];
+                for (int q = 0; q < NRHS; ++q) ys[((par ^ 1) * NRHS + q) * 16 + i - K - 16] = b[q];
         }
-        __syncthreads();
+        front_sync<WAVE>();
         PROF_MARK(PH_DIAG);
-        // ---- trailing lower triangle (rows, cols >= T0) -= L D L^T with MFMA
-        const int T0 = K + kb;
-        const int nT = (m - T0 + 15) >> 4;
-        const int ntile = nT * (nT + 1) / 2;
-        for (int tix = gw; tix < ntile; tix += nw) {
-            int I = 0, rem = tix;
-            while (rem > I) { rem -= I + 1; ++I; }
-            const int J = rem;
-            const int ra = T0 + 16 * I + (lane & 15), rb = T0 + 16 * J + (lane & 15);
-            // operands from clamped addresses inside the front (column K and row
-            // m - 1 stand in past the block or the front) times 0/1 masks, so all
-            // twelve reads issue together without branches
-            // (MFMA of the factor type: v_mfma_f64_16x16x4 or v_mfma_f32_16x16x4)
-            typedef Mfma16<T> M;
-            T a[4], bb[4];
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const int kk = 4 * ks + (lane >> 4);
-                const int kc = kk < kb ? K + kk : K;
-                const int base = cpk(kc, m) - kc;
-                const T dk = F[base + kc];
-                const T ma = (kk < kb && ra < m) ? T(1) : T(0), mb = (kk < kb && rb < m) ? T(1) : T(0);
-                a[ks] = F[base + min(ra, m - 1)] * dk * ma;
-                bb[ks] = F[base + min(rb, m - 1)] * mb;
-            }
-            typename M::V acc = M::zero();
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) acc = M::mma(a[ks], bb[ks], acc);
-            // the tile's targets are distinct: all four read (clamped), then written
-            const int cc = T0 + 16 * J + (lane & 15), ccl = min(cc, m - 1);
-            const int base = cpk(ccl, m) - ccl;
-            T o[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int rr = T0 + 16 * I + M::row(lane, v);
-                o[v] = F[base + min(max(rr, ccl), m - 1)];
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int rr = T0 + 16 * I + M::row(lane, v);
-                if (cc < m && rr < m && rr >= cc) F[base + rr] = o[v] - acc[v];
-            }
+        if (K + kb < p) {
+            panel_update<T>(F, m, p, K, kb, gw, nw);
+            front_sync<WAVE>();
         }
-        __syncthreads();
         PROF_MARK(PH_MFMA);
     }
-    // L panel, D, y; update matrix (packed) and its rhs onto the stack
-    const int lp = cpk(p, m);
-    for (int t = gt; t < lp; t += GT) Lg[t] = F[t];
-    for (int t = gt; t < p; t += GT) Dg[t] = F[cpk(t, m)];
-    for (int t = gt; t < p * nrhs; t += GT) {
-        const int j = t % p, col = t / p;
-        yg[t] = rl[col * m + j];
+    if (i < p && (!(fabs((double)mypiv) > 1e-14 * fabs(d0)) || !isfinite((double)mypiv))) *flag = 2;
+    // D, y, rhs rows of the update matrix, L panel; then the update matrix
+    if (i < p) {
+        (pl.L + fr.D_off)[i] = (double)mypiv;
+#pragma unroll
+        for (int q = 0; q < NRHS; ++q) (pl.L + fr.y_off)[q * p + i] = (double)b[q];
+    }
+    for (int t0 = gt; t0 < lp; t0 += 8 * GT) {
+        T v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = F[min(t0 + u * GT, lp - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (t0 + u * GT < lp) Lg[t0 + u * GT] = v[u];
     }
     if (mu > 0) {
-        T* dst = reinterpret_cast<T*>(c.U + fr.U_off);
-        const int usz = tot - lp;
-        for (int t = gt; t < usz; t += GT) dst[t] = F[lp + t];
-        for (int t = gt; t < mu * nrhs; t += GT) {
-            const int i = t % mu, col = t / mu;
-            dst[usz + t] = rl[col * m + p + i];
-        }
+        auto update_out = [&](auto dst) {
+            if (i >= p && i < m)
+#pragma unroll
+                for (int q = 0; q < NRHS; ++q) dst[cpk(mu, mu) + q * mu + i - p] = b[q];
+            schur_tiles<T>(pl, fr.child_begin, nch, F, Ul, iv, cu[0], cu[1], dst, m, p, gw, nw);
+        };
+        if (WAVE && fr.u_lds >= 0) update_out(Ul + fr.u_lds);
+        else update_out((FEHMM_GLB T*)(pl.U + fr.U_off));
     }
-    __syncthreads();
+    front_sync<WAVE>();
     PROF_MARK(PH_OUT);
 }
 
+struct Step {
+    int32_t front[kStepFronts];
+};
+
 template <int D, int NRHS, typename T>
-__device__ __noinline__ void factorize_lds(const RveCtx& c, Smem& sm, T* F, T* rl, int wave_slice) {
-    constexpr int nrhs = NRHS;
-    const DevPlan& pl = *c.plan;
+__device__ __noinline__ void factorize_lds(const RveCtx& c, Smem& sm, T* Fgen) {
+    const PanelCtx pl = panel_ctx(c);
+    const auto* ke = glb(ke_of<D, NRHS, T>(c));
+    const FEHMM_GLB double* rhs = glb((const double*)c.rhs);
+    FEHMM_LDS T* F = (FEHMM_LDS T*)Fgen;
+    FEHMM_LDS int* flag = (FEHMM_LDS int*)&sm.flag;
+    FEHMM_LDS int32_t* iv = (FEHMM_LDS int32_t*)sm.red;  // inverse row maps of two children of every front in flight
+    static_assert(sizeof(Smem::red) >= 2 * NT * sizeof(int32_t), "inverse row maps");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    PROF_T0();
-    // small subtrees: one front per wave, all fronts of one height at a time
-    for (int h = 0; h < pl.nwave_h; ++h) {
-        T* Fw = F + (int64_t)wave * wave_slice;
-        for (int k = pl.wave_hbeg[h] + wave; k < pl.wave_hbeg[h + 1]; k += NWAVE) {
-            const int sw = pl.wave_list[k];
-            const int mw = pl.fronts[sw].m;
-            wave_front<D, NRHS, T>(c, sm, sw, Fw, Fw + cpk(mw, mw));
+    constexpr int YS = 2 * NRHS * 16;
+    // small subtrees, one per wave: a task is a contiguous range of fronts, the
+    // update matrices inside it stay in the wave's LDS; tasks of a level are
+    // independent
+    FEHMM_LDS T* const Fw = F + wave * pl.wave_slice;
+    FEHMM_LDS T* const Ul = F + pl.ul_base + wave * pl.ul_stride;
+    for (int h = 0; h < pl.ntask_lev; ++h) {
+        const int k1 = load_const(pl.task_beg + h + 1);
+        for (int k = load_const(pl.task_beg + h) + wave; k < k1; k += NWAVE) {
+            const int s1 = load_const(pl.task + 2 * k + 1);
+            for (int s = load_const(pl.task + 2 * k); s <= s1; ++s)
+                front_lds<D, NRHS, T, true>(pl, ke, rhs, flag, s, Fw + YS, Fw, iv + 128 * wave, Ul, tid & 63, 64, 0, 1);
         }
         __syncthreads();
     }
-    PROF_MARK(PH_TRSM);
-    // workgroup fronts: one per step on the whole workgroup, or nf = 2 or 4 side
-    // by side on G equal groups of threads (at least 128 each; with fewer groups
-    // than fronts each group takes nf / G of them in turn), front k's storage
-    // after the rhs rows of fronts 0..k-1
+    // workgroup fronts: one per step on the whole workgroup, or 2 or 4 side by
+    // side on two halves (each half takes one or two of them in turn), a half's
+    // storage after the other's
     for (int st = 0; st < pl.nwg_steps; ++st) {
-        const int32_t* e = pl.wg_steps + kStepFronts * st;
-        const int nf = e[3] >= 0 ? 4 : (e[1] >= 0 ? 2 : 1);
+        const Step e = load_const((const FEHMM_GLB Step*)pl.wg_steps + st);
+        const int nf = e.front[3] >= 0 ? 4 : (e.front[1] >= 0 ? 2 : 1);
         const int G = min(nf, NT / 128);
-        const int GT = NT / G, NW = NWAVE / G, g = tid / GT;
+        const int GT = NT / G, NW = NWAVE / G, g = wave / NW;
+        int need = 0;
+        for (int j = 0; j < nf; ++j) {
+            const DevFront f = load_const(pl.fronts + e.front[j]);
+            need = max(need, cpk(f.p, f.m));
+        }
+        FEHMM_LDS T* const base = F + g * (need + YS);
         for (int r = 0; r < nf / G; ++r) {
-            const int k = r * G + g;
-            int off = 0;
-            for (int j = 0; j < k; ++j) {
-                const int mj = pl.fronts[e[j]].m;
-                off += cpk(mj, mj) + mj * (nrhs + 1);
-            }
-            const int ms = pl.fronts[e[k]].m;
-            T* const Fk = F + off;
-            T* const rlk = nf > 1 ? Fk + cpk(ms, ms) : rl;
-            wg_front<D, NRHS, T>(c, sm, e[k], Fk, rlk, tid - g * GT, GT, wave - g * NW, NW, sm.pub[g]);
+            const int s = load_const(pl.wg_steps + kStepFronts * st + r * G + g);
+            front_lds<D, NRHS, T, false>(pl, ke, rhs, flag, s, base + YS, base, iv + 2 * GT * g, (FEHMM_LDS T*)nullptr,
+                                         tid - g * GT, GT, wave - g * NW, NW);
         }
     }
 }
 
-// backward substitution of one small front (m <= 64) by one wave, lane j =
-// pivot j: the packed panel is staged in the wave's LDS slice S, the update
-// rows' solution values are loaded one per lane and broadcast by readlane, and
-// the pivot triangle is swept from the last pivot (no barrier)
-template <int D, int NRHS, typename T>
-__device__ void backsolve_wave_front(const RveCtx& c, int s, T* S, double* x) {
-    const DevPlan& pl = *c.plan;
-    const int lane = threadIdx.x & 63;
-    const DevFront fr = pl.fronts[uni(s)];  // (uniform per wave: scalar loads)
-    const int m = uni(fr.m), p = uni(fr.p), mu = m - p;
-    const int32_t* rows = pl.rows + fr.rows_off;
-    const T* Lg = reinterpret_cast<const T*>(c.L + fr.L_off);
-    const double* Dg = c.L + fr.D_off;
-    const double* yg = c.L + fr.y_off;
-    const int lp = cpk(p, m);
-    copy_in(S, Lg, lp, lane, 64);
-    double v[NRHS], xs[NRHS];
+// Backward substitution of one front s (threads gt, waves gw as in front_lds):
+//   v = D^-1 y - L21^T x_u on FP64 MFMA (16 pivots x 4 update rows x up to 16 rhs
+//   columns; L read from global memory once, the update rows split over the
+//   waves, their partial sums added in wave order), then the unit triangle in
+//   16-pivot blocks from the last by the first wave: each rhs column's chain in a
+//   16-lane row with DPP broadcasts, earlier pivots folded by all lanes.
+// vb: FP64 scratch, [NRHS][p] pivot values, [NRHS][mu] update rows' solution and
+// [nw][NRHS][p] partial sums.
+template <int D, int NRHS, typename T, bool WAVE>
+__device__ inline void backsolve_front(const PanelCtx& pl, int s, FEHMM_LDS double* vb, FEHMM_GLB double* x, int gt, int GT,
+                                       int gw, int nw) {
+    typedef Mfma16<double> M;
+    const int lane = threadIdx.x & 63, l15 = lane & 15, lg = lane >> 4;
+    const DevFront fr = load_const(pl.fronts + s);
+    const int m = fr.m, p = fr.p, mu = m - p;
+    const FEHMM_GLB int32_t* rows = pl.rows + fr.rows_off;
+    const FEHMM_GLB T* Lg = (const FEHMM_GLB T*)(pl.L + fr.L_off);
+    const FEHMM_GLB double* Dg = pl.L + fr.D_off;
+    const FEHMM_GLB double* yg = pl.L + fr.y_off;
+    FEHMM_LDS double* v = vb;                  // [NRHS][p]
+    FEHMM_LDS double* xs = vb + NRHS * p;      // [NRHS][mu]
+    FEHMM_LDS double* part = vb + NRHS * m;    // [nw][NRHS][p]
+    for (int j = gt; j < p; j += GT) {
+        const double rd = 1.0 / Dg[j];
 #pragma unroll
-    for (int q = 0; q < NRHS; ++q) {
-        v[q] = (lane < p) ? yg[(int64_t)q * p + lane] / Dg[lane] : 0.0;
-        xs[q] = (lane < mu) ? x[(int64_t)rows[p + lane] * NRHS + q] : 0.0;
+        for (int q = 0; q < NRHS; ++q) v[q * p + j] = yg[q * p + j] * rd;
     }
-    __builtin_amdgcn_wave_barrier();
-    // column `lane` of the panel is S[cj + i], i >= lane; lanes >= p read column 0
-    // (in bounds: p + i < m <= cpk(p, m)) and discard the value
-    const int jl = lane < p ? lane : 0;
-    const int cj = cpk(jl, m) - jl;
-    // four entries per pass, read ahead of the updates (clamped indices, masked
-    // values; the broadcast lanes are uniform)
-    const double pm = lane < p ? 1.0 : 0.0;
-    for (int i0 = 0; i0 < mu; i0 += 4) {
-        double l[4];
+    for (int i = gt; i < mu; i += GT) {
+        const int xr = rows[p + i] * NRHS;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) l[u] = (double)S[cj + p + min(i0 + u, mu - 1)] * (i0 + u < mu ? pm : 0.0);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int q = 0; q < NRHS; ++q) v[q] -= l[u] * readlane_d(xs[q], min(i0 + u, mu - 1));
+        for (int q = 0; q < NRHS; ++q) xs[q * mu + i] = x[xr + q];
     }
-    for (int j0 = p - 1; j0 > 0; j0 -= 4) {
-        double l[4];
+    front_sync<WAVE>();
+    if (mu > 0) {
+        const int nks = (mu + 3) >> 2;
+        for (int t = 0; 16 * t < p; ++t) {
+            const int j = min(16 * t + l15, p - 1);
+            const int col = cpkv(j, m) - j + p;
+            M::V acc = M::zero();
+            for (int k0 = gw; k0 < nks; k0 += 8 * nw) {
+                T a[8];
+                double bx[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int jj = max(j0 - u, 1);
-            l[u] = (double)S[cj + jj] * ((j0 - u >= 1 && lane < jj) ? 1.0 : 0.0);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int q = 0; q < NRHS; ++q) v[q] -= l[u] * readlane_d(v[q], max(j0 - u, 1));
-    }
-    if (lane < p)
-#pragma unroll
-        for (int q = 0; q < NRHS; ++q) x[(int64_t)rows[lane] * NRHS + q] = v[q];
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Backward substitution of one workgroup front s on threads gt = 0..GT-1 (wave
-// gw of the group; the whole workgroup, or one half of it beside a second
-// front): the packed L panel staged at Ls (or read from global memory when Ls is
-// null), FP64 scratch vb ([NRHS][p] pivot values, [NRHS][m-p] update-row
-// solution, [3][p] partial sums), then the update-row products, the pivot
-// triangle in 16-pivot blocks (readlane chains in wave 0 of the group) and the
-// solution scattered to x.  Fronts sharing a step have equal pivot counts, so
-// both halves pass the same barriers.
-template <int D, int NRHS, typename T>
-__device__ inline void wg_backsolve(const RveCtx& c, int s, T* Ls, double* vb, double* x, int gt, int GT, int gw) {
-    const DevPlan& pl = *c.plan;
-    const int lane = threadIdx.x & 63;
-    constexpr int NPART = (NRHS == 1) ? 3 : 1;
-    const DevFront fr = pl.fronts[uni(s)];  // (uniform per wave: scalar loads)
-    const int m = uni(fr.m), p = uni(fr.p);
-    const int32_t* rows = pl.rows + fr.rows_off;
-    const T* Lg = reinterpret_cast<const T*>(c.L + fr.L_off);
-    const double* Dg = c.L + fr.D_off;
-    const double* yg = c.L + fr.y_off;
-    const int lp = cpk(p, m);
-    // (FP64 panels are always staged: one address space for the reads)
-    const T* Lp = Lg;
-    if (sizeof(T) == sizeof(double) || Ls) {
-        copy_in(Ls, Lg, lp, gt, GT);
-        Lp = Ls;
-    }
-    double* v = vb;                 // [NRHS][p]
-    double* xs = vb + NRHS * p;     // [NRHS][m - p]
-    double* part = vb + NRHS * m;   // [NPART][p] (NRHS == 1)
-    for (int t = gt; t < p * NRHS; t += GT) {
-        const int j = t % p, q = t / p;
-        v[t] = yg[(int64_t)q * p + j] / Dg[j];
-    }
-    for (int t = gt; t < (m - p) * NRHS; t += GT) {
-        const int i = t % (m - p), q = t / (m - p);
-        xs[t] = x[(int64_t)rows[p + i] * NRHS + q];
-    }
-    __syncthreads();
-    if constexpr (NRHS == 1) {
-        for (int t = gt; t < NPART * p; t += GT) {
-            const int j = t % p, pt = t / p;
-            const T* colj = Lp + cpk(j, m) - j;
-            double acc = 0.0;
-#pragma unroll 4
-            for (int i = p + pt; i < m; i += NPART) acc += (double)colj[i] * xs[i - p];
-            part[t] = acc;
-        }
-        __syncthreads();
-        for (int j = gt; j < p; j += GT) v[j] -= (part[j] + part[p + j]) + part[2 * p + j];
-    } else {
-        for (int j = gt; j < p; j += GT) {
-            const T* colj = Lp + cpk(j, m) - j;
-            double acc[NRHS];
-#pragma unroll
-            for (int q = 0; q < NRHS; ++q) acc[q] = 0.0;
-#pragma unroll 4
-            for (int i = p; i < m; ++i) {
-                const double l = colj[i];
-#pragma unroll
-                for (int q = 0; q < NRHS; ++q) acc[q] += l * xs[q * (m - p) + i - p];
-            }
-#pragma unroll
-            for (int q = 0; q < NRHS; ++q) v[q * p + j] -= acc[q];
-        }
-    }
-    __syncthreads();
-    if (p <= 64) {
-        // the pivot triangle by the group's wave 0 alone, lane = pivot, from the last pivot
-        // (readlane broadcasts of the finished values, no barrier)
-        if (gw == 0) {
-            const int jl = lane < p ? lane : 0;
-            const T* colj = Lp + cpk(jl, m) - jl;  // L(i, lane) = colj[i], i >= lane
-            double vv[NRHS];
-#pragma unroll
-            for (int q = 0; q < NRHS; ++q) vv[q] = lane < p ? v[q * p + lane] : 0.0;
-            // four pivots per pass, read ahead of the updates (row max(i, jl) of
-            // column jl, inside the panel for every lane; masked values)
-            for (int i0 = p - 1; i0 > 0; i0 -= 4) {
-                double l[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = max(i0 - u, 1);
-                    l[u] = (double)colj[max(i, jl)] * ((i0 - u >= 1 && lane < i) ? 1.0 : 0.0);
+                for (int u = 0; u < 8; ++u) {
+                    const int i = 4 * (k0 + u * nw) + lg;
+                    a[u] = Lg[col + min(i, mu - 1)];
+                    bx[u] = xs[(NRHS == 1 ? 0 : min(l15, NRHS - 1) * mu) + min(i, mu - 1)];
+                    bx[u] *= (i < mu && l15 < NRHS) ? 1.0 : 0.0;
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int q = 0; q < NRHS; ++q) vv[q] -= l[u] * readlane_d(vv[q], max(i0 - u, 1));
+                for (int u = 0; u < 8; ++u)
+                    if (k0 + u * nw < nks) acc = M::mma((double)a[u], bx[u], acc);
             }
+            // result element v of lane: pivot 16 t + lg + 4 v, rhs column l15
+            if (l15 < NRHS)
 #pragma unroll
-            for (int q = 0; q < NRHS; ++q)
-                if (lane < p) v[q * p + lane] = vv[q];
+                for (int e = 0; e < 4; ++e) {
+                    const int jj = 16 * t + M::row(lane, e);
+                    if (jj < p) part[(gw * NRHS + l15) * p + jj] = acc[e];
+                }
         }
-        __syncthreads();
+        front_sync<WAVE>();
+        for (int t = gt; t < p * NRHS; t += GT) {
+            double sum = part[t];
+            for (int w = 1; w < nw; ++w) sum += part[w * NRHS * p + t];
+            v[t] -= sum;
+        }
+        front_sync<WAVE>();
     }
-    const int nb = p <= 64 ? 0 : (p + 15) >> 4;
-    for (int bk = nb - 1; bk >= 0; --bk) {
-        const int K = 16 * bk, kb = min(16, p - K);
-        if (gw == 0) {
-            const bool own = lane < kb;
+    if (gw == 0) {
+        for (int K = 16 * ((p - 1) >> 4); K >= 0; K -= 16) {
+            const int kb = min(16, p - K);
+            // block triangle: L(K + cc, K + l15), cc > l15
             double Lr[16];
+            {
+                const int col = cpkv(K + min(l15, kb - 1), m) - min(l15, kb - 1);
 #pragma unroll
-            for (int cc = 0; cc < 16; ++cc)
-                Lr[cc] = (own && cc < kb && cc > lane) ? (double)Lp[cpk(K + lane, m) + cc - lane] : 0.0;
+                for (int cc = 1; cc < 16; ++cc)
+                    Lr[cc] = (double)Lg[col + min(max(cc, l15), kb - 1)] * ((cc < kb && cc > l15) ? 1.0 : 0.0);
+            }
+            // the block's rows of the earlier columns j = lane (+ 64)
+            T lk[16];
+            const int j0 = min(lane, max(K - 1, 0));
+            const int cj = cpkv(j0, m) - j0 + K;
 #pragma unroll
-            for (int q = 0; q < NRHS; ++q) {
-                double vv = own ? v[q * p + K + lane] : 0.0;
+            for (int cc = 0; cc < 16; ++cc) lk[cc] = Lg[cj + min(cc, kb - 1)];
+            // one rhs column per 16-lane row
 #pragma unroll
-                for (int cc = 15; cc >= 0; --cc) {
-                    if (cc < kb) {
-                        const double xc = readlane_d(vv, cc);
-                        if (lane < cc) vv -= Lr[cc] * xc;
-                    }
+            for (int q0 = 0; q0 < NRHS; q0 += 4) {
+                const int q = min(q0 + lg, NRHS - 1);
+                double vv = v[q * p + K + min(l15, kb - 1)];
+                static_for<0, 15>([&](auto C) {
+                    constexpr int cc = 15 - decltype(C)::value;
+                    if (cc < kb) vv -= Lr[cc] * row_bcast<cc>(vv);
+                });
+                if (l15 < kb && q0 + lg < NRHS) v[q * p + K + l15] = vv;
+            }
+            front_sync<true>();
+            for (int j = lane; j < K; j += 64) {
+                if (j >= 64) {
+                    const int c2 = cpkv(j, m) - j + K;
+#pragma unroll
+                    for (int cc = 0; cc < 16; ++cc) lk[cc] = Lg[c2 + min(cc, kb - 1)];
                 }
-                if (own) v[q * p + K + lane] = vv;
+#pragma unroll
+                for (int q = 0; q < NRHS; ++q) {
+                    double acc = v[q * p + j];
+#pragma unroll
+                    for (int cc = 0; cc < 16; ++cc) {
+                        const double xk = v[q * p + K + min(cc, kb - 1)];
+                        acc -= (cc < kb ? (double)lk[cc] : 0.0) * xk;
+                    }
+                    v[q * p + j] = acc;
+                }
             }
+            front_sync<true>();
         }
-        __syncthreads();
-        for (int j = gt; j < K; j += GT) {
-            const T* colj = Lp + cpk(j, m) - j;
-            double lk[16];
-#pragma unroll
-            for (int cc = 0; cc < 16; ++cc) lk[cc] = (cc < kb) ? (double)colj[K + cc] : 0.0;
-#pragma unroll
-            for (int q = 0; q < NRHS; ++q) {
-                double acc = v[q * p + j];
-#pragma unroll
-                for (int cc = 0; cc < 16; ++cc)
-                    if (cc < kb) acc -= lk[cc] * v[q * p + K + cc];
-                v[q * p + j] = acc;
-            }
-        }
-        __syncthreads();
     }
-    for (int t = gt; t < p * NRHS; t += GT) {
-        const int j = t % p, q = t / p;
-        x[(int64_t)rows[j] * NRHS + q] = v[t];
+    front_sync<WAVE>();
+    for (int j = gt; j < p; j += GT) {
+        const int xr = rows[j] * NRHS;
+#pragma unroll
+        for (int q = 0; q < NRHS; ++q) x[xr + q] = v[q * p + j];
     }
-    __syncthreads();
+    front_sync<WAVE>();
 }
 
 // backward substitution L^T x = D^-1 y with NRHS columns; y is each front's
 // stored forward-substituted rhs, x (node-major [dof][NRHS], FP64) receives the
-// solution.  The workgroup fronts in the plan's steps, in reverse (wg_backsolve;
-// panels staged in LDS, for FP32 when they fit beside the FP64 scratch), then
-// the small subtrees one front per wave, parents first.
+// solution.  The workgroup fronts in the plan's steps, in reverse, then the
+// small subtrees one front per wave, parents first.  S: FP64 scratch, `slice`
+// doubles per wave.
 template <int D, int NRHS, typename T>
-__device__ __noinline__ void backsolve_lds(const RveCtx& c, Smem& sm, T* F, T* rl, double* x, int front_elems,
-                                         int wave_slice) {
-    const DevPlan& pl = *c.plan;
+__device__ __noinline__ void backsolve_lds(const RveCtx& c, double* Sgen, double* xgen, int slice) {
+    const PanelCtx pl = panel_ctx(c);
+    FEHMM_LDS double* S = (FEHMM_LDS double*)Sgen;
+    FEHMM_GLB double* x = glb(xgen);
+    slice = uni(slice);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    zero_pinned<D>(c, x, NRHS);
-    // large fronts (the top of the tree) in the plan's steps, then the small
-    // subtrees wave by wave
+    zero_pinned<D>(c, xgen, NRHS);
     for (int st = pl.nwg_steps - 1; st >= 0; --st) {
-        const int32_t* e = pl.wg_steps + kStepFronts * st;
-        const int nf = e[3] >= 0 ? 4 : (e[1] >= 0 ? 2 : 1);
+        const Step e = load_const((const FEHMM_GLB Step*)pl.wg_steps + st);
+        const int nf = e.front[3] >= 0 ? 4 : (e.front[1] >= 0 ? 2 : 1);
         const int G = min(nf, NT / 128);
-        const int GT = NT / G, NW = NWAVE / G, g = tid / GT;
-        // scratch and staged panel: one front uses the front region and (FP64) the
-        // rhs region as before; several fronts split the front region, front k
-        // taking [panel | FP64 scratch] (FP32: [FP64 scratch | panel]) after
-        // those of fronts 0..k-1
-        constexpr int dpe = sizeof(double) / sizeof(T);  // T elements per double
-        for (int r = 0; r < nf / G; ++r) {
-            const int k = r * G + g;
-            int off = 0;
-            for (int j = 0; j < k; ++j) {
-                const int mj = pl.fronts[e[j]].m, pj = pl.fronts[e[j]].p;
-                off += (cpk(pj, mj) + dpe * (mj * NRHS + 3 * pj) + 1) & ~1;
-            }
-            const int m = pl.fronts[e[k]].m, p = pl.fronts[e[k]].p, lp = cpk(p, m);
-            const int vneed = dpe * (m * NRHS + 3 * p);
-            T* const base = F + off;
-            T* Ls;
-            double* vb;
-            if constexpr (sizeof(T) == sizeof(double)) {
-                Ls = base;
-                vb = nf > 1 ? reinterpret_cast<double*>(base + lp) : reinterpret_cast<double*>(rl);
-            } else {
-                // FP32 panel staged after the FP64 scratch when both fit the front region
-                vb = reinterpret_cast<double*>(base);
-                Ls = (nf > 1 || vneed + lp <= front_elems) ? base + vneed : nullptr;
-            }
-            wg_backsolve<D, NRHS, T>(c, e[k], Ls, vb, x, tid - g * GT, GT, wave - g * NW);
-        }
+        const int GT = NT / G, NW = NWAVE / G, g = wave / NW;
+        for (int r = 0; r < nf / G; ++r)
+            backsolve_front<D, NRHS, T, false>(pl, load_const(pl.wg_steps + kStepFronts * st + r * G + g),
+                                               S + g * NW * slice, x, tid - g * GT, GT, wave - g * NW, NW);
     }
     // small subtrees: one front per wave, parents (greater height) first
+    PROF_T0();
     for (int h = pl.nwave_h - 1; h >= 0; --h) {
-        T* S = F + (int64_t)wave * wave_slice;
-        for (int k = pl.wave_hbeg[h] + wave; k < pl.wave_hbeg[h + 1]; k += NWAVE)
-            backsolve_wave_front<D, NRHS, T>(c, pl.wave_list[k], S, x);
+        const int k1 = load_const(pl.wave_hbeg + h + 1);
+        for (int k = load_const(pl.wave_hbeg + h) + wave; k < k1; k += NWAVE)
+            backsolve_front<D, NRHS, T, true>(pl, load_const(pl.wave_list + k), S + wave * slice, x, tid & 63, 64, 0, 1);
         __syncthreads();
     }
+    PROF_MARK(PH_TRSM);
 }
 
+// global -> LDS copy, eight strides per pass: all loads first, then all stores
+// (the compiler does not move a load past a store that may alias it)
+template <typename T>
+__device__ inline void copy_in(T* dst, const T* src, int n, int first, int stride) {
+    for (int t0 = first; t0 < n; t0 += 8 * stride) {
+        T v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = src[min(t0 + u * stride, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (t0 + u * stride < n) dst[t0 + u * stride] = v[u];
+    }
+}
 // forward substitution L y = b for a new rhs b (node-major [dof][NRHS], FP64,
 // overwritten): fronts in elimination order; per front the pivot rows are
 // solved in 16-pivot blocks (readlane chain in wave 0) and folded into the rows
@@ -2357,6 +2411,7 @@ __device__ inline void rve_setup(const SolveArgs& a, int rve, double* base, RveC
         for (int k = 0; k < D; ++k) wj *= (c.elem == 1 ? h : 0.5 * h);
         if (c.elem == 1) wj /= (D == 2 ? 2.0 : 6.0);  // simplex volume h^d / d!
         sm.wJ = wj;
+        c.U[0] = 0.0;  // the zero that fronts read for entries a child does not have
         sm.flag = 0;
         sm.atol = a.atol >= 0 ? a.atol : a.rve_atol[rve];
     }
@@ -2471,13 +2526,13 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                     for (int t = threadIdx.x; t < ndof; t += NT) c.rhs[(int64_t)t * NSPEC] = -c.R[t];
                     __syncthreads();
                     if (!c.plan->lds_ok) factorize_glb<D, T>(c, sm, NSPEC, dynF);
-                    else if constexpr (D == 2) factorize_lds<D, NSPEC, T>(c, sm, dynF, dynF + a.lds_front, a.wave_slice);
+                    else if constexpr (D == 2) factorize_lds<D, NSPEC, T>(c, sm, dynF);
                 }
             }
             if (!spec) {
                 for (int t = threadIdx.x; t < ndof; t += NT) c.rhs[t] = -c.R[t];
                 __syncthreads();
-                if (c.plan->lds_ok) factorize_lds<D, 1, T>(c, sm, dynF, dynF + a.lds_front, a.wave_slice);
+                if (c.plan->lds_ok) factorize_lds<D, 1, T>(c, sm, dynF);
                 else factorize_glb<D, T>(c, sm, 1, dynF);
             }
             if (sm.flag) { status = 3; break; }
@@ -2489,13 +2544,13 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                     // stays there for the condensation if the next state converges
                     if (!c.plan->lds_ok) backsolve_glb<D, NSPEC, T>(c, sm, c.rhs);
                     else if constexpr (D == 2)
-                        backsolve_lds<D, NSPEC, T>(c, sm, dynF, dynF + a.lds_front, c.rhs, a.lds_front, a.wave_slice);
+                        backsolve_lds<D, NSPEC, T>(c, dynRaw, c.rhs, a.bs_slice);
                     for (int t = threadIdx.x; t < ndof; t += NT) c.x[t] = c.rhs[(int64_t)t * NSPEC];
                     __syncthreads();
                 }
             }
             if (!spec) {
-                if (c.plan->lds_ok) backsolve_lds<D, 1, T>(c, sm, dynF, dynF + a.lds_front, c.x, a.lds_front, a.wave_slice);
+                if (c.plan->lds_ok) backsolve_lds<D, 1, T>(c, dynRaw, c.x, a.bs_slice);
                 else backsolve_glb<D, 1, T>(c, sm, c.x);
             }
             PROF_MARK(PH_BACK);
@@ -2510,8 +2565,8 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                     const double rl2 = sqrt(free_norm2<D>(c, sm, ir1));
                     if (!(rl2 > a.ir_eta * rn)) break;
                     if (c.plan->lds_ok) {
-                        forward_lds<D, 1, T>(c, sm, dynF, ir1, a.lds_front);
-                        backsolve_lds<D, 1, T>(c, sm, dynF, dynF + a.lds_front, ir2, a.lds_front, a.wave_slice);
+                        forward_lds<D, 1, T>(c, sm, dynF, ir1, a.lds_elems);
+                        backsolve_lds<D, 1, T>(c, dynRaw, ir2, a.bs_slice);
                     } else {
                         forward_glb<D, 1, T>(c, sm, ir1);
                         backsolve_glb<D, 1, T>(c, sm, ir2);
@@ -2596,9 +2651,9 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                 else if (!c.plan->lds_ok)
                     factorize_glb<D, double>(c, sm, D2, dynRaw);
                 else if (IR && a.tan64)
-                    factorize_lds<D, D2, double>(c, sm, dynRaw, dynRaw + a.lds_front64, a.wave_slice);
+                    factorize_lds<D, D2, double>(c, sm, dynRaw);
                 else
-                    factorize_lds<D, D2, T>(c, sm, dynF, dynF + a.lds_front, a.wave_slice);
+                    factorize_lds<D, D2, T>(c, sm, dynF);
                 if (sm.flag) {
                     status = 3;
                 } else if (!tan64) {
@@ -2607,7 +2662,7 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                     // (second-order) form
                     //   Abar = <A> - Y^T X - X^T r,  r = Y - K X,
                     // whose error is (X - X*)^T K (X - X*) (energy-norm error squared)
-                    if (!stale) backsolve_lds<D, D2, T>(c, sm, dynF, dynF + a.lds_front, X, a.lds_front, a.wave_slice);
+                    if (!stale) backsolve_lds<D, D2, T>(c, dynRaw, X, a.bs_slice);
                     // refinement corrections: ir2 unless it holds Y
                     double* const corr = stale ? c.rhs : ir2;
                     const int max_ref = stale ? 2 : a.ir_max_tan;
@@ -2628,8 +2683,8 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                             if (done) break;
                         }
                         if (c.plan->lds_ok) {
-                            forward_lds<D, D2, T>(c, sm, dynF, ir1, a.lds_front);
-                            backsolve_lds<D, D2, T>(c, sm, dynF, dynF + a.lds_front, corr, a.lds_front, a.wave_slice);
+                            forward_lds<D, D2, T>(c, sm, dynF, ir1, a.lds_elems);
+                            backsolve_lds<D, D2, T>(c, dynRaw, corr, a.bs_slice);
                         } else {
                             forward_glb<D, D2, T>(c, sm, ir1);
                             backsolve_glb<D, D2, T>(c, sm, corr);
@@ -2765,30 +2820,16 @@ hipError_t launch_rve_solve(const SolveArgs& a, int nslots, size_t dyn_bytes, bo
     return hipGetLastError();
 }
 
-}  // namespace FEHMM_VARIANT
 }  // namespace fehmm
 
 #if FEHMM_PHASE_PROF
-#define FEHMM_CAT2(a, b) a##_##b
-#define FEHMM_CAT(a, b) FEHMM_CAT2(a, b)
-extern "C" int FEHMM_CAT(rve_debug_phase_clocks, FEHMM_VARIANT)(unsigned long long* out, int reset) {
-    namespace V = fehmm::FEHMM_VARIANT;
-    if (hipMemcpyFromSymbol(out, HIP_SYMBOL(V::g_phase), sizeof(unsigned long long) * V::PH_N) != hipSuccess)
-        return -3;
+extern "C" int rve_debug_phase_clocks(unsigned long long* out, int reset) {
+    using namespace fehmm;
+    if (hipMemcpyFromSymbol(out, HIP_SYMBOL(g_phase), sizeof(unsigned long long) * PH_N) != hipSuccess) return -3;
     if (reset) {
-        unsigned long long z[V::PH_N] = {0};
-        if (hipMemcpyToSymbol(HIP_SYMBOL(V::g_phase), z, sizeof(z)) != hipSuccess) return -3;
+        unsigned long long z[PH_N] = {0};
+        if (hipMemcpyToSymbol(HIP_SYMBOL(g_phase), z, sizeof(z)) != hipSuccess) return -3;
     }
     return 0;
 }
-#if FEHMM_NT == 256
-// the phase clocks of both workgroup sizes, summed
-extern "C" int rve_debug_phase_clocks_nt512(unsigned long long* out, int reset);
-extern "C" int rve_debug_phase_clocks(unsigned long long* out, int reset) {
-    unsigned long long b[fehmm::nt256::PH_N];
-    if (rve_debug_phase_clocks_nt256(out, reset) || rve_debug_phase_clocks_nt512(b, reset)) return -3;
-    for (int i = 0; i < fehmm::nt256::PH_N; ++i) out[i] += b[i];
-    return 0;
-}
-#endif
 #endif

@@ -7,8 +7,15 @@
 namespace fehmm {
 
 struct DevFront {
-    int32_t m, p, parent, child_begin, child_end, kmap_begin, kmap_end, asm_begin, asm_end, wave;
+    int32_t m, p, parent, child_begin, child_end, kmap_begin, kmap_end, asm_begin, asm_end, u_lds;
     int64_t rows_off, relind_off, L_off, D_off, y_off, U_off, ea_off;
+};
+
+// a front's child as its parent reads it, in the order of children[]
+struct DevChild {
+    int32_t mc, npre;  // update rows; update entries (a prefix) that go to the parent's panel
+    int32_t u_lds, pad;
+    int64_t ea_off, inv_off, U_off;
 };
 
 struct DevPlan {
@@ -19,15 +26,21 @@ struct DevPlan {
     const int32_t* children;
     const KPair* kpair;
     const KContrib* kcontrib;
-    const int32_t* asm_rc;
+    const int32_t* asm_dst;
     const int32_t* asm_src;
     const int32_t* ea_dst;
+    const int32_t* inv;
+    const DevChild* childrec;
     const int32_t* wave_list;
     const int32_t* wave_hbeg;
     int32_t nwave_h;       // number of heights in the wave phase
-    int32_t wave_slice;    // doubles per wave slice
+    int32_t wave_slice;    // LDS elements per wave slice
     const int32_t* wg_steps;  // [nwg_steps][kStepFronts] workgroup-front steps (-1 padded)
     int32_t nwg_steps;
+    const int32_t* task;      // wave phase: first and last front of every task
+    const int32_t* task_beg;  // [ntask_lev + 1] tasks of each level
+    int32_t ntask_lev;
+    int32_t ul_base, ul_stride;  // LDS update matrices: first element of wave 0's, elements from wave to wave
     int32_t bc;               // micro boundary conditions: 0 periodic, 1 linear displacements
 };
 
@@ -61,13 +74,12 @@ struct SolveArgs {
     int32_t* iters;
     double rtol, atol;
     int32_t max_iter, backtrack, want_A, dim;
-    int32_t lds_front;           // elements (of the front type) of the LDS front region; rhs rows follow
+    int32_t lds_elems;           // elements (of the front type) of the dynamic LDS
+    int32_t bs_slice;            // FP64 scratch per wave of the LDS plans' backward substitution
     int32_t flags;               // RVE_FLAG_* of the options
-    int32_t wave_slice;          // elements of one wave's LDS slice in the wave phase
     int32_t ir_max;              // refinement sweeps per Newton step (FP32 factors)
     int32_t ir_max_tan;          // refinement sweeps of the tangent solves
     int32_t tan64;               // FP32 factors: the condensation factorization of LDS plans in FP64
-    int32_t lds_front64;         // FP64 elements of the front region for that factorization
     int32_t reuse_tan;           // 2D LDS plans: the condensation from the last Newton factorization
     double ir_eta;               // stop refining when ||b - K x|| <= ir_eta ||R||
     double ir_eta_tan;           // same for the d^2 tangent columns (Frobenius)
