@@ -414,7 +414,7 @@ def assembly_block(s, wl, meta, reps=20):
     nen = 2 ** d
     nd = nen * d
     alg = 8 * nn * d * 2 + ne + 8 * nn * d * d * (3 ** d + 1) / 2
-    moved = 8 * nn * d * 2 + ne + 8 * ne * nd * 2 + 8 * ne * nd * nd + 8 * nn * d
+    moved = 8 * nn * d * 2 + ne + 8 * ne * nd * 2 + 8 * ne * nd * (nd + 1) // 2 + 8 * nn * d
     stream = torch.cuda.current_stream()
     for _ in range(3):
         s.batch.assemble(s.F, None, s.status, stream=stream.cuda_stream)

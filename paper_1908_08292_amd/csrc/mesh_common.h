@@ -57,4 +57,19 @@ FEHMM_HD bool plan_pinned(int bc, int d, int n, int v) {
     return false;
 }
 
+// plane of the symmetric element tangent's entry ((a, i), (b, k)): for every i the
+// pairs a >= b of k_(a,i),(b,i) (2^d (2^d + 1) / 2 planes), then for i < k all of
+// k_(a,i),(b,k) (4^d planes each); 36 planes in 2D, 300 in 3D.  Entry planes
+// [entry][element] keep consecutive elements adjacent.
+FEHMM_HD int sym_entry(int d, int a, int i, int b, int k) {
+    const int nen = 1 << d, np = nen * (nen + 1) / 2;
+    if (i == k) {
+        const int hi = a > b ? a : b, lo = a > b ? b : a;
+        return i * np + hi * (hi + 1) / 2 + lo;
+    }
+    const int x = i < k ? a : b, y = i < k ? b : a, lo = i < k ? i : k, hi = i < k ? k : i;
+    return d * np + (lo + hi - 1) * nen * nen + x * nen + y;
+}
+constexpr int sym_entries(int d) { return (1 << d) * d * ((1 << d) * d + 1) / 2; }
+
 }  // namespace fehmm

@@ -296,21 +296,20 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
         F.kmap_end = (int)P.kpair.size();
         F.asm_begin = (int)P.asm_dst.size();
         {
-            const int nen = 1 << d, ndl = nen * d;
+            const int nen = 1 << d;
             for (int q = F.kmap_begin; q < F.kmap_end; ++q) {
                 const KPair& kp = P.kpair[q];
                 for (int k = 0; k < d; ++k)
                     for (int l = 0; l < d; ++l) {
                         int r = kp.row_node * d + k, col = kp.col_node * d + l;
                         if (r < col) continue;
-                        const int64_t dst = (int64_t)col * F.m - (int64_t)col * (col - 1) / 2 + r - col;
-                        if (dst > INT32_MAX) throw std::runtime_error("front too large for the gather list");
-                        P.asm_dst.push_back((int32_t)dst);
+                        if (r >= 32768 || col >= 32768) throw std::runtime_error("front too large for the gather list");
+                        P.asm_dst.push_back((r << 16) | col);
                         for (int t = 0; t < nen; ++t) {
                             int src = -1;
                             if (t < kp.c_count) {
                                 const KContrib& cb = P.kcontrib[kp.c_begin + t];
-                                int64_t flat = ((int64_t)cb.elem * ndl + cb.lb * d + k) * ndl + cb.la * d + l;
+                                const int64_t flat = (int64_t)sym_entry(d, cb.lb, k, cb.la, l) * P.nelem + cb.elem;
                                 if (flat > INT32_MAX) throw std::runtime_error("element matrix index overflow");
                                 src = (int)flat;
                             }
@@ -390,6 +389,12 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
         // substitution the front's rows and one partial sum per wave
         const int64_t rhs_cols = d * d + (d == 2 ? 1 : 0), block_rhs = 2 * 16 * rhs_cols;
         auto packed_panel = [](const FrontHost& X) { return (int64_t)X.p * X.m - (int64_t)X.p * (X.p - 1) / 2; };
+        // targets of the original entries as offsets in the packed panel
+        for (const FrontHost& F : P.fronts)
+            for (int t = F.asm_begin; t < F.asm_end; ++t) {
+                const int r = P.asm_dst[t] >> 16, col = P.asm_dst[t] & 0xffff;
+                P.asm_dst[t] = col * F.m - col * (col - 1) / 2 + r - col;
+            }
         for (int s = 0; s < ns; ++s) {
             FrontHost& F = P.fronts[s];
             F.inv_off = (int64_t)P.inv.size();

@@ -57,10 +57,9 @@ struct PlanHost {
     std::vector<int32_t> rows, relind, children;
     std::vector<KPair> kpair;
     std::vector<KContrib> kcontrib;
-    // flat gather list of the original entries: offset in the packed front
-    // (cpk(col, m) + row - col) and up to 2^d element-matrix sources (flat index
-    // into the element matrices [elem][2^d d][2^d d], -1 = none),
-    // asm_src[t * 2^d + q]
+    // flat gather list of the original entries: target (LDS plans: offset in the
+    // packed panel, cpk(col, m) + row - col; else row << 16 | col) and up to 2^d
+    // element-tangent sources (sym_entry * nelem + elem, -1 = none), asm_src[t * 2^d + q]
     std::vector<int32_t> asm_dst, asm_src;
     // extend-add map: for every entry t of a front's packed update matrix
     // (column-major lower, (m-p)(m-p+1)/2 entries) the offset of its target in

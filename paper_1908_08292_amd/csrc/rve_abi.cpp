@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "../../include/rve.h"
+#include "mesh_common.h"
 #include "plan.h"
 #include "solver_dev.h"
 
@@ -56,8 +57,6 @@ struct PlanEntry {
     int32_t* d_rows = nullptr;
     int32_t* d_relind = nullptr;
     int32_t* d_children = nullptr;
-    KPair* d_kpair = nullptr;
-    KContrib* d_kcontrib = nullptr;
     int32_t* d_asm_dst = nullptr;
     int32_t* d_inv = nullptr;
     DevChild* d_childrec = nullptr;
@@ -103,7 +102,7 @@ int upload(const std::vector<T>& v, T** out) {
 
 void free_plan_dev(PlanEntry& e) {
     (void)hipFree(e.d_fronts); (void)hipFree(e.d_rows); (void)hipFree(e.d_relind);
-    (void)hipFree(e.d_children); (void)hipFree(e.d_kpair); (void)hipFree(e.d_kcontrib);
+    (void)hipFree(e.d_children); 
     (void)hipFree(e.d_asm_dst); (void)hipFree(e.d_inv); (void)hipFree(e.d_childrec); (void)hipFree(e.d_task); (void)hipFree(e.d_task_beg);
     (void)hipFree(e.d_asm_src); (void)hipFree(e.d_ea_dst);
     (void)hipFree(e.d_wave_list); (void)hipFree(e.d_wave_hbeg); (void)hipFree(e.d_wg_steps);
@@ -139,7 +138,7 @@ int plan_device(PlanEntry* e) {
     std::vector<DevFront> fr(P.fronts.size());
     for (size_t s = 0; s < fr.size(); ++s) {
         const FrontHost& f = P.fronts[s];
-        fr[s] = DevFront{f.m, f.p, f.parent, f.child_begin, f.child_end, f.kmap_begin, f.kmap_end, f.asm_begin,
+        fr[s] = DevFront{f.m, f.p, f.parent, f.child_begin, f.child_end, f.asm_begin,
                          f.asm_end, f.u_lds, f.rows_off, f.relind_off, f.L_off, f.D_off, f.y_off, f.U_off, f.ea_off};
     }
     std::vector<DevChild> cr(P.children.size());
@@ -150,8 +149,7 @@ int plan_device(PlanEntry* e) {
     int st;
     if ((st = upload(fr, &e->d_fronts)) || (st = upload(P.inv, &e->d_inv)) || (st = upload(cr, &e->d_childrec)) ||
         (st = upload(P.task, &e->d_task)) || (st = upload(P.task_beg, &e->d_task_beg)) || (st = upload(P.rows, &e->d_rows)) || (st = upload(P.relind, &e->d_relind)) ||
-        (st = upload(P.children, &e->d_children)) || (st = upload(P.kpair, &e->d_kpair)) ||
-        (st = upload(P.kcontrib, &e->d_kcontrib)) || (st = upload(P.asm_dst, &e->d_asm_dst)) ||
+        (st = upload(P.children, &e->d_children)) || (st = upload(P.asm_dst, &e->d_asm_dst)) ||
         (st = upload(P.asm_src, &e->d_asm_src)) || (st = upload(P.ea_dst, &e->d_ea_dst)) ||
         (st = upload(P.wave_list, &e->d_wave_list)) || (st = upload(P.wave_hbeg, &e->d_wave_hbeg)) ||
         (st = upload(P.wg_steps, &e->d_wg_steps))) {
@@ -159,7 +157,7 @@ int plan_device(PlanEntry* e) {
         return st;
     }
     e->dev = DevPlan{P.d, P.n, P.nnode, P.nelem, (int32_t)P.fronts.size(), 0,
-                     e->d_fronts, e->d_rows, e->d_relind, e->d_children, e->d_kpair, e->d_kcontrib,
+                     e->d_fronts, e->d_rows, e->d_relind, e->d_children, 
                      e->d_asm_dst, e->d_asm_src, e->d_ea_dst, e->d_inv, e->d_childrec, e->d_wave_list, e->d_wave_hbeg,
                      (int32_t)P.wave_hbeg.size() - 1, (int32_t)P.wave_slice, e->d_wg_steps,
                      (int32_t)(P.wg_steps.size() / kStepFronts), e->d_task, e->d_task_beg,
@@ -464,7 +462,7 @@ int rve_batch_create(const rve_mesh* meshes, int64_t B, rve_batch* out) {
     L.rhs = o; o += rnd(nn * d * (d2 + 1));
     L.x = o; o += rnd(nn * d);
     L.fe = o; o += rnd(ne * nd);
-    L.ke = o; o += rnd(ne * nd * nd);
+    L.ke = o; o += rnd(ne * sym_entries(d));
     L.re = o; o += rnd(ne * nd * d2);
     L.L = o; o += rnd(Lsz);
     L.U = o; o += rnd(std::max<int64_t>(Ust, 1));

@@ -102,28 +102,6 @@ __device__ inline void block_sum(double (&v)[K], Smem& sm) {
     __syncthreads();
 }
 
-template <int D>
-__device__ inline void inv_det(const double* F, double* Fi, double& J) {
-    if (D == 2) {
-        J = F[0] * F[3] - F[1] * F[2];
-        double r = 1.0 / J;
-        Fi[0] = F[3] * r; Fi[1] = -F[1] * r; Fi[2] = -F[2] * r; Fi[3] = F[0] * r;
-    } else {
-        double c00 = F[4] * F[8] - F[5] * F[7], c01 = F[5] * F[6] - F[3] * F[8], c02 = F[3] * F[7] - F[4] * F[6];
-        J = F[0] * c00 + F[1] * c01 + F[2] * c02;
-        double r = 1.0 / J;
-        Fi[0] = c00 * r;
-        Fi[1] = (F[2] * F[7] - F[1] * F[8]) * r;
-        Fi[2] = (F[1] * F[5] - F[2] * F[4]) * r;
-        Fi[3] = c01 * r;
-        Fi[4] = (F[0] * F[8] - F[2] * F[6]) * r;
-        Fi[5] = (F[2] * F[3] - F[0] * F[5]) * r;
-        Fi[6] = c02 * r;
-        Fi[7] = (F[1] * F[6] - F[0] * F[7]) * r;
-        Fi[8] = (F[0] * F[4] - F[1] * F[3]) * r;
-    }
-}
-
 struct RveCtx {
     const DevPlan* plan;
     int d, n, ne, nn, nen, nd;
@@ -162,453 +140,701 @@ __device__ inline void zero_pinned(const RveCtx& c, double* x, int nc) {
         if (is_pinned(pl, t / (D * nc))) x[t] = 0.0;
 }
 
-// P and A = dP/dF (row-major [(i*D+J)*D*D + k*D+L]) of the St. Venant-Kirchhoff
-// law (law 1) or of the fully linear law (law 2) at F; plane strain in 2D
+// wave-uniform copies of values a non-inlined function receives in vector
+// registers: with them the compiler keeps loop bounds and addresses scalar, so
+// loops stay uniform and its wait counts across loop edges stay exact
+__device__ inline int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ inline int64_t uni(int64_t v) {
+    const uint64_t u = (uint64_t)v;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+template <typename P>
+__device__ inline P* uni(P* p) {
+    return (P*)(uintptr_t)uni((int64_t)(uintptr_t)p);
+}
+
+// Address spaces.  The large functions are not inlined into the solver kernel
+// and receive generic pointers in vector registers; these views restore what the
+// compiler cannot see: workspace pointers are wave-uniform and global (scalar
+// bases, 32-bit lane offsets, no flat instructions), the LDS is LDS, and the plan
+// is constant while the kernel runs, so wave-uniform reads of it are scalar loads.
+#define FEHMM_GLB __attribute__((address_space(1)))
+#define FEHMM_LDS __attribute__((address_space(3)))
+#define FEHMM_CST __attribute__((address_space(4)))
+template <typename T>
+__device__ inline FEHMM_GLB T* glb(T* p) {
+    return (FEHMM_GLB T*)uni((int64_t)(uintptr_t)p);
+}
+template <typename S>
+__device__ inline S load_const(const FEHMM_GLB S* p) {
+    static_assert(sizeof(S) % 4 == 0, "whole words");
+    const FEHMM_CST uint32_t* q = (const FEHMM_CST uint32_t*)uni((int64_t)p);
+    uint32_t w[sizeof(S) / 4];
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(S) / 4; ++k) w[k] = q[k];
+    S out;
+    __builtin_memcpy(&out, w, sizeof(S));
+    return out;
+}
+
+// Constitutive state at a Gauss point.  For each law the tangent has the form
+//     A_iJkL = d_ik S_JL + beta_ik d_JL + a1 M_kJ M_iL + a2 M_iJ M_kL
+// neo-Hookean:             S = mu 1, beta = 0,        M = F^-T, a1 = mu - lambda/2 (J^2 - 1), a2 = lambda J^2
+// St. Venant-Kirchhoff:    S = S(E), beta = mu F F^T, M = F,    a1 = mu,                      a2 = lambda
+// fully linear:            S = mu 1, beta = 0,        M = 1,    a1 = mu,                      a2 = lambda
+// so with v_a = M grad N_a, t_a = S grad N_a
+//     k_(a,i),(b,k) = d_ik t_a . grad N_b + beta_ik grad N_a . grad N_b + a1 v_a,k v_b,i + a2 v_a,i v_b,k
+//     Y_(a,i),(kL)  = d_ik t_a,L + beta_ik dN_a,L + a1 v_a,k M_iL + a2 v_a,i M_kL
+//     A : G         = G S + beta G + a1 M G^T M + a2 (M : G) M
+// Everything is scaled by the point's weight w|J|.
 template <int D>
-__device__ inline void law_PA(int law, double lam, double mu, const double* F, double* P, double* A) {
+struct PointState {
+    double M[D * D], S[D * D], beta[D * D], P[D * D];
+    double a1, a2;
+};
+// false where J <= 0 (or NaN); beta is set for the St. Venant-Kirchhoff law only
+template <int D>
+__device__ inline bool point_state(int law, double lam, double mu, double wJ, const double* F, PointState<D>& s) {
     constexpr int D2 = D * D;
+    double J, c[D2];  // cofactors: F^-T = c / J
+    if constexpr (D == 2) {
+        J = F[0] * F[3] - F[1] * F[2];
+        c[0] = F[3]; c[1] = -F[2]; c[2] = -F[1]; c[3] = F[0];
+    } else {
+        c[0] = F[4] * F[8] - F[5] * F[7];
+        c[1] = F[5] * F[6] - F[3] * F[8];
+        c[2] = F[3] * F[7] - F[4] * F[6];
+        c[3] = F[2] * F[7] - F[1] * F[8];
+        c[4] = F[0] * F[8] - F[2] * F[6];
+        c[5] = F[1] * F[6] - F[0] * F[7];
+        c[6] = F[1] * F[5] - F[2] * F[4];
+        c[7] = F[2] * F[3] - F[0] * F[5];
+        c[8] = F[0] * F[4] - F[1] * F[3];
+        J = F[0] * c[0] + F[1] * c[1] + F[2] * c[2];
+    }
+    if (!(J > 0.0)) return false;
+    const double mw = mu * wJ, lw = lam * wJ;
+    if (law == 0) {
+        const double r = 1.0 / J;
+        s.a1 = mw - 0.5 * lw * (J * J - 1.0);
+        s.a2 = lw * J * J;
+#pragma unroll
+        for (int q = 0; q < D2; ++q) {
+            s.M[q] = c[q] * r;
+            s.P[q] = mw * F[q] - s.a1 * s.M[q];
+            s.S[q] = (q % (D + 1)) == 0 ? mw : 0.0;
+        }
+        return true;
+    }
+    s.a1 = mw;
+    s.a2 = lw;
     if (law == 1) {
-        double S[D2], B[D2];
-        double trE = 0.0;
+        double tr = 0.0;
 #pragma unroll
         for (int I = 0; I < D; ++I)
 #pragma unroll
-            for (int J = 0; J < D; ++J) {
-                double c = 0.0, b = 0.0;
+            for (int K = 0; K < D; ++K) {
+                double g = 0.0, b = 0.0;
 #pragma unroll
                 for (int k = 0; k < D; ++k) {
-                    c += F[k * D + I] * F[k * D + J];
-                    b += F[I * D + k] * F[J * D + k];
+                    g += F[k * D + I] * F[k * D + K];
+                    b += F[I * D + k] * F[K * D + k];
                 }
-                S[I * D + J] = 0.5 * (c - (I == J ? 1.0 : 0.0));  // E for now
-                B[I * D + J] = b;
+                g = 0.5 * (g - (I == K ? 1.0 : 0.0));
+                if (I == K) tr += g;
+                s.S[I * D + K] = 2.0 * mw * g;
+                s.beta[I * D + K] = mw * b;
             }
 #pragma unroll
-        for (int I = 0; I < D; ++I) trE += S[I * D + I];
-#pragma unroll
-        for (int q = 0; q < D2; ++q) S[q] = 2.0 * mu * S[q] + ((q % (D + 1)) == 0 ? lam * trE : 0.0);
+        for (int I = 0; I < D; ++I) s.S[I * (D + 1)] += lw * tr;
 #pragma unroll
         for (int i = 0; i < D; ++i)
 #pragma unroll
-            for (int J = 0; J < D; ++J) {
+            for (int K = 0; K < D; ++K) {
                 double v = 0.0;
 #pragma unroll
-                for (int K = 0; K < D; ++K) v += F[i * D + K] * S[K * D + J];
-                P[i * D + J] = v;
+                for (int k = 0; k < D; ++k) v += F[i * D + k] * s.S[k * D + K];
+                s.P[i * D + K] = v;
+                s.M[i * D + K] = F[i * D + K];
             }
-#pragma unroll
-        for (int i = 0; i < D; ++i)
-#pragma unroll
-            for (int J = 0; J < D; ++J)
-#pragma unroll
-                for (int k = 0; k < D; ++k)
-#pragma unroll
-                    for (int L = 0; L < D; ++L)
-                        A[(i * D + J) * D2 + k * D + L] = (i == k ? S[J * D + L] : 0.0) + lam * F[i * D + J] * F[k * D + L] +
-                                                          mu * (F[i * D + L] * F[k * D + J] + (J == L ? B[i * D + k] : 0.0));
-    } else {
-        double tr = 0.0;
-#pragma unroll
-        for (int I = 0; I < D; ++I) tr += F[I * D + I] - 1.0;
-#pragma unroll
-        for (int i = 0; i < D; ++i)
-#pragma unroll
-            for (int J = 0; J < D; ++J)
-                P[i * D + J] = mu * (F[i * D + J] + F[J * D + i] - (i == J ? 2.0 : 0.0)) + (i == J ? lam * tr : 0.0);
-#pragma unroll
-        for (int i = 0; i < D; ++i)
-#pragma unroll
-            for (int J = 0; J < D; ++J)
-#pragma unroll
-                for (int k = 0; k < D; ++k)
-#pragma unroll
-                    for (int L = 0; L < D; ++L)
-                        A[(i * D + J) * D2 + k * D + L] = (i == J && k == L ? lam : 0.0) +
-                                                          mu * ((i == k && J == L ? 1.0 : 0.0) + (i == L && J == k ? 1.0 : 0.0));
+        return true;
     }
+    double tr = 0.0;
+#pragma unroll
+    for (int I = 0; I < D; ++I) tr += F[I * (D + 1)] - 1.0;
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+#pragma unroll
+        for (int K = 0; K < D; ++K) {
+            const double id = i == K ? 1.0 : 0.0;
+            s.P[i * D + K] = mw * (F[i * D + K] + F[K * D + i] - 2.0 * id) + lw * tr * id;
+            s.M[i * D + K] = id;
+            s.S[i * D + K] = mw * id;
+        }
+    return true;
 }
 
-// F at Gauss point gp of element e for nodal fluctuation w
+// t = A : g at a point
 template <int D>
-__device__ inline void gp_F(const RveCtx& c, const Smem& sm, const double* wl, int gp, double* F) {
-    constexpr int NEN = 1 << D;
+__device__ inline void point_apply(int law, const PointState<D>& s, const double* g, double* t) {
+    double mg = 0.0, h[D * D];  // M : g; h = g^T M
+#pragma unroll
+    for (int q = 0; q < D * D; ++q) mg += s.M[q] * g[q];
+    mg *= s.a2;
 #pragma unroll
     for (int i = 0; i < D; ++i)
 #pragma unroll
         for (int J = 0; J < D; ++J) {
-            double s = sm.Fbar[i * D + J];
+            double v = 0.0;
 #pragma unroll
-            for (int b = 0; b < NEN; ++b) s += wl[b * D + i] * sm.dN[(gp * 8 + b) * 3 + J];
-            F[i * D + J] = s;
+            for (int k = 0; k < D; ++k) v += g[k * D + i] * s.M[k * D + J];
+            h[i * D + J] = v;
         }
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+#pragma unroll
+        for (int J = 0; J < D; ++J) {
+            double v = mg * s.M[i * D + J], u = 0.0;
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                v += g[i * D + k] * s.S[k * D + J];
+                u += s.M[i * D + k] * h[k * D + J];
+            }
+            t[i * D + J] = v + s.a1 * u;
+        }
+    if (law == 1)
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+#pragma unroll
+            for (int J = 0; J < D; ++J)
+#pragma unroll
+                for (int k = 0; k < D; ++k) t[i * D + J] += s.beta[i * D + k] * g[k * D + J];
 }
 
+// What an element pass reads, in scalar registers (the passes are not inlined)
+struct ElemCtx {
+    int n, ne, law, npt;
+    double wJ;
+    const FEHMM_GLB uint8_t* phase;
+    const FEHMM_GLB double* lame;
+    const FEHMM_LDS double* dN;    // [point][node][3]
+    const FEHMM_LDS double* Fbar;
+    FEHMM_LDS int* flag;
+};
 template <int D>
-__device__ inline void load_wl(const RveCtx& c, const double* w, int e, double* wl, int* nodes) {
+__device__ inline ElemCtx elem_ctx(const RveCtx& c, Smem& sm) {
+    ElemCtx k;
+    k.n = uni(c.n);
+    k.ne = uni(c.ne);
+    k.law = uni(c.law);
+    k.npt = uni(c.elem) == 0 ? (1 << D) : (D == 2 ? 2 : 6);
+    k.phase = glb(c.phase);
+    k.lame = glb(c.lame);
+    k.dN = (const FEHMM_LDS double*)sm.dN;
+    k.Fbar = (const FEHMM_LDS double*)sm.Fbar;
+    k.flag = (FEHMM_LDS int*)&sm.flag;
+    k.wJ = sm.wJ;
+    return k;
+}
+
+// grid indices of node or element id (id < 2^18: the quotients are exact)
+template <int D>
+__device__ inline void grid_of(int n, int id, int* c) {
+    const float r = 1.0f / (float)n;
+#pragma unroll
+    for (int k = 0; k + 1 < D; ++k) {
+        const int q = (int)(((float)id + 0.5f) * r);
+        c[k] = id - q * n;
+        id = q;
+    }
+    c[D - 1] = id;
+}
+// nodes of element e (numbering of element_nodes, without its divisions)
+template <int D>
+__device__ inline void nodes_of_element(int n, int e, int* nodes) {
+    int c[3];
+    grid_of<D>(n, e, c);
+    int lo[3], hi[3], s = 1;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        lo[k] = c[k] * s;
+        hi[k] = (c[k] + 1 == n ? 0 : c[k] + 1) * s;
+        s *= n;
+    }
+#pragma unroll
+    for (int a = 0; a < (1 << D); ++a) {
+        int o[3];
+        local_offset(D, a, o);
+        int id = 0;
+#pragma unroll
+        for (int k = 0; k < D; ++k) id += o[k] ? hi[k] : lo[k];
+        nodes[a] = id;
+    }
+}
+// elements around node v: el[a] is the one in which v is local node a
+template <int D>
+__device__ inline void elements_of_node(int n, int v, int* el) {
+    int c[3];
+    grid_of<D>(n, v, c);
+    int lo[3], hi[3], s = 1;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        hi[k] = c[k] * s;
+        lo[k] = (c[k] == 0 ? n - 1 : c[k] - 1) * s;
+        s *= n;
+    }
+#pragma unroll
+    for (int a = 0; a < (1 << D); ++a) {
+        int o[3];
+        local_offset(D, a, o);
+        int id = 0;
+#pragma unroll
+        for (int k = 0; k < D; ++k) id += o[k] ? lo[k] : hi[k];
+        el[a] = id;
+    }
+}
+
+// Fbar + grad w of an element's nodal values at point gp; Fbar = null: grad w
+template <int D>
+__device__ inline void grad_at(const ElemCtx& k, const double* wl, int gp, bool with_Fbar, double* F) {
+#pragma unroll
+    for (int q = 0; q < D * D; ++q) F[q] = with_Fbar ? k.Fbar[q] : 0.0;
+#pragma unroll
+    for (int b = 0; b < (1 << D); ++b)
+#pragma unroll
+        for (int J = 0; J < D; ++J) {
+            const double dn = k.dN[(gp * 8 + b) * 3 + J];
+#pragma unroll
+            for (int i = 0; i < D; ++i) F[i * D + J] += wl[b * D + i] * dn;
+        }
+}
+template <int D>
+__device__ inline void nodal(const FEHMM_GLB double* x, const int* nodes, double* xl) {
+#pragma unroll
+    for (int b = 0; b < (1 << D); ++b)
+#pragma unroll
+        for (int i = 0; i < D; ++i) xl[b * D + i] = x[nodes[b] * D + i];
+}
+
+// Element residuals f and symmetric tangents at w, entry planes [entry][element]
+// (fe: rows a D + i; ke: sym_entry).  Work items: 2D (element, component i): the
+// ten k_(.,i)(.,i) and half of the sixteen k_(.,x)(.,y); 3D (element, node a): the
+// blocks of a with a .. a + 3 and, for a < 4, a + 4 (mod 8): each unordered pair of
+// nodes once.  Consecutive threads take consecutive elements, so every store is
+// contiguous.  Bound by FP64 issue and, in 3D, by registers.  Against one item per
+// (element, node[, component]) with full rows of 2^d d entries: a half (2D) to a
+// third (3D) of the Gauss-point work and half the stored entries; one pass of a
+// workgroup takes 87 instead of 190 kclk at 32 x 32 and 1.3 instead of 7 Mclk at 8^3
+// (whose accumulators were in scratch), the batch of 4096 RVEs of 32 x 32 55 instead
+// of 64 ms.
+template <int D, typename KT>
+__device__ __noinline__ void element_tangents(const RveCtx& c, Smem& sm, const double* wgen) {
     constexpr int NEN = 1 << D;
-    element_nodes(D, c.n, e, nodes);
-#pragma unroll
-    for (int b = 0; b < NEN; ++b)
-#pragma unroll
-        for (int i = 0; i < D; ++i) wl[b * D + i] = w[nodes[b] * D + i];
-}
-
-// Mode 4 (2D): one work item's share of the condensation in the stationary
-// form, sum over the element rows t of X_t^T y_t + y_t^T X_t - X_t^T (k_t X_e)
-// (the assembled Y^T X + X^T Y - X^T K X), with X [dof][ldx] at xv (zero on the
-// pinned dofs) and the FP64 tangent and Y rows of the state, into acc.
-template <int D, int RPI>
-__device__ inline void cond_item(int row0, const double (&kr)[RPI][(1 << D) * D], const double (&yr)[RPI][D * D],
-                                 const double* xv, int ldx, const int* nodes, double* acc) {
-    constexpr int NEN = 1 << D, ND = NEN * D, D2 = D * D;
-#pragma unroll
-    for (int r = 0; r < RPI; ++r) {
-        const int row = row0 + r;
-        const double* xr = xv + ((int64_t)nodes[row / D] * D + row % D) * ldx;
-        double x[D2], kx[D2];
-#pragma unroll
-        for (int g = 0; g < D2; ++g) {
-            x[g] = xr[g];
-            kx[g] = 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < ND; ++q) {
-            const double* xq = xv + ((int64_t)nodes[q / D] * D + q % D) * ldx;
-#pragma unroll
-            for (int h = 0; h < D2; ++h) kx[h] += kr[r][q] * xq[h];
-        }
-#pragma unroll
-        for (int g = 0; g < D2; ++g)
-#pragma unroll
-            for (int h = 0; h < D2; ++h) acc[g * D2 + h] += x[g] * yr[r][h] + yr[r][g] * x[h] - x[g] * kx[h];
-    }
-}
-
-// Outputs of an element pass work item (element e, rows row0 .. row0 + RPI - 1):
-// mode 0 the internal forces and tangent rows (FP32 when c.ke32, the factors'
-// input); mode 2 the Y rows and, when c.ke32, the FP64 tangent rows at the
-// converged state (the condensation's input); mode 3 the FP64 product of the
-// tangent rows with xv at the element's nodes, into the force slots.
-template <int D, int RPI>
-__device__ inline void element_store(const RveCtx& c, int e, int row0, int mode, const double (&fr)[RPI],
-                                     const double (&kr)[RPI][(1 << D) * D], const double (&yr)[RPI][D * D],
-                                     const double* xv, const int* nodes) {
-    constexpr int NEN = 1 << D, ND = NEN * D, D2 = D * D;
-    if (mode == 0) {
-#pragma unroll
-        for (int r = 0; r < RPI; ++r) {
-            const int64_t row = (int64_t)e * ND + row0 + r;
-            c.fe[row] = fr[r];
-            if (c.ke32) {
-                float* kd = reinterpret_cast<float*>(c.ke) + row * ND;
-#pragma unroll
-                for (int q = 0; q < ND; ++q) kd[q] = (float)kr[r][q];
-            } else {
-                double* kd = c.ke + row * ND;
-#pragma unroll
-                for (int q = 0; q < ND; ++q) kd[q] = kr[r][q];
-            }
-        }
-    } else if (mode == 2) {
-#pragma unroll
-        for (int r = 0; r < RPI; ++r) {
-            const int64_t row = (int64_t)e * ND + row0 + r;
-            double* yd = c.re + row * D2;
-#pragma unroll
-            for (int q = 0; q < D2; ++q) yd[q] = yr[r][q];
-            if (c.ke32) {
-                double* kd = c.ke + row * ND;
-#pragma unroll
-                for (int q = 0; q < ND; ++q) kd[q] = kr[r][q];
-            }
-        }
-    } else if (mode == 3) {
-        double xl[ND];
-#pragma unroll
-        for (int b = 0; b < NEN; ++b)
-#pragma unroll
-            for (int k = 0; k < D; ++k) xl[b * D + k] = xv[nodes[b] * D + k];
-#pragma unroll
-        for (int r = 0; r < RPI; ++r) {
-            double s = 0.0;
-#pragma unroll
-            for (int q = 0; q < ND; ++q) s += kr[r][q] * xl[q];
-            c.fe[(int64_t)e * ND + row0 + r] = s;
-        }
-    }
-}
-
-// Element pass of the St. Venant-Kirchhoff and fully linear laws: as
-// element_pass_nh, with P and A evaluated at each Gauss point (law_PA) and the rows
-// contracted with the material gradients,
-//     f_(a,i) = sum P_iJ dN_a,J w|J|,  k_(a,i),(b,k) = sum dN_a,J A_iJkL dN_b,L w|J|,
-//     Y_(a,i),(kL) = sum dN_a,J A_iJkL w|J|.
-template <int D, int NPT>
-__device__ __noinline__ void element_pass_law(const RveCtx& c, Smem& sm, const double* w, int mode, double* accP,
-                                              double* accA, const double* xv, int ldx) {
-    constexpr int NEN = 1 << D, ND = NEN * D, D2 = D * D, RPI = (D == 2) ? 2 : 1;
-    const int nitems = c.ne * NEN * (D / RPI);
-    const double wJ = sm.wJ;
-    constexpr int NCOND = D == 2 ? 16 : 1;  // mode 4 (2D): the condensation's share of this thread
-    double accC[NCOND];
-#pragma unroll
-    for (int q = 0; q < NCOND; ++q) accC[q] = 0.0;
+    const ElemCtx k = elem_ctx<D>(c, sm);
+    const FEHMM_GLB double* w = glb(wgen);
+    FEHMM_GLB double* fe = glb(c.fe);
+    FEHMM_GLB KT* ke = (FEHMM_GLB KT*)glb(c.ke);
+    const int nitems = k.ne * (D == 2 ? 2 : NEN);
     for (int it = threadIdx.x; it < nitems; it += NT) {
-        int e, a, i0;
-        if (D == 2) { e = it / NEN; a = it % NEN; i0 = 0; }
-        else { e = it / (NEN * D); a = (it / D) % NEN; i0 = it % D; }
-        if (mode == 1 && (a != 0 || i0 != 0)) continue;
-        double wl[ND];
-        int nodes[NEN];
-        load_wl<D>(c, w, e, wl, nodes);
-        const int ph = c.phase[e];
-        const double lam = c.lame[2 * ph], mu = c.lame[2 * ph + 1];
-        double kr[RPI][ND];
-        double fr[RPI];
-        double yr[RPI][D2];
-#pragma unroll
-        for (int r = 0; r < RPI; ++r) {
-            fr[r] = 0;
-#pragma unroll
-            for (int q = 0; q < ND; ++q) kr[r][q] = 0;
-#pragma unroll
-            for (int q = 0; q < D2; ++q) yr[r][q] = 0;
+        int sub, e;
+        if constexpr (D == 2) {
+            sub = it >= k.ne ? 1 : 0;
+            e = it - sub * k.ne;
+        } else {
+            sub = (int)(((float)it + 0.5f) / (float)k.ne);  // (it < 2^18)
+            e = it - sub * k.ne;
         }
-        for (int gp = 0; gp < NPT; ++gp) {
-            double F[D2], Fi[D2], J;
-            gp_F<D>(c, sm, wl, gp, F);
-            inv_det<D>(F, Fi, J);
-            if (!(J > 0.0)) { sm.flag = 1; continue; }
-            if (mode == 1) continue;
-            double Pg[D2], Ag[D2 * D2];
-            law_PA<D>(c.law, lam, mu, F, Pg, Ag);
-            if ((mode == 2 || mode == 4) && a == 0 && i0 == 0) {
+        int nodes[NEN];
+        nodes_of_element<D>(k.n, e, nodes);
+        double wl[NEN * D];
+        nodal<D>(w, nodes, wl);
+        const int ph = k.phase[e];
+        const double lam = k.lame[2 * ph], mu = k.lame[2 * ph + 1];
+        if constexpr (D == 2) {
+            double kii[10], kxy[8], f[4];
 #pragma unroll
-                for (int q = 0; q < D2; ++q) accP[q] += Pg[q] * wJ;
+            for (int q = 0; q < 10; ++q) kii[q] = 0.0;
 #pragma unroll
-                for (int q = 0; q < D2 * D2; ++q) accA[q] += Ag[q] * wJ;
-            }
-            const double* dNa = &sm.dN[(gp * 8 + a) * 3];
+            for (int q = 0; q < 8; ++q) kxy[q] = 0.0;
 #pragma unroll
-            for (int r = 0; r < RPI; ++r) {
-                const int i = i0 + r;
-                if (mode == 0) {
-                    double f = 0.0;
-#pragma unroll
-                    for (int Jj = 0; Jj < D; ++Jj) f += Pg[i * D + Jj] * dNa[Jj];
-                    fr[r] += f * wJ;
+            for (int q = 0; q < 4; ++q) f[q] = 0.0;
+#pragma unroll 1
+        for (int gp = 0; gp < k.npt; ++gp) {
+                double F[4];
+                PointState<2> s;
+                grad_at<2>(k, wl, gp, true, F);
+                if (!point_state<2>(k.law, lam, mu, k.wJ, F, s)) {
+                    *k.flag = 1;
+                    continue;
                 }
-                if (mode == 0 || mode == 3 || mode == 4 || (mode == 2 && c.ke32)) {
+                double dn[4][2], v[4][2];
 #pragma unroll
-                    for (int b = 0; b < NEN; ++b) {
-                        const double* dNb = &sm.dN[(gp * 8 + b) * 3];
+                for (int a = 0; a < 4; ++a) {
+                    dn[a][0] = k.dN[(gp * 8 + a) * 3];
+                    dn[a][1] = k.dN[(gp * 8 + a) * 3 + 1];
+                    v[a][0] = s.M[0] * dn[a][0] + s.M[1] * dn[a][1];
+                    v[a][1] = s.M[2] * dn[a][0] + s.M[3] * dn[a][1];
+                }
+                const double p0 = sub ? s.P[2] : s.P[0], p1 = sub ? s.P[3] : s.P[1];
+                double bi = 0.0, bxy = 0.0;
+                if (k.law == 1) {
+                    bi = sub ? s.beta[3] : s.beta[0];
+                    bxy = s.beta[1];
+                }
+                const double a12 = s.a1 + s.a2;
 #pragma unroll
-                        for (int k = 0; k < D; ++k) {
-                            double v = 0.0;
+                for (int a = 0; a < 4; ++a) {
+                    f[a] += p0 * dn[a][0] + p1 * dn[a][1];
+                    const double t0 = s.S[0] * dn[a][0] + s.S[1] * dn[a][1] + bi * dn[a][0];
+                    const double t1 = s.S[2] * dn[a][0] + s.S[3] * dn[a][1] + bi * dn[a][1];
+                    const double va = (sub ? v[a][1] : v[a][0]) * a12;
 #pragma unroll
-                            for (int Jj = 0; Jj < D; ++Jj)
+                    for (int b = 0; b <= a; ++b)
+                        kii[a * (a + 1) / 2 + b] += t0 * dn[b][0] + t1 * dn[b][1] + va * (sub ? v[b][1] : v[b][0]);
+                }
 #pragma unroll
-                                for (int L = 0; L < D; ++L) v += dNa[Jj] * Ag[(i * D + Jj) * D2 + k * D + L] * dNb[L];
-                            kr[r][b * D + k] += v * wJ;
-                        }
+                for (int h = 0; h < 2; ++h) {
+                    const double v0 = sub ? v[2 + h][0] : v[h][0], v1 = sub ? v[2 + h][1] : v[h][1];
+                    const double d0 = (sub ? dn[2 + h][0] : dn[h][0]) * bxy, d1 = (sub ? dn[2 + h][1] : dn[h][1]) * bxy;
+                    const double x1 = s.a1 * v1, x0 = s.a2 * v0;
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        kxy[4 * h + b] += x1 * v[b][0] + x0 * v[b][1];
+                        if (k.law == 1) kxy[4 * h + b] += d0 * dn[b][0] + d1 * dn[b][1];
                     }
                 }
-                if (mode == 2 || mode == 4) {
+            }
 #pragma unroll
-                    for (int k = 0; k < D; ++k)
+            for (int a = 0; a < 4; ++a) fe[(a * 2 + sub) * k.ne + e] = f[a];
 #pragma unroll
-                        for (int L = 0; L < D; ++L) {
-                            double v = 0.0;
+            for (int q = 0; q < 10; ++q) ke[(10 * sub + q) * k.ne + e] = (KT)kii[q];
 #pragma unroll
-                            for (int Jj = 0; Jj < D; ++Jj) v += dNa[Jj] * Ag[(i * D + Jj) * D2 + k * D + L];
-                            yr[r][k * D + L] += v * wJ;
+            for (int q = 0; q < 8; ++q) ke[(20 + 8 * sub + q) * k.ne + e] = (KT)kxy[q];
+        } else {
+            double kd[6], kb[4][9], f[3];
+#pragma unroll
+            for (int q = 0; q < 6; ++q) kd[q] = 0.0;
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+#pragma unroll
+                for (int q = 0; q < 9; ++q) kb[h][q] = 0.0;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) f[q] = 0.0;
+#pragma unroll 1
+        for (int gp = 0; gp < k.npt; ++gp) {
+                double F[9];
+                PointState<3> s;
+                grad_at<3>(k, wl, gp, true, F);
+                if (!point_state<3>(k.law, lam, mu, k.wJ, F, s)) {
+                    *k.flag = 1;
+                    continue;
+                }
+                double da[3], va[3], ta[3];
+#pragma unroll
+                for (int J = 0; J < 3; ++J) da[J] = k.dN[(gp * 8 + sub) * 3 + J];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    va[i] = s.M[3 * i] * da[0] + s.M[3 * i + 1] * da[1] + s.M[3 * i + 2] * da[2];
+                    ta[i] = s.S[3 * i] * da[0] + s.S[3 * i + 1] * da[1] + s.S[3 * i + 2] * da[2];
+                    f[i] += s.P[3 * i] * da[0] + s.P[3 * i + 1] * da[1] + s.P[3 * i + 2] * da[2];
+                }
+                const double a12 = s.a1 + s.a2;
+                {
+                    const double sd = ta[0] * da[0] + ta[1] * da[1] + ta[2] * da[2];
+                    kd[0] += sd + a12 * va[0] * va[0];
+                    kd[1] += sd + a12 * va[1] * va[1];
+                    kd[2] += sd + a12 * va[2] * va[2];
+                    kd[3] += a12 * va[0] * va[1];
+                    kd[4] += a12 * va[0] * va[2];
+                    kd[5] += a12 * va[1] * va[2];
+                    if (k.law == 1) {
+                        const double dd = da[0] * da[0] + da[1] * da[1] + da[2] * da[2];
+                        kd[0] += s.beta[0] * dd;
+                        kd[1] += s.beta[4] * dd;
+                        kd[2] += s.beta[8] * dd;
+                        kd[3] += s.beta[1] * dd;
+                        kd[4] += s.beta[2] * dd;
+                        kd[5] += s.beta[5] * dd;
+                    }
+                }
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    const int b = (sub + 1 + h) & 7;  // (h = 3 belongs to the items with sub < 4)
+                    double db[3], vb[3];
+#pragma unroll
+                    for (int J = 0; J < 3; ++J) db[J] = k.dN[(gp * 8 + b) * 3 + J];
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        vb[i] = s.M[3 * i] * db[0] + s.M[3 * i + 1] * db[1] + s.M[3 * i + 2] * db[2];
+                    const double sab = ta[0] * db[0] + ta[1] * db[1] + ta[2] * db[2];
+                    const double dab = da[0] * db[0] + da[1] * db[1] + da[2] * db[2];
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+#pragma unroll
+                        for (int l = 0; l < 3; ++l) {
+                            double t = (s.a1 * va[l]) * vb[i] + (s.a2 * va[i]) * vb[l];
+                            if (i == l) t += sab;
+                            if (k.law == 1) t += s.beta[3 * i + l] * dab;
+                            kb[h][3 * i + l] += t;
                         }
                 }
             }
-        }
-        if constexpr (D == 2) {
-            if (mode == 4) {
-                cond_item<D, RPI>(a * D + i0, kr, yr, xv, ldx, nodes, accC);
-                continue;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) fe[(sub * 3 + i) * k.ne + e] = f[i];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) ke[sym_entry(3, sub, i, sub, i) * k.ne + e] = (KT)kd[i];
+            ke[sym_entry(3, sub, 0, sub, 1) * k.ne + e] = (KT)kd[3];
+            ke[sym_entry(3, sub, 0, sub, 2) * k.ne + e] = (KT)kd[4];
+            ke[sym_entry(3, sub, 1, sub, 2) * k.ne + e] = (KT)kd[5];
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const int b = (sub + 1 + h) & 7;
+                if (h < 3 || sub < 4)
+#pragma unroll
+                    for (int q = 0; q < 9; ++q) ke[sym_entry(3, sub, q / 3, b, q % 3) * k.ne + e] = (KT)kb[h][q];
             }
         }
-        element_store<D, RPI>(c, e, a * D + i0, mode, fr, kr, yr, xv, nodes);
     }
-    if constexpr (D == 2)
-        if (mode == 4)
-#pragma unroll
-            for (int q = 0; q < NCOND; ++q) accA[q] -= accC[q];
 }
 
-// Element pass of the neo-Hookean law.  mode 0: residual + tangent rows
-// (Newton); mode 1: J > 0 check only (on w); mode 2: final outputs (Pbar, <A>,
-// Y rows); mode 3: the FP64 tangent applied to xv, matrix-free (refinement of
-// FP32 solves); mode 4 (2D): Pbar and <A> minus the condensation in the
-// stationary form with X at xv (cond_item), nothing stored.  Work item = (e, a)
-// in 2D (rows i = 0,1), (e, a, i) in 3D.
-template <int D, int NPT>
-__device__ __noinline__ void element_pass_nh(const RveCtx& c, Smem& sm, const double* w, int mode, double* accP,
-                                             double* accA, const double* xv, int ldx) {
-    constexpr int NEN = 1 << D, ND = NEN * D, RPI = (D == 2) ? 2 : 1;
-    const int nitems = c.ne * NEN * (D / RPI);
-    const double wJ = sm.wJ;
-    constexpr int NCOND = D == 2 ? 16 : 1;  // mode 4 (2D): the condensation's share of this thread
-    double accC[NCOND];
-#pragma unroll
-    for (int q = 0; q < NCOND; ++q) accC[q] = 0.0;
-    for (int it = threadIdx.x; it < nitems; it += NT) {
-        int e, a, i0;
-        if (D == 2) { e = it / NEN; a = it % NEN; i0 = 0; }
-        else { e = it / (NEN * D); a = (it / D) % NEN; i0 = it % D; }
-        if (mode == 1 && (a != 0 || i0 != 0)) continue;
-        double wl[ND];
-        int nodes[NEN];
-        load_wl<D>(c, w, e, wl, nodes);
-        const int ph = c.phase[e];
-        const double lam = c.lame[2 * ph], mu = c.lame[2 * ph + 1];
-        double kr[RPI][ND];
-        double fr[RPI];
-        double yr[RPI][D * D];
-#pragma unroll
-        for (int r = 0; r < RPI; ++r) {
-            fr[r] = 0;
-#pragma unroll
-            for (int q = 0; q < ND; ++q) kr[r][q] = 0;
-#pragma unroll
-            for (int q = 0; q < D * D; ++q) yr[r][q] = 0;
-        }
-        for (int gp = 0; gp < NPT; ++gp) {
-            double F[D * D], Fi[D * D], J;
-            gp_F<D>(c, sm, wl, gp, F);
-            inv_det<D>(F, Fi, J);
-            if (!(J > 0.0)) { sm.flag = 1; continue; }
-            if (mode == 1) continue;
-            const double c1 = mu - 0.5 * lam * (J * J - 1.0), c2 = lam * J * J;
-            if ((mode == 2 || mode == 4) && a == 0 && i0 == 0) {
-#pragma unroll
-                for (int i = 0; i < D; ++i)
-#pragma unroll
-                    for (int Jj = 0; Jj < D; ++Jj) accP[i * D + Jj] += (mu * F[i * D + Jj] - c1 * Fi[Jj * D + i]) * wJ;
-#pragma unroll
-                for (int i = 0; i < D; ++i)
-#pragma unroll
-                    for (int Jj = 0; Jj < D; ++Jj)
-#pragma unroll
-                        for (int k = 0; k < D; ++k)
-#pragma unroll
-                            for (int L = 0; L < D; ++L)
-                                accA[(i * D + Jj) * D * D + k * D + L] +=
-                                    ((i == k && Jj == L ? mu : 0.0) + c1 * Fi[Jj * D + k] * Fi[L * D + i] +
-                                     c2 * Fi[Jj * D + i] * Fi[L * D + k]) * wJ;
-            }
-            // spatial gradients g_b = F^-T grad N_b
-            double g[NEN][D];
-#pragma unroll
-            for (int b = 0; b < NEN; ++b)
-#pragma unroll
-                for (int k = 0; k < D; ++k) {
-                    double s = 0;
-#pragma unroll
-                    for (int Jj = 0; Jj < D; ++Jj) s += Fi[Jj * D + k] * sm.dN[(gp * 8 + b) * 3 + Jj];
-                    g[b][k] = s;
-                }
-            const double* dNa = &sm.dN[(gp * 8 + a) * 3];
-            double ga[D];
-#pragma unroll
-            for (int k = 0; k < D; ++k) ga[k] = 0;
-            for (int b = 0; b < NEN; ++b)
-                if (b == a)
-#pragma unroll
-                    for (int k = 0; k < D; ++k) ga[k] = g[b][k];
-#pragma unroll
-            for (int r = 0; r < RPI; ++r) {
-                const int i = i0 + r;
-                if (mode == 0) {
-                    double FdN = 0;
-#pragma unroll
-                    for (int Jj = 0; Jj < D; ++Jj) FdN += F[i * D + Jj] * dNa[Jj];
-                    fr[r] += (mu * FdN - c1 * ga[i]) * wJ;
-                }
-                if (mode == 0 || mode == 3 || mode == 4 || (mode == 2 && c.ke32)) {
-#pragma unroll
-                    for (int b = 0; b < NEN; ++b) {
-                        double dab = 0.0;
-#pragma unroll
-                        for (int k2 = 0; k2 < D; ++k2) dab += dNa[k2] * sm.dN[(gp * 8 + b) * 3 + k2];
-#pragma unroll
-                        for (int k = 0; k < D; ++k)
-                            kr[r][b * D + k] += ((i == k ? mu * dab : 0.0) + c1 * ga[k] * g[b][i] + c2 * ga[i] * g[b][k]) * wJ;
-                    }
-                }
-                if (mode == 2 || mode == 4) {
-#pragma unroll
-                    for (int k = 0; k < D; ++k)
-#pragma unroll
-                        for (int L = 0; L < D; ++L)
-                            yr[r][k * D + L] += ((i == k ? mu * dNa[L] : 0.0) + c1 * ga[k] * Fi[L * D + i] +
-                                                 c2 * ga[i] * Fi[L * D + k]) * wJ;
-                }
-            }
-        }
-        if constexpr (D == 2) {
-            if (mode == 4) {
-                cond_item<D, RPI>(a * D + i0, kr, yr, xv, ldx, nodes, accC);
-                continue;
-            }
-        }
-        element_store<D, RPI>(c, e, a * D + i0, mode, fr, kr, yr, xv, nodes);
-    }
-    if constexpr (D == 2)
-        if (mode == 4)
-#pragma unroll
-            for (int q = 0; q < NCOND; ++q) accA[q] -= accC[q];
-}
-
-// the element pass of the RVE's law (neo-Hookean closed forms, or the generic
-// path) and element kind (2^d Gauss points of Q1 / hex8, or d! P1 simplices)
+// flags sm.flag where some J <= 0 at w
 template <int D>
-__device__ inline void element_pass(const RveCtx& c, Smem& sm, const double* w, int mode, double* accP, double* accA,
-                                    const double* xv = nullptr, int ldx = 0) {
-    constexpr int NQ1 = 1 << D, NP1 = D == 2 ? 2 : 6;
-    if (c.elem == 0) {
-        if (c.law != 0) element_pass_law<D, NQ1>(c, sm, w, mode, accP, accA, xv, ldx);
-        else element_pass_nh<D, NQ1>(c, sm, w, mode, accP, accA, xv, ldx);
-    } else {
-        if (c.law != 0) element_pass_law<D, NP1>(c, sm, w, mode, accP, accA, xv, ldx);
-        else element_pass_nh<D, NP1>(c, sm, w, mode, accP, accA, xv, ldx);
+__device__ __noinline__ void element_check(const RveCtx& c, Smem& sm, const double* wgen) {
+    const ElemCtx k = elem_ctx<D>(c, sm);
+    const FEHMM_GLB double* w = glb(wgen);
+    for (int e = threadIdx.x; e < k.ne; e += NT) {
+        int nodes[1 << D];
+        nodes_of_element<D>(k.n, e, nodes);
+        double wl[(1 << D) * D];
+        nodal<D>(w, nodes, wl);
+#pragma unroll 1
+        for (int gp = 0; gp < k.npt; ++gp) {
+            double F[D * D], J;
+            grad_at<D>(k, wl, gp, true, F);
+            if constexpr (D == 2)
+                J = F[0] * F[3] - F[1] * F[2];
+            else
+                J = F[0] * (F[4] * F[8] - F[5] * F[7]) + F[1] * (F[5] * F[6] - F[3] * F[8]) +
+                    F[2] * (F[3] * F[7] - F[4] * F[6]);
+            if (!(J > 0.0)) *k.flag = 1;
+        }
     }
+}
+
+// the FP64 tangent at w applied to x, matrix-free, into the force planes (the
+// refinement residual of FP32 factors)
+template <int D>
+__device__ __noinline__ void element_apply(const RveCtx& c, Smem& sm, const double* wgen, const double* xgen) {
+    constexpr int NEN = 1 << D;
+    const ElemCtx k = elem_ctx<D>(c, sm);
+    const FEHMM_GLB double* w = glb(wgen);
+    const FEHMM_GLB double* x = glb(xgen);
+    FEHMM_GLB double* fe = glb(c.fe);
+    for (int e = threadIdx.x; e < k.ne; e += NT) {
+        int nodes[NEN];
+        nodes_of_element<D>(k.n, e, nodes);
+        double wl[NEN * D], xl[NEN * D], f[NEN * D];
+        nodal<D>(w, nodes, wl);
+        nodal<D>(x, nodes, xl);
+        const int ph = k.phase[e];
+        const double lam = k.lame[2 * ph], mu = k.lame[2 * ph + 1];
+#pragma unroll
+        for (int q = 0; q < NEN * D; ++q) f[q] = 0.0;
+#pragma unroll 1
+        for (int gp = 0; gp < k.npt; ++gp) {
+            double F[D * D], g[D * D], t[D * D];
+            PointState<D> s;
+            grad_at<D>(k, wl, gp, true, F);
+            if (!point_state<D>(k.law, lam, mu, k.wJ, F, s)) continue;
+            grad_at<D>(k, xl, gp, false, g);
+            point_apply<D>(k.law, s, g, t);
+#pragma unroll
+            for (int a = 0; a < NEN; ++a)
+#pragma unroll
+                for (int J = 0; J < D; ++J) {
+                    const double dn = k.dN[(gp * 8 + a) * 3 + J];
+#pragma unroll
+                    for (int i = 0; i < D; ++i) f[a * D + i] += t[i * D + J] * dn;
+                }
+        }
+#pragma unroll
+        for (int q = 0; q < NEN * D; ++q) fe[q * k.ne + e] = f[q];
+    }
+}
+
+// rows Y_(a,i),(kL) of every element, planes [((a D + i) D^2 + q)][element];
+// work items (element, node)
+template <int D>
+__device__ __noinline__ void element_coupling(const RveCtx& c, Smem& sm, const double* wgen) {
+    constexpr int NEN = 1 << D, D2 = D * D;
+    const ElemCtx k = elem_ctx<D>(c, sm);
+    const FEHMM_GLB double* w = glb(wgen);
+    FEHMM_GLB double* re = glb(c.re);
+    const int nitems = k.ne * NEN;
+    for (int it = threadIdx.x; it < nitems; it += NT) {
+        const int a = (int)(((float)it + 0.5f) / (float)k.ne), e = it - a * k.ne;
+        int nodes[NEN];
+        nodes_of_element<D>(k.n, e, nodes);
+        double wl[NEN * D];
+        nodal<D>(w, nodes, wl);
+        const int ph = k.phase[e];
+        const double lam = k.lame[2 * ph], mu = k.lame[2 * ph + 1];
+        double y[D][D2];
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+#pragma unroll
+            for (int q = 0; q < D2; ++q) y[i][q] = 0.0;
+#pragma unroll 1
+        for (int gp = 0; gp < k.npt; ++gp) {
+            double F[D2];
+            PointState<D> s;
+            grad_at<D>(k, wl, gp, true, F);
+            if (!point_state<D>(k.law, lam, mu, k.wJ, F, s)) continue;
+            double da[D], va[D], ta[D];
+#pragma unroll
+            for (int J = 0; J < D; ++J) da[J] = k.dN[(gp * 8 + a) * 3 + J];
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                va[i] = ta[i] = 0.0;
+#pragma unroll
+                for (int J = 0; J < D; ++J) {
+                    va[i] += s.M[i * D + J] * da[J];
+                    ta[i] += s.S[i * D + J] * da[J];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < D; ++i)
+#pragma unroll
+                for (int l = 0; l < D; ++l)
+#pragma unroll
+                    for (int L = 0; L < D; ++L) {
+                        double t = (s.a1 * va[l]) * s.M[i * D + L] + (s.a2 * va[i]) * s.M[l * D + L];
+                        if (i == l) t += ta[L];
+                        if (k.law == 1) t += s.beta[i * D + l] * da[L];
+                        y[i][l * D + L] += t;
+                    }
+        }
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+#pragma unroll
+            for (int q = 0; q < D2; ++q) re[((a * D + i) * D2 + q) * k.ne + e] = y[i][q];
+    }
+}
+
+// Averages at the converged state, this thread's share: accP = <P> and accA, the
+// lower triangle (g (g + 1) / 2 + h) of
+//   X = null:  <A>
+//   2D, X:     <(E_g - grad X_g) : A : (E_h - grad X_h)>, which is the condensed
+//              tangent <A> - Y^T X - X^T Y + X^T K X in the stationary form, with
+//              X_g the column g of X ([dof][ldx], zero on the pinned dofs) and E_g
+//              the unit macro gradients: neither Y nor K is formed.
+// Work items (element, point).
+template <int D, bool COND>
+__device__ __noinline__ void element_average(const RveCtx& c, Smem& sm, const double* wgen, double* outP, double* outA,
+                                             const double* Xgen, int ldx) {
+    constexpr int NEN = 1 << D, D2 = D * D, NA = D2 * (D2 + 1) / 2;
+    const ElemCtx k = elem_ctx<D>(c, sm);
+    const FEHMM_GLB double* w = glb(wgen);
+    double accP[D2], accA[NA];
+#pragma unroll
+    for (int q = 0; q < D2; ++q) accP[q] = 0.0;
+#pragma unroll
+    for (int q = 0; q < NA; ++q) accA[q] = 0.0;
+    const int nitems = k.ne * k.npt;
+    for (int it = threadIdx.x; it < nitems; it += NT) {
+        const int gp = (int)(((float)it + 0.5f) / (float)k.ne), e = it - gp * k.ne;
+        int nodes[NEN];
+        nodes_of_element<D>(k.n, e, nodes);
+        double wl[NEN * D], F[D2];
+        nodal<D>(w, nodes, wl);
+        const int ph = k.phase[e];
+        const double lam = k.lame[2 * ph], mu = k.lame[2 * ph + 1];
+        PointState<D> s;
+        grad_at<D>(k, wl, gp, true, F);
+        if (!point_state<D>(k.law, lam, mu, k.wJ, F, s)) continue;
+#pragma unroll
+        for (int q = 0; q < D2; ++q) accP[q] += s.P[q];
+        if constexpr (COND) {
+            const FEHMM_GLB double* X = glb(Xgen);
+            double G[D2][D2];
+#pragma unroll
+            for (int g = 0; g < D2; ++g)
+#pragma unroll
+                for (int q = 0; q < D2; ++q) G[g][q] = g == q ? 1.0 : 0.0;
+#pragma unroll
+            for (int b = 0; b < NEN; ++b)
+#pragma unroll
+                for (int i = 0; i < D; ++i)
+#pragma unroll
+                    for (int g = 0; g < D2; ++g) {
+                        const double x = X[(nodes[b] * D + i) * ldx + g];
+#pragma unroll
+                        for (int J = 0; J < D; ++J) G[g][i * D + J] -= x * k.dN[(gp * 8 + b) * 3 + J];
+                    }
+#pragma unroll
+            for (int h = 0; h < D2; ++h) {
+                double t[D2];
+                point_apply<D>(k.law, s, G[h], t);
+#pragma unroll
+                for (int g = h; g < D2; ++g)
+#pragma unroll
+                    for (int q = 0; q < D2; ++q) accA[g * (g + 1) / 2 + h] += G[g][q] * t[q];
+            }
+        } else {
+#pragma unroll
+            for (int g = 0; g < D2; ++g)
+#pragma unroll
+                for (int h = 0; h <= g; ++h) {
+                    const int i = g / D, J = g % D, l = h / D, L = h % D;
+                    double t = (s.a1 * s.M[l * D + J]) * s.M[i * D + L] + (s.a2 * s.M[i * D + J]) * s.M[l * D + L];
+                    if (i == l) t += s.S[J * D + L];
+                    if (J == L && k.law == 1) t += s.beta[i * D + l];
+                    accA[g * (g + 1) / 2 + h] += t;
+                }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < D2; ++q) outP[q] = accP[q];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) outA[q] = accA[q];
 }
 
 // out = sb * b - K x on the free dofs (0 on the pinned ones), from the element
-// products k_e x_e that element pass mode 3 left in the force slots
+// products k_e x_e that element_apply left in the force planes
 template <int D>
 __device__ void residual_act(const RveCtx& c, const double* b, double sb, double* out) {
-    constexpr int NEN = 1 << D, ND = NEN * D;
-    for (int vi = threadIdx.x; vi < c.nn * D; vi += NT) {
-        const int v = vi / D, i = vi % D;
-        double s = 0.0;
+    constexpr int NEN = 1 << D;
+    for (int v = threadIdx.x; v < c.nn; v += NT) {
+        int el[NEN];
+        elements_of_node<D>(c.n, v, el);
+        const bool pin = is_pinned(*c.plan, v);
 #pragma unroll
-        for (int a = 0; a < NEN; ++a) s += c.fe[(int64_t)element_of_node(D, c.n, v, a) * ND + a * D + i];
-        out[vi] = is_pinned(*c.plan, v) ? 0.0 : sb * b[vi] - s;
+        for (int i = 0; i < D; ++i) {
+            double s = 0.0;
+#pragma unroll
+            for (int a = 0; a < NEN; ++a) s += c.fe[(a * D + i) * c.ne + el[a]];
+            out[v * D + i] = pin ? 0.0 : sb * b[v * D + i] - s;
+        }
     }
 }
 
-// node gather of element vectors: out[(v*D+i)*ldo + q0 + col] = sum_a src[e_a(v)][(a*D+i)*nc + col]
-// (ldo = nc, q0 = 0 by default)
+// node gather of element planes src[((a D + i) nc + col)][element]:
+// out[(v D + i) ldo + q0 + col] = sum over the elements around v
 template <int D>
-__device__ void node_gather(const RveCtx& c, const double* src, int nc, double* out, double sign, int ldo = 0,
-                            int q0 = 0) {
-    constexpr int NEN = 1 << D, ND = NEN * D;
-    const int tot = c.nn * D * nc, ld = ldo > 0 ? ldo : nc;
-    for (int t = threadIdx.x; t < tot; t += NT) {
-        int col = t % nc, vi = t / nc, v = vi / D, i = vi % D;
-        double s = 0;
+__device__ void node_gather(const RveCtx& c, const double* src, int nc, double* out, int ldo, int q0) {
+    constexpr int NEN = 1 << D;
+    for (int v = threadIdx.x; v < c.nn; v += NT) {
+        int el[NEN];
+        elements_of_node<D>(c.n, v, el);
+        for (int q = 0; q < D * nc; ++q) {
+            const int i = q / nc, col = q - i * nc;
+            double s = 0.0;
 #pragma unroll
-        for (int a = 0; a < NEN; ++a) {
-            int e = element_of_node(D, c.n, v, a);
-            s += src[((int64_t)e * ND + a * D + i) * nc + col];
+            for (int a = 0; a < NEN; ++a) s += src[((a * D + i) * nc + col) * c.ne + el[a]];
+            out[(int64_t)(v * D + i) * ldo + q0 + col] = s;
         }
-        out[(int64_t)vi * ld + q0 + col] = sign * s;
     }
 }
 
@@ -813,21 +1039,6 @@ template <typename T>
 __device__ inline const __attribute__((address_space(1))) T* as_global(const T* p) {
     return (const __attribute__((address_space(1))) T*)p;
 }
-// wave-uniform copies of values a non-inlined function receives in vector
-// registers: with them the compiler keeps loop bounds and addresses scalar, so
-// loops stay uniform and its wait counts across loop edges stay exact
-__device__ inline int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ inline int64_t uni(int64_t v) {
-    const uint64_t u = (uint64_t)v;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-template <typename P>
-__device__ inline P* uni(P* p) {
-    return (P*)(uintptr_t)uni((int64_t)(uintptr_t)p);
-}
-
 // walk of the tiles: column tiles c0 = 0, TN, ...; row tiles r0 = c0, c0 + kTileM, ...
 template <int TN>
 struct TileCursor {
@@ -978,7 +1189,7 @@ __device__ __attribute__((noinline)) void tiles_update(const T* A, const T* dv, 
 template <int D, typename T>
 __device__ __attribute__((noinline)) void factorize_glb(const RveCtx& c, Smem& sm, int nrhs, T* lds) {
     typedef Mfma16<T> M;
-    constexpr int NEN = 1 << D, ND = NEN * D;
+    constexpr int NEN = 1 << D;
     const DevPlan& pl = *c.plan;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     T* W = reinterpret_cast<T*>(sm.red);  // 16 x 16
@@ -988,6 +1199,9 @@ __device__ __attribute__((noinline)) void factorize_glb(const RveCtx& c, Smem& s
     double* const cS = uni(c.S);
     PROF_T0();
     const int nfront = uni(pl.nfront);
+    const FEHMM_GLB int32_t* asm_rc = glb(pl.asm_dst);
+    const FEHMM_GLB int32_t* asm_src = glb(pl.asm_src);
+    const FEHMM_GLB T* ke = (const FEHMM_GLB T*)glb(c.ke);
     for (int s = 0; s < nfront; ++s) {
         const DevFront fr = pl.fronts[s];
         const int m = uni(fr.m), p = uni(fr.p), mu = m - p;
@@ -1010,26 +1224,30 @@ __device__ __attribute__((noinline)) void factorize_glb(const RveCtx& c, Smem& s
         }
         __syncthreads();
         // 2. original entries K(b, a) of the pivot nodes a
-        const int nk = (fr.kmap_end - fr.kmap_begin) * D * D;
-        for (int t = threadIdx.x; t < nk; t += NT) {
-            const KPair kp = pl.kpair[fr.kmap_begin + t / (D * D)];
-            const int k = (t % (D * D)) / D, l = t % D;
-            const int r = kp.row_node * D + k, col = kp.col_node * D + l;
-            if (r < col) continue;
-            // at most 2^d elements share a node pair: every contribution's loads
-            // are issued together (clamped, zeros selected; the sum order is kept)
-            KContrib cbs[NEN];
+        for (int t0 = fr.asm_begin + tid; t0 < fr.asm_end; t0 += 2 * NT) {
+            // two strides per pass, every load of both issued together
+            int rc[2], src[2][NEN];
 #pragma unroll
-            for (int q = 0; q < NEN; ++q) cbs[q] = pl.kcontrib[kp.c_begin + min(q, kp.c_count - 1)];
-            double v = 0;
+            for (int u = 0; u < 2; ++u) {
+                const int t = min(t0 + u * NT, fr.asm_end - 1);
+                rc[u] = asm_rc[t];
 #pragma unroll
-            for (int q = 0; q < NEN; ++q) {
-                const double kv = (double)ke_of<D, 1, T>(c)[((int64_t)cbs[q].elem * ND + cbs[q].lb * D + k) * ND +
-                                                         cbs[q].la * D + l];
-                v += (q < kp.c_count) ? kv : 0.0;
+                for (int q = 0; q < NEN; ++q) src[u][q] = asm_src[(int64_t)t * NEN + q];
             }
-            Fp[(int64_t)col * m + r] = (T)v;
-            if (r == col) Dg[col] = (T)v;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                double v = 0;
+#pragma unroll
+                for (int q = 0; q < NEN; ++q) {
+                    const double kv = (double)ke[max(src[u][q], 0)];
+                    v += src[u][q] >= 0 ? kv : 0.0;
+                }
+                if (t0 + u * NT < fr.asm_end) {
+                    const int r = rc[u] >> 16, col = rc[u] & 0xffff;
+                    Fp[(int64_t)col * m + r] = (T)v;
+                    if (r == col) Dg[col] = (T)v;
+                }
+            }
         }
         __syncthreads();
         // 3. extend-add of the children's update matrices and rhs updates
@@ -1362,30 +1580,6 @@ __device__ __attribute__((noinline)) void backsolve_glb(const RveCtx& c, Smem& s
 // per front), at a third of the vector unit's issue slots.  Measured against whole
 // packed fronts eliminated with a barrier per pivot, on one MI355X: 4096 RVEs of
 // 32 x 32 85.7 -> 64 ms (FP32 factors 66.7 -> 56), 14288 of 16 x 16 55.3 -> 48.5 ms.
-
-// Address spaces.  The panels' functions are not inlined into the solver kernel
-// and receive generic pointers in vector registers; these views restore what the
-// compiler cannot see: workspace pointers are wave-uniform and global (scalar
-// bases, 32-bit lane offsets, no flat instructions), the LDS is LDS, and the plan
-// is constant while the kernel runs, so wave-uniform reads of it are scalar loads.
-#define FEHMM_GLB __attribute__((address_space(1)))
-#define FEHMM_LDS __attribute__((address_space(3)))
-#define FEHMM_CST __attribute__((address_space(4)))
-template <typename T>
-__device__ inline FEHMM_GLB T* glb(T* p) {
-    return (FEHMM_GLB T*)uni((int64_t)(uintptr_t)p);
-}
-template <typename S>
-__device__ inline S load_const(const FEHMM_GLB S* p) {
-    static_assert(sizeof(S) % 4 == 0, "whole words");
-    const FEHMM_CST uint32_t* q = (const FEHMM_CST uint32_t*)uni((int64_t)p);
-    uint32_t w[sizeof(S) / 4];
-#pragma unroll
-    for (unsigned k = 0; k < sizeof(S) / 4; ++k) w[k] = q[k];
-    S out;
-    __builtin_memcpy(&out, w, sizeof(S));
-    return out;
-}
 
 // what the LDS-plan functions read of the plan and the slot, in scalar registers
 struct PanelCtx {
@@ -2289,38 +2483,54 @@ __device__ __noinline__ void forward_lds(const RveCtx& c, Smem& sm, T* F, double
     }
 }
 
-// out = b - K x with the FP64 element tangents (matrix-free), free rows only;
-// node-major [dof][NRHS]
+// out = b - K x with the stored FP64 element tangents, free rows only; node-major
+// [dof][NRHS], one node per thread
 template <int D, int NRHS>
-__device__ void residual_ke(const RveCtx& c, const double* b, const double* x, double* out) {
-    constexpr int NEN = 1 << D, ND = NEN * D;
-    const int tot = c.nn * D;
-    for (int vi = threadIdx.x; vi < tot; vi += NT) {
-        const int v = vi / D, i = vi % D;
-        double acc[NRHS];
-#pragma unroll
-        for (int q = 0; q < NRHS; ++q) acc[q] = 0.0;
+__device__ __noinline__ void residual_ke(const RveCtx& c, const double* bgen, const double* xgen, double* ogen) {
+    constexpr int NEN = 1 << D;
+    const int n = uni(c.n), ne = uni(c.ne), nn = uni(c.nn);
+    const FEHMM_GLB double* b = glb(bgen);
+    const FEHMM_GLB double* x = glb(xgen);
+    const FEHMM_GLB double* ke = glb(c.ke);
+    FEHMM_GLB double* out = glb(ogen);
+    for (int v = threadIdx.x; v < nn; v += NT) {
         const bool pin = is_pinned(*c.plan, v);
-        if (!pin) {
+        int el[NEN];
+        elements_of_node<D>(n, v, el);
+        double acc[D][NRHS];
 #pragma unroll
-            for (int a = 0; a < NEN; ++a) {
-                const int e = element_of_node(D, c.n, v, a);
-                int nodes[NEN];
-                element_nodes(D, c.n, e, nodes);
-                const double* kr = c.ke + ((int64_t)e * ND + a * D + i) * ND;
+        for (int i = 0; i < D; ++i)
 #pragma unroll
-                for (int bb = 0; bb < NEN; ++bb)
+            for (int q = 0; q < NRHS; ++q) acc[i][q] = 0.0;
+        // (a rolled loop over the 2^d elements: a is uniform, so the entry planes
+        // are scalar)
+#pragma unroll 1
+        for (int a = 0; a < NEN; ++a) {
+            int e = 0;
 #pragma unroll
-                    for (int k = 0; k < D; ++k) {
-                        const double kv = kr[bb * D + k];
-                        const double* xr = x + ((int64_t)nodes[bb] * D + k) * NRHS;
+            for (int h = 0; h < NEN; ++h) e = h == a ? el[h] : e;
+            int nodes[NEN];
+            nodes_of_element<D>(n, e, nodes);
 #pragma unroll
-                        for (int q = 0; q < NRHS; ++q) acc[q] += kv * xr[q];
+            for (int bb = 0; bb < NEN; ++bb)
+#pragma unroll
+                for (int k = 0; k < D; ++k) {
+                    double xr[NRHS];
+#pragma unroll
+                    for (int q = 0; q < NRHS; ++q) xr[q] = x[(nodes[bb] * D + k) * NRHS + q];
+#pragma unroll
+                    for (int i = 0; i < D; ++i) {
+                        const double kv = ke[sym_entry(D, a, i, bb, k) * ne + e];
+#pragma unroll
+                        for (int q = 0; q < NRHS; ++q) acc[i][q] += kv * xr[q];
                     }
-            }
+                }
         }
 #pragma unroll
-        for (int q = 0; q < NRHS; ++q) out[(int64_t)vi * NRHS + q] = pin ? 0.0 : b[(int64_t)vi * NRHS + q] - acc[q];
+        for (int i = 0; i < D; ++i)
+#pragma unroll
+            for (int q = 0; q < NRHS; ++q)
+                out[(v * D + i) * NRHS + q] = pin ? 0.0 : b[(v * D + i) * NRHS + q] - acc[i][q];
     }
 }
 
@@ -2478,7 +2688,8 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
         PROF_T0();
         while (status == 0) {
             PROF_RESET();
-            element_pass<D>(c, sm, c.w, 0, nullptr, nullptr);
+            if constexpr (IR) element_tangents<D, float>(c, sm, c.w);
+            else element_tangents<D, double>(c, sm, c.w);
             __syncthreads();
             PROF_MARK(PH_ELEM);
             if (sm.flag) {
@@ -2495,7 +2706,7 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                 status = 2;
                 break;
             }
-            node_gather<D>(c, c.fe, 1, c.R, 1.0);
+            node_gather<D>(c, c.fe, 1, c.R, 1, 0);
             __syncthreads();
             const double rn = sqrt(free_norm2<D>(c, sm, c.R));
             PROF_MARK(PH_GATHER);
@@ -2511,18 +2722,9 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
             rprev = rn;
             if constexpr (NSPEC <= kMaxNrhs) {
                 if (spec) {
-                    // Y rows of this state: element pass mode 2 with the FP64
-                    // tangent rows off (the factor-type tangents stay in place)
-                    RveCtx cy = c;
-                    cy.ke32 = 0;
-                    double dP[D2], dA[D2 * D2];
-#pragma unroll
-                    for (int q = 0; q < D2; ++q) dP[q] = 0;
-#pragma unroll
-                    for (int q = 0; q < D2 * D2; ++q) dA[q] = 0;
-                    element_pass<D>(cy, sm, c.w, 2, dP, dA);
+                    element_coupling<D>(c, sm, c.w);
                     __syncthreads();
-                    node_gather<D>(c, c.re, D2, c.rhs, 1.0, NSPEC, 1);
+                    node_gather<D>(c, c.re, D2, c.rhs, NSPEC, 1);
                     for (int t = threadIdx.x; t < ndof; t += NT) c.rhs[(int64_t)t * NSPEC] = -c.R[t];
                     __syncthreads();
                     if (!c.plan->lds_ok) factorize_glb<D, T>(c, sm, NSPEC, dynF);
@@ -2556,9 +2758,9 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
             PROF_MARK(PH_BACK);
             if constexpr (IR) {
                 // refinement against the FP64 tangent: dx = K32^-1 (b - K64 x), with
-                // K64 x computed matrix-free by the element pass in FP64
+                // K64 x computed matrix-free from the elements in FP64
                 for (int ref = 0; ref < a.ir_max; ++ref) {
-                    element_pass<D>(c, sm, c.w, 3, nullptr, nullptr, c.x);
+                    element_apply<D>(c, sm, c.w, c.x);
                     __syncthreads();
                     residual_act<D>(c, c.R, -1.0, ir1);  // b = -R
                     __syncthreads();
@@ -2582,7 +2784,7 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                 for (int t = threadIdx.x; t < ndof; t += NT) c.wt[t] = c.w[t] + alpha * c.x[t];
                 if (threadIdx.x == 0) sm.flag = 0;
                 __syncthreads();
-                element_pass<D>(c, sm, c.wt, 1, nullptr, nullptr);
+                element_check<D>(c, sm, c.wt);
                 __syncthreads();
                 const int bad = sm.flag;
                 __syncthreads();
@@ -2609,24 +2811,34 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
             // the average tangent itself (mode 4)
             const bool stale = Aout && spec && !capped && rprev <= 1e-4 * r0;
             const bool stale2 = stale && D == 2;
-            double accP[D2], accA[D2 * D2];
-#pragma unroll
-            for (int q = 0; q < D2; ++q) accP[q] = 0;
-#pragma unroll
-            for (int q = 0; q < D2 * D2; ++q) accA[q] = 0;
-            element_pass<D>(c, sm, c.w, stale2 ? 4 : 2, accP, accA, stale2 ? c.rhs + 1 : nullptr, NSPEC);
+            constexpr int NA = D2 * (D2 + 1) / 2;  // lower triangle of a symmetric d^2 x d^2
+            double accP[D2], accA[NA];
+            if constexpr (D == 2) {
+                if (stale2) element_average<D, true>(c, sm, c.w, accP, accA, c.rhs + 1, NSPEC);
+                else element_average<D, false>(c, sm, c.w, accP, accA, nullptr, 0);
+            } else {
+                element_average<D, false>(c, sm, c.w, accP, accA, nullptr, 0);
+            }
+            if (Aout && !stale2) element_coupling<D>(c, sm, c.w);
+            // entry (threadIdx.x / d^2, threadIdx.x % d^2) of such a triangle
+            const int sym_g = threadIdx.x / D2, sym_h = threadIdx.x % D2;
+            const int sym_at = max(sym_g, sym_h) * (max(sym_g, sym_h) + 1) / 2 + min(sym_g, sym_h);
             __syncthreads();
             block_sum<D2>(accP, sm);
             if (threadIdx.x < D2) Pout[threadIdx.x] = sm.outv[threadIdx.x];
             __syncthreads();
             if (Aout && stale2) {
-                block_sum<D2 * D2>(accA, sm);
-                if (threadIdx.x < D2 * D2) Aout[threadIdx.x] = sm.outv[threadIdx.x];
+                block_sum<NA>(accA, sm);
+                if (threadIdx.x < D2 * D2) Aout[threadIdx.x] = sm.outv[sym_at];
                 __syncthreads();
             } else if (Aout) {
-                block_sum<D2 * D2>(accA, sm);
-                double Aavg = threadIdx.x < D2 * D2 ? sm.outv[threadIdx.x] : 0.0;
+                block_sum<NA>(accA, sm);
+                double Aavg = threadIdx.x < D2 * D2 ? sm.outv[sym_at] : 0.0;
                 __syncthreads();
+                if (c.ke32) {  // the FP64 tangents of w for the condensation
+                    element_tangents<D, double>(c, sm, c.w);
+                    __syncthreads();
+                }
                 // otherwise (3D) the stationary form assembled below, refined
                 // while ||Y - K X||_F > 1e-4 ||Y||_F (at most twice), or a
                 // factorization at w: FP64 (direct Schur form below, no
@@ -2637,7 +2849,7 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                 // beside X (ir2), X then moved into the element-Y slots
                 double* const Y = stale ? ir2 : c.rhs;
                 double* const X = c.re;  // [dof][D2] once the element Y rows are gathered
-                node_gather<D>(c, c.re, D2, Y, 1.0);
+                node_gather<D>(c, c.re, D2, Y, D2, 0);
                 __syncthreads();
                 if constexpr (NSPEC <= kMaxNrhs) {
                     if (stale) {
@@ -2772,9 +2984,9 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_assembly_kernel(SolveArgs a)
         const double* wst = a.wstate ? a.wstate + a.state_off[rve] : nullptr;
         for (int t = threadIdx.x; t < ndof; t += NT) c.w[t] = (wst && !is_pinned(*c.plan, t / D)) ? wst[t] : 0.0;
         __syncthreads();
-        element_pass<D>(c, sm, c.w, 0, nullptr, nullptr);
+        element_tangents<D, double>(c, sm, c.w);
         __syncthreads();
-        node_gather<D>(c, c.fe, 1, c.R, 1.0);
+        node_gather<D>(c, c.fe, 1, c.R, 1, 0);
         if (threadIdx.x == 0 && a.status) a.status[rve] = sm.flag ? 2 : 0;
         __syncthreads();
     }

@@ -7,7 +7,7 @@
 namespace fehmm {
 
 struct DevFront {
-    int32_t m, p, parent, child_begin, child_end, kmap_begin, kmap_end, asm_begin, asm_end, u_lds;
+    int32_t m, p, parent, child_begin, child_end, asm_begin, asm_end, u_lds;
     int64_t rows_off, relind_off, L_off, D_off, y_off, U_off, ea_off;
 };
 
@@ -24,8 +24,6 @@ struct DevPlan {
     const int32_t* rows;
     const int32_t* relind;
     const int32_t* children;
-    const KPair* kpair;
-    const KContrib* kcontrib;
     const int32_t* asm_dst;
     const int32_t* asm_src;
     const int32_t* ea_dst;
