@@ -413,6 +413,13 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
             F.npre = npiv * mc - npiv * (npiv - 1) / 2;
         }
         int maxh = 0;
+        // the backward substitution also keeps the pivot triangle beside its scratch
+        // where four waves' slices stay within the wave phase's budget
+        int64_t bs_fit = 0;
+        auto bs_want = [&](const FrontHost& X, int nw) {
+            const int64_t all = (rhs_cols * (X.m + (X.m > X.p ? nw : 0) * (int64_t)X.p) + (int64_t)X.p * (X.p + 1) / 2 + nw - 1) / nw;
+            if (kSolveWaves * all <= kWaveElemsMax) bs_fit = std::max(bs_fit, all);
+        };
         for (int s = 0; s < ns; ++s) {
             FrontHost& F = P.fronts[s];
             F.wave = F.m <= prm.wave_max_m ? 1 : 0;
@@ -425,7 +432,7 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
             if (F.wave) {
                 maxh = std::max(maxh, F.height);
                 P.wave_slice = std::max<int64_t>(P.wave_slice, packed_panel(F) + block_rhs);
-                P.bs_slice = std::max<int64_t>(P.bs_slice, rhs_cols * (F.m + F.p));
+                P.bs_slice = std::max<int64_t>(P.bs_slice, 4 * (rhs_cols * kWaveFrontMaxM + 4));
             }
         }
         for (int h = 0; h <= maxh; ++h) {
@@ -560,16 +567,19 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
                 }
                 for (int k = 0; k < kStepFronts; ++k) P.wg_steps.push_back(k < (int)grp.size() ? grp[k] : -1);
                 // (the kernel runs a step's fronts on one or two thread groups)
-                const int ng = std::min<int>((int)grp.size(), kStepGroups), nw = kSolveWaves / ng;
+                // (the backward substitution takes a four-front step one front per wave)
+                const int ng = std::min<int>((int)grp.size(), kStepGroups), nw = kSolveWaves / (int)grp.size();
                 int64_t need = 0;
                 for (int f : grp) {
                     need = std::max(need, packed_panel(P.fronts[f]) + block_rhs);
                     P.bs_slice = std::max<int64_t>(
                         P.bs_slice, (rhs_cols * (P.fronts[f].m + nw * (int64_t)P.fronts[f].p) + nw - 1) / nw);
+                    bs_want(P.fronts[f], nw);
                 }
                 P.wg_elems = std::max(P.wg_elems, ng * need);
             }
         }
+        P.bs_slice = std::max(P.bs_slice, bs_fit);
     }
     return P;
 }

@@ -63,7 +63,7 @@ struct PlanEntry {
     int32_t *d_task = nullptr, *d_task_beg = nullptr;
     int32_t* d_asm_src = nullptr;
     int32_t* d_ea_dst = nullptr;
-    int32_t* d_wave_list = nullptr;
+    BackRec* d_back = nullptr;
     int32_t* d_wave_hbeg = nullptr;
     int32_t* d_wg_steps = nullptr;
     int refs = 0;
@@ -105,7 +105,7 @@ void free_plan_dev(PlanEntry& e) {
     (void)hipFree(e.d_children); 
     (void)hipFree(e.d_asm_dst); (void)hipFree(e.d_inv); (void)hipFree(e.d_childrec); (void)hipFree(e.d_task); (void)hipFree(e.d_task_beg);
     (void)hipFree(e.d_asm_src); (void)hipFree(e.d_ea_dst);
-    (void)hipFree(e.d_wave_list); (void)hipFree(e.d_wave_hbeg); (void)hipFree(e.d_wg_steps);
+    (void)hipFree(e.d_back); (void)hipFree(e.d_wave_hbeg); (void)hipFree(e.d_wg_steps);
     e.d_fronts = nullptr;
 }
 
@@ -139,26 +139,31 @@ int plan_device(PlanEntry* e) {
     for (size_t s = 0; s < fr.size(); ++s) {
         const FrontHost& f = P.fronts[s];
         fr[s] = DevFront{f.m, f.p, f.parent, f.child_begin, f.child_end, f.asm_begin,
-                         f.asm_end, f.u_lds, f.rows_off, f.relind_off, f.L_off, f.D_off, f.y_off, f.U_off, f.ea_off};
+                         f.asm_end, f.u_lds, f.wave, 0, f.rows_off, f.relind_off, f.L_off, f.D_off, f.y_off, f.U_off, f.ea_off};
     }
     std::vector<DevChild> cr(P.children.size());
     for (size_t q = 0; q < cr.size(); ++q) {
         const FrontHost& f = P.fronts[P.children[q]];
         cr[q] = DevChild{f.m - f.p, f.npre, f.u_lds, 0, f.ea_off, f.inv_off, f.U_off};
     }
+    std::vector<BackRec> back;
+    for (int32_t k : P.wave_list) {
+        const FrontHost& f = P.fronts[k];
+        back.push_back(BackRec{f.m, f.p, (int32_t)f.rows_off, (int32_t)f.L_off, (int32_t)f.D_off, (int32_t)f.y_off});
+    }
     int st;
     if ((st = upload(fr, &e->d_fronts)) || (st = upload(P.inv, &e->d_inv)) || (st = upload(cr, &e->d_childrec)) ||
         (st = upload(P.task, &e->d_task)) || (st = upload(P.task_beg, &e->d_task_beg)) || (st = upload(P.rows, &e->d_rows)) || (st = upload(P.relind, &e->d_relind)) ||
         (st = upload(P.children, &e->d_children)) || (st = upload(P.asm_dst, &e->d_asm_dst)) ||
         (st = upload(P.asm_src, &e->d_asm_src)) || (st = upload(P.ea_dst, &e->d_ea_dst)) ||
-        (st = upload(P.wave_list, &e->d_wave_list)) || (st = upload(P.wave_hbeg, &e->d_wave_hbeg)) ||
+        (st = upload(back, &e->d_back)) || (st = upload(P.wave_hbeg, &e->d_wave_hbeg)) ||
         (st = upload(P.wg_steps, &e->d_wg_steps))) {
         free_plan_dev(*e);
         return st;
     }
     e->dev = DevPlan{P.d, P.n, P.nnode, P.nelem, (int32_t)P.fronts.size(), 0,
                      e->d_fronts, e->d_rows, e->d_relind, e->d_children, 
-                     e->d_asm_dst, e->d_asm_src, e->d_ea_dst, e->d_inv, e->d_childrec, e->d_wave_list, e->d_wave_hbeg,
+                     e->d_asm_dst, e->d_asm_src, e->d_ea_dst, e->d_inv, e->d_childrec, e->d_back, e->d_wave_hbeg,
                      (int32_t)P.wave_hbeg.size() - 1, (int32_t)P.wave_slice, e->d_wg_steps,
                      (int32_t)(P.wg_steps.size() / kStepFronts), e->d_task, e->d_task_beg,
                      std::max<int32_t>((int32_t)P.task_beg.size() - 1, 0), (int32_t)P.ul_base, (int32_t)P.ul_stride, 0};

@@ -42,7 +42,7 @@ namespace fehmm {
 
 constexpr int NWAVE = kSolveWaves;
 constexpr int NT = 64 * NWAVE;
-static_assert(NT / 128 == kStepGroups, "thread groups of a step");
+static_assert(NT / 128 == kStepGroups && NWAVE == kStepFronts, "thread groups of a step");
 
 // Optional per-phase clock accounting (slot 0, thread 0), compiled in only
 // with -DFEHMM_PHASE_PROF=1; the default build records nothing.
@@ -1585,7 +1585,8 @@ __device__ __attribute__((noinline)) void backsolve_glb(const RveCtx& c, Smem& s
 struct PanelCtx {
     const FEHMM_GLB DevFront* fronts;
     const FEHMM_GLB DevChild* childrec;
-    const FEHMM_GLB int32_t *rows, *asm_dst, *asm_src, *ea_dst, *inv, *wave_list, *wave_hbeg, *wg_steps, *task, *task_beg;
+    const FEHMM_GLB int32_t *rows, *asm_dst, *asm_src, *ea_dst, *inv, *wave_hbeg, *wg_steps, *task, *task_beg;
+    const FEHMM_GLB BackRec* back;
     int nwave_h, nwg_steps, ntask_lev, ul_base, ul_stride, wave_slice;
     FEHMM_GLB double *L, *U;
 };
@@ -1599,7 +1600,7 @@ __device__ inline PanelCtx panel_ctx(const RveCtx& c) {
     k.asm_src = glb(pl.asm_src);
     k.ea_dst = glb(pl.ea_dst);
     k.inv = glb(pl.inv);
-    k.wave_list = glb(pl.wave_list);
+    k.back = glb(pl.back);
     k.wave_hbeg = glb(pl.wave_hbeg);
     k.wg_steps = glb(pl.wg_steps);
     k.task = glb(pl.task);
@@ -2112,13 +2113,32 @@ __device__ inline void front_lds(const PanelCtx& pl, const FEHMM_GLB KeType<D, N
 #pragma unroll
         for (int q = 0; q < NRHS; ++q) (pl.L + fr.y_off)[q * p + i] = (double)b[q];
     }
-    for (int t0 = gt; t0 < lp; t0 += 8 * GT) {
-        T v[8];
+    if constexpr (WAVE) {
+        // row-major [m][p]: sixteen columns of four rows at a time (what one pass of
+        // backsolve_rows reads); entries above the diagonal are some panel entry
+        const int lg = lane >> 4;
+        for (int j0 = 0; j0 < p; j0 += 16) {
+            const int j = min(j0 + l15, p - 1), cj = cpkv(j, m) - j;
+            for (int r0 = j0; r0 < m; r0 += 16) {
+                T v[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = F[min(t0 + u * GT, lp - 1)];
+                for (int u = 0; u < 4; ++u) v[u] = F[cj + max(min(r0 + 4 * u + lg, m - 1), j)];
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (t0 + u * GT < lp) Lg[t0 + u * GT] = v[u];
+                for (int u = 0; u < 4; ++u) {
+                    const int r = r0 + 4 * u + lg;
+                    if (r < m && j0 + l15 < p) Lg[r * p + j] = v[u];
+                }
+            }
+        }
+    } else {
+        for (int t0 = gt; t0 < lp; t0 += 8 * GT) {
+            T v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = F[min(t0 + u * GT, lp - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (t0 + u * GT < lp) Lg[t0 + u * GT] = v[u];
+        }
     }
     if (mu > 0) {
         auto update_out = [&](auto dst) {
@@ -2185,17 +2205,63 @@ __device__ __noinline__ void factorize_lds(const RveCtx& c, Smem& sm, T* Fgen) {
     }
 }
 
+// 16-pivot blocks of L11^T v = v from the last, by one wave: each rhs column's chain
+// in a 16-lane row with DPP broadcasts, then all lanes fold the block into the
+// earlier pivots.  L(i, j) at tri[col(j) + i - j].
+template <int NRHS, typename Tri, typename Col>
+__device__ inline void back_triangle(const Tri* tri, Col col, FEHMM_LDS double* v, int p) {
+    const int lane = threadIdx.x & 63, l15 = lane & 15, lg = lane >> 4;
+    for (int K = 16 * ((p - 1) >> 4); K >= 0; K -= 16) {
+        const int kb = min(16, p - K);
+        // block triangle: L(K + cc, K + l15), cc > l15
+        const int jl = min(l15, kb - 1), cl = col(K + jl) - jl;
+        double Lr[16];
+#pragma unroll
+        for (int cc = 1; cc < 16; ++cc)
+            Lr[cc] = (double)tri[cl + min(max(cc, jl), kb - 1)] * ((cc < kb && cc > l15) ? 1.0 : 0.0);
+        // one rhs column per 16-lane row
+#pragma unroll
+        for (int q0 = 0; q0 < NRHS; q0 += 4) {
+            const int q = min(q0 + lg, NRHS - 1);
+            double vv = v[q * p + K + jl];
+            static_for<0, 15>([&](auto C) {
+                constexpr int cc = 15 - decltype(C)::value;
+                if (cc < kb) vv -= Lr[cc] * row_bcast<cc>(vv);
+            });
+            if (l15 < kb && q0 + lg < NRHS) v[q * p + K + l15] = vv;
+        }
+        front_sync<true>();
+        // the block's rows of the earlier columns
+        for (int j0 = 0; j0 < K; j0 += 64) {
+            const int j = min(j0 + lane, K - 1), cj = col(j) + K - j;
+            double lk[16];
+#pragma unroll
+            for (int cc = 0; cc < 16; ++cc) lk[cc] = (double)tri[cj + min(cc, kb - 1)] * (cc < kb ? 1.0 : 0.0);
+#pragma unroll
+            for (int q = 0; q < NRHS; ++q) {
+                double acc = v[q * p + j];
+#pragma unroll
+                for (int cc = 0; cc < 16; ++cc) acc -= lk[cc] * v[q * p + K + min(cc, kb - 1)];
+                if (j0 + lane < K) v[q * p + j] = acc;
+            }
+        }
+        front_sync<true>();
+    }
+}
+
 // Backward substitution of one front s (threads gt, waves gw as in front_lds):
 //   v = D^-1 y - L21^T x_u on FP64 MFMA (16 pivots x 4 update rows x up to 16 rhs
-//   columns; L read from global memory once, the update rows split over the
-//   waves, their partial sums added in wave order), then the unit triangle in
-//   16-pivot blocks from the last by the first wave: each rhs column's chain in a
-//   16-lane row with DPP broadcasts, earlier pivots folded by all lanes.
-// vb: FP64 scratch, [NRHS][p] pivot values, [NRHS][mu] update rows' solution and
-// [nw][NRHS][p] partial sums.
+//   columns; L21 read from global memory once, the update rows split over the
+//   waves, their partial sums added in wave order), then the unit triangle by the
+//   first wave (back_triangle) from a copy of L11 in LDS.  Bound by latency: the
+//   triangle's copy, the first products' operands, D, y and the row numbers are all
+//   requested before the first wait, so a front is two memory round trips.
+// vb: FP64 scratch of `cap` doubles: [NRHS][p] pivot values, [NRHS][mu] update rows'
+// solution, [nw][NRHS][p] partial sums, then the packed triangle where it fits (else
+// it is read from global memory).
 template <int D, int NRHS, typename T, bool WAVE>
-__device__ inline void backsolve_front(const PanelCtx& pl, int s, FEHMM_LDS double* vb, FEHMM_GLB double* x, int gt, int GT,
-                                       int gw, int nw) {
+__device__ inline void backsolve_front(const PanelCtx& pl, int s, FEHMM_LDS double* vb, int cap, FEHMM_GLB double* x,
+                                       int gt, int GT, int gw, int nw) {
     typedef Mfma16<double> M;
     const int lane = threadIdx.x & 63, l15 = lane & 15, lg = lane >> 4;
     const DevFront fr = load_const(pl.fronts + s);
@@ -2204,46 +2270,83 @@ __device__ inline void backsolve_front(const PanelCtx& pl, int s, FEHMM_LDS doub
     const FEHMM_GLB T* Lg = (const FEHMM_GLB T*)(pl.L + fr.L_off);
     const FEHMM_GLB double* Dg = pl.L + fr.D_off;
     const FEHMM_GLB double* yg = pl.L + fr.y_off;
-    FEHMM_LDS double* v = vb;                  // [NRHS][p]
-    FEHMM_LDS double* xs = vb + NRHS * p;      // [NRHS][mu]
-    FEHMM_LDS double* part = vb + NRHS * m;    // [nw][NRHS][p]
-    for (int j = gt; j < p; j += GT) {
-        const double rd = 1.0 / Dg[j];
+    const int npart = mu > 0 ? nw : 0;
+    FEHMM_LDS double* v = vb;                // [NRHS][p]
+    FEHMM_LDS double* xs = vb + NRHS * p;    // [NRHS][mu]
+    FEHMM_LDS double* part = vb + NRHS * m;  // [npart][NRHS][p]
+    const int scratch = NRHS * (m + npart * p), ntri = p * (p + 1) / 2;
+    FEHMM_LDS T* tri = (FEHMM_LDS T*)(vb + scratch);
+    const bool staged = scratch + (ntri * (int)sizeof(T) + 7) / 8 <= cap;
+    // one row and one pivot per thread first (m <= GT but for four-front steps)
+    const int r0 = mu > 0 ? rows[p + min(gt, mu - 1)] : 0;
+    const int jp = min(gt, p - 1);
+    const double d0 = Dg[jp];
+    double y0[NRHS];
 #pragma unroll
-        for (int q = 0; q < NRHS; ++q) v[q * p + j] = yg[q * p + j] * rd;
+    for (int q = 0; q < NRHS; ++q) y0[q] = yg[q * p + jp];
+    // the products' first operands: tile 0, the first eight of this wave's k-steps
+    const int nks = (mu + 3) >> 2;
+    T a[8];
+    auto a_load = [&](int t, int k0) {
+        const int j = min(16 * t + l15, p - 1), col = cpkv(j, m) - j + p;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] = Lg[col + min(4 * (k0 + u * nw) + lg, mu - 1)];
+    };
+    if (mu > 0) a_load(0, gw);
+    if (staged) {  // columns of the triangle, wave by wave, eight columns in flight
+        for (int jb = gw; jb < p; jb += 8 * nw) {
+            T c[8][2];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int j = min(jb + u * nw, p - 1), cj = cpk(j, m) - j;
+                c[u][0] = Lg[cj + min(j + lane, p - 1)];
+                if (p > 64) c[u][1] = Lg[cj + min(j + lane + 64, p - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int j = jb + u * nw;
+                if (j < p) {
+                    const int cj = cpk(j, p) - j;
+                    if (j + lane < p) tri[cj + j + lane] = c[u][0];
+                    if (p > 64 && j + lane + 64 < p) tri[cj + j + lane + 64] = c[u][1];
+                }
+            }
+        }
     }
+    if (gt < p)
+#pragma unroll
+        for (int q = 0; q < NRHS; ++q) v[q * p + gt] = y0[q] / d0;
+    for (int j = gt + GT; j < p; j += GT)
+#pragma unroll
+        for (int q = 0; q < NRHS; ++q) v[q * p + j] = yg[q * p + j] / Dg[j];
     for (int i = gt; i < mu; i += GT) {
-        const int xr = rows[p + i] * NRHS;
+        const int xr = (i == gt ? r0 : rows[p + i]) * NRHS;
 #pragma unroll
         for (int q = 0; q < NRHS; ++q) xs[q * mu + i] = x[xr + q];
     }
     front_sync<WAVE>();
     if (mu > 0) {
-        const int nks = (mu + 3) >> 2;
         for (int t = 0; 16 * t < p; ++t) {
-            const int j = min(16 * t + l15, p - 1);
-            const int col = cpkv(j, m) - j + p;
-            M::V acc = M::zero();
+            M::V acc[2] = {M::zero(), M::zero()};
             for (int k0 = gw; k0 < nks; k0 += 8 * nw) {
-                T a[8];
+                if (t > 0 || k0 != gw) a_load(t, k0);
                 double bx[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const int i = 4 * (k0 + u * nw) + lg;
-                    a[u] = Lg[col + min(i, mu - 1)];
                     bx[u] = xs[(NRHS == 1 ? 0 : min(l15, NRHS - 1) * mu) + min(i, mu - 1)];
                     bx[u] *= (i < mu && l15 < NRHS) ? 1.0 : 0.0;
                 }
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    if (k0 + u * nw < nks) acc = M::mma((double)a[u], bx[u], acc);
+                    if (k0 + u * nw < nks) acc[u & 1] = M::mma((double)a[u], bx[u], acc[u & 1]);
             }
-            // result element v of lane: pivot 16 t + lg + 4 v, rhs column l15
+            // result element e of lane: pivot 16 t + row(lane, e), rhs column l15
             if (l15 < NRHS)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int jj = 16 * t + M::row(lane, e);
-                    if (jj < p) part[(gw * NRHS + l15) * p + jj] = acc[e];
+                    if (jj < p) part[(gw * NRHS + l15) * p + jj] = acc[0][e] + acc[1][e];
                 }
         }
         front_sync<WAVE>();
@@ -2255,53 +2358,8 @@ __device__ inline void backsolve_front(const PanelCtx& pl, int s, FEHMM_LDS doub
         front_sync<WAVE>();
     }
     if (gw == 0) {
-        for (int K = 16 * ((p - 1) >> 4); K >= 0; K -= 16) {
-            const int kb = min(16, p - K);
-            // block triangle: L(K + cc, K + l15), cc > l15
-            double Lr[16];
-            {
-                const int col = cpkv(K + min(l15, kb - 1), m) - min(l15, kb - 1);
-#pragma unroll
-                for (int cc = 1; cc < 16; ++cc)
-                    Lr[cc] = (double)Lg[col + min(max(cc, l15), kb - 1)] * ((cc < kb && cc > l15) ? 1.0 : 0.0);
-            }
-            // the block's rows of the earlier columns j = lane (+ 64)
-            T lk[16];
-            const int j0 = min(lane, max(K - 1, 0));
-            const int cj = cpkv(j0, m) - j0 + K;
-#pragma unroll
-            for (int cc = 0; cc < 16; ++cc) lk[cc] = Lg[cj + min(cc, kb - 1)];
-            // one rhs column per 16-lane row
-#pragma unroll
-            for (int q0 = 0; q0 < NRHS; q0 += 4) {
-                const int q = min(q0 + lg, NRHS - 1);
-                double vv = v[q * p + K + min(l15, kb - 1)];
-                static_for<0, 15>([&](auto C) {
-                    constexpr int cc = 15 - decltype(C)::value;
-                    if (cc < kb) vv -= Lr[cc] * row_bcast<cc>(vv);
-                });
-                if (l15 < kb && q0 + lg < NRHS) v[q * p + K + l15] = vv;
-            }
-            front_sync<true>();
-            for (int j = lane; j < K; j += 64) {
-                if (j >= 64) {
-                    const int c2 = cpkv(j, m) - j + K;
-#pragma unroll
-                    for (int cc = 0; cc < 16; ++cc) lk[cc] = Lg[c2 + min(cc, kb - 1)];
-                }
-#pragma unroll
-                for (int q = 0; q < NRHS; ++q) {
-                    double acc = v[q * p + j];
-#pragma unroll
-                    for (int cc = 0; cc < 16; ++cc) {
-                        const double xk = v[q * p + K + min(cc, kb - 1)];
-                        acc -= (cc < kb ? (double)lk[cc] : 0.0) * xk;
-                    }
-                    v[q * p + j] = acc;
-                }
-            }
-            front_sync<true>();
-        }
+        if (staged) back_triangle<NRHS>((const FEHMM_LDS T*)tri, [&](int j) { return cpkv(j, p); }, v, p);
+        else back_triangle<NRHS>(Lg, [&](int j) { return cpkv(j, m); }, v, p);
     }
     front_sync<WAVE>();
     for (int j = gt; j < p; j += GT) {
@@ -2312,11 +2370,107 @@ __device__ inline void backsolve_front(const PanelCtx& pl, int s, FEHMM_LDS doub
     front_sync<WAVE>();
 }
 
+// Backward substitution of four wave fronts k .. k + 3 of the plan's list at once, one
+// per 16-lane row of the wave (fronts past `end` repeat the last and store nothing).
+// Lane l of a row holds pivot K + l of each 16-pivot block K, from the last block: the
+// rows below the block are folded in with their solution values read from LDS
+// (xk, [NRHS][64] of each front), the block's own triangle by DPP broadcasts.  L is
+// row-major, so a row's 16 entries are one 128-byte load and a chunk of 16 rows is
+// requested while the one before it is used.  Bound by those loads' latency.  Against
+// one front per wave (MFMA products, packed columns) the wave fronts of a 32 x 32
+// solve take 0.13 instead of 0.31 Mclk; with the triangles in LDS above, 4096 of them
+// 55.3 -> 52 ms (FP32 factors 46.9 -> 43.3).
+template <int NRHS, typename T>
+__device__ inline void backsolve_rows(const PanelCtx& pl, int k, int end, FEHMM_LDS double* xk, FEHMM_GLB double* x) {
+    constexpr int CH = 16;  // rows per chunk
+    const int lane = threadIdx.x & 63, l = lane & 15, r = lane >> 4;
+    BackRec f;
+    {
+        const FEHMM_GLB int32_t* w = (const FEHMM_GLB int32_t*)(pl.back + min(k + r, end - 1));
+        f = BackRec{w[0], w[1], w[2], w[3], w[4], w[5]};
+    }
+    const bool live = k + r < end;
+    const int m = f.m, p = f.p;
+    const FEHMM_GLB int32_t* rows = pl.rows;
+    const FEHMM_GLB T* Lg = (const FEHMM_GLB T*)pl.L;
+    const int Lo = f.L_off * (8 / (int)sizeof(T));
+    xk += r * (NRHS * 64 + 4);
+    auto row_max = [](int w) {  // largest of the four rows' values
+        w = max(w, __shfl_xor(w, 16));
+        return uni(max(w, __shfl_xor(w, 32)));
+    };
+    const int pmax = row_max(p);
+    // solution of the update rows
+    {
+        int ri[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ri[u] = rows[f.rows_off + min(p + 16 * u + l, m - 1)] * NRHS;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (p + 16 * u + l < m)
+#pragma unroll
+                for (int q = 0; q < NRHS; ++q) xk[q * 64 + p + 16 * u + l] = x[ri[u] + q];
+    }
+    for (int K = 16 * ((pmax - 1) >> 4); K >= 0; K -= 16) {
+        const int kb = min(max(p - K, 0), 16), j = min(K + l, p - 1);
+        const bool act = l < kb;
+        const int ri = rows[f.rows_off + j] * NRHS;
+        const double d = (pl.L + f.D_off)[j];
+        double v[NRHS];
+#pragma unroll
+        for (int q = 0; q < NRHS; ++q) v[q] = (pl.L + f.y_off)[q * p + j];
+        T Lr[16];
+#pragma unroll
+        for (int cc = 1; cc < 16; ++cc) Lr[cc] = Lg[Lo + min(K + cc, m - 1) * p + j];
+        // rows K + kb .. m - 1 in chunks
+        const int i0 = K + kb, trip = row_max(kb > 0 ? m - i0 : 0);
+        T a[CH];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) a[u] = Lg[Lo + min(i0 + u, m - 1) * p + j];
+        front_sync<true>();
+        double acc[NRHS];
+#pragma unroll
+        for (int q = 0; q < NRHS; ++q) acc[q] = 0.0;
+        for (int t = 0; t < trip || t == 0; t += CH) {
+            T b[CH];
+#pragma unroll
+            for (int u = 0; u < CH; ++u) b[u] = Lg[Lo + min(i0 + t + CH + u, m - 1) * p + j];
+#pragma unroll
+            for (int u = 0; u < CH; ++u) {
+                const int i = i0 + t + u;
+                const double lv = i < m ? (double)a[u] : 0.0;
+#pragma unroll
+                for (int q = 0; q < NRHS; ++q) acc[q] += lv * (i < m ? xk[q * 64 + i] : 0.0);
+            }
+#pragma unroll
+            for (int u = 0; u < CH; ++u) a[u] = b[u];
+        }
+#pragma unroll
+        for (int q = 0; q < NRHS; ++q) v[q] = v[q] / d - acc[q];
+        static_for<0, 15>([&](auto C) {
+            constexpr int cc = 15 - decltype(C)::value;
+            if (cc < pmax - K) {  // (uniform)
+                const double lc = (cc < kb && cc > l) ? (double)Lr[cc] : 0.0;
+#pragma unroll
+                for (int q = 0; q < NRHS; ++q) v[q] -= lc * row_bcast<cc>(v[q]);
+            }
+        });
+        if (act) {
+#pragma unroll
+            for (int q = 0; q < NRHS; ++q) {
+                xk[q * 64 + j] = v[q];
+                if (live) x[ri + q] = v[q];
+            }
+        }
+        front_sync<true>();
+    }
+}
+
 // backward substitution L^T x = D^-1 y with NRHS columns; y is each front's
 // stored forward-substituted rhs, x (node-major [dof][NRHS], FP64) receives the
-// solution.  The workgroup fronts in the plan's steps, in reverse, then the
-// small subtrees one front per wave, parents first.  S: FP64 scratch, `slice`
-// doubles per wave.
+// solution.  The workgroup fronts in the plan's steps, in reverse (four-front steps
+// one front per wave), then the small subtrees four fronts per wave, parents first.
+// S: FP64 scratch, `slice` doubles per wave.
 template <int D, int NRHS, typename T>
 __device__ __noinline__ void backsolve_lds(const RveCtx& c, double* Sgen, double* xgen, int slice) {
     const PanelCtx pl = panel_ctx(c);
@@ -2327,19 +2481,23 @@ __device__ __noinline__ void backsolve_lds(const RveCtx& c, double* Sgen, double
     zero_pinned<D>(c, xgen, NRHS);
     for (int st = pl.nwg_steps - 1; st >= 0; --st) {
         const Step e = load_const((const FEHMM_GLB Step*)pl.wg_steps + st);
-        const int nf = e.front[3] >= 0 ? 4 : (e.front[1] >= 0 ? 2 : 1);
-        const int G = min(nf, NT / 128);
+        if (e.front[3] >= 0) {
+            backsolve_front<D, NRHS, T, true>(pl, load_const(pl.wg_steps + kStepFronts * st + wave), S + wave * slice, slice,
+                                              x, tid & 63, 64, 0, 1);
+            __syncthreads();
+            continue;
+        }
+        const int G = e.front[1] >= 0 ? 2 : 1;
         const int GT = NT / G, NW = NWAVE / G, g = wave / NW;
-        for (int r = 0; r < nf / G; ++r)
-            backsolve_front<D, NRHS, T, false>(pl, load_const(pl.wg_steps + kStepFronts * st + r * G + g),
-                                               S + g * NW * slice, x, tid - g * GT, GT, wave - g * NW, NW);
+        backsolve_front<D, NRHS, T, false>(pl, load_const(pl.wg_steps + kStepFronts * st + g), S + g * NW * slice,
+                                           NW * slice, x, tid - g * GT, GT, wave - g * NW, NW);
     }
-    // small subtrees: one front per wave, parents (greater height) first
+    // small subtrees: four fronts per wave, parents (greater height) first
     PROF_T0();
     for (int h = pl.nwave_h - 1; h >= 0; --h) {
         const int k1 = load_const(pl.wave_hbeg + h + 1);
-        for (int k = load_const(pl.wave_hbeg + h) + wave; k < k1; k += NWAVE)
-            backsolve_front<D, NRHS, T, true>(pl, load_const(pl.wave_list + k), S + wave * slice, x, tid & 63, 64, 0, 1);
+        for (int k = load_const(pl.wave_hbeg + h) + 4 * wave; k < k1; k += 4 * NWAVE)
+            backsolve_rows<NRHS, T>(pl, k, k1, S + wave * slice, x);
         __syncthreads();
     }
     PROF_MARK(PH_TRSM);
@@ -2376,7 +2534,7 @@ __device__ __noinline__ void forward_lds(const RveCtx& c, Smem& sm, T* F, double
         {
             // stage the panel after the FP64 rows of b when both fit
             const int vneed = (int)((sizeof(double) / sizeof(T)) * m * NRHS);
-            const int lp = cpk(p, m);
+            const int lp = fr.wave ? m * p : cpk(p, m);
             if (vneed + lp <= front_elems) {
                 T* Ls = F + vneed;
                 copy_in(Ls, Lp, lp, tid, NT);
@@ -2384,6 +2542,9 @@ __device__ __noinline__ void forward_lds(const RveCtx& c, Smem& sm, T* F, double
             }
         }
         double* yg = c.L + fr.y_off;
+        // L(i, j), i >= j: wave fronts row-major, the others packed columns
+        const bool wv = fr.wave != 0;
+        auto at = [&](int i, int j) { return wv ? i * p + j : cpk(j, m) + i - j; };
         for (int t = tid; t < m * NRHS; t += NT) {
             const int i = t % m, q = t / m;
             vb[t] = (i < p) ? b[(int64_t)rows[i] * NRHS + q] : 0.0;
@@ -2406,7 +2567,7 @@ __device__ __noinline__ void forward_lds(const RveCtx& c, Smem& sm, T* F, double
                     for (int u = 0; u < 4; ++u) {
                         const int j = min(j0 + u, p - 2);
                         const int row = max(min(lane, m - 1), j + 1);
-                        l[u] = (double)Lp[cpk(j, m) + row - j] *
+                        l[u] = (double)Lp[at(row, j)] *
                                ((j0 + u < p - 1 && lane > j && lane < p) ? 1.0 : 0.0);
                     }
 #pragma unroll
@@ -2425,7 +2586,7 @@ __device__ __noinline__ void forward_lds(const RveCtx& c, Smem& sm, T* F, double
                 for (int q = 0; q < NRHS; ++q) acc[q] = vb[q * m + i];
 #pragma unroll 4
                 for (int j = 0; j < p; ++j) {
-                    const double l = (double)Lp[cpk(j, m) + i - j];
+                    const double l = (double)Lp[at(i, j)];
 #pragma unroll
                     for (int q = 0; q < NRHS; ++q) acc[q] -= l * vb[q * m + j];
                 }
@@ -2441,7 +2602,7 @@ __device__ __noinline__ void forward_lds(const RveCtx& c, Smem& sm, T* F, double
                 double Lr[16];
 #pragma unroll
                 for (int cc = 0; cc < 16; ++cc)
-                    Lr[cc] = (own && cc < kb && cc < lane) ? (double)Lp[cpk(K + cc, m) + lane - cc] : 0.0;
+                    Lr[cc] = (own && cc < kb && cc < lane) ? (double)Lp[at(K + lane, K + cc)] : 0.0;
 #pragma unroll
                 for (int q = 0; q < NRHS; ++q) {
                     double vv = own ? vb[q * m + K + lane] : 0.0;
@@ -2459,7 +2620,7 @@ __device__ __noinline__ void forward_lds(const RveCtx& c, Smem& sm, T* F, double
             for (int i = K + kb + tid; i < m; i += NT) {
                 double lk[16];
 #pragma unroll
-                for (int cc = 0; cc < 16; ++cc) lk[cc] = (cc < kb) ? (double)Lp[cpk(K + cc, m) + i - K - cc] : 0.0;
+                for (int cc = 0; cc < 16; ++cc) lk[cc] = (cc < kb) ? (double)Lp[at(i, K + cc)] : 0.0;
 #pragma unroll
                 for (int q = 0; q < NRHS; ++q) {
                     double acc = vb[q * m + i];

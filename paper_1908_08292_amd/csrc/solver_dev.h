@@ -7,7 +7,7 @@
 namespace fehmm {
 
 struct DevFront {
-    int32_t m, p, parent, child_begin, child_end, asm_begin, asm_end, u_lds;
+    int32_t m, p, parent, child_begin, child_end, asm_begin, asm_end, u_lds, wave, pad;
     int64_t rows_off, relind_off, L_off, D_off, y_off, U_off, ea_off;
 };
 
@@ -16,6 +16,11 @@ struct DevChild {
     int32_t mc, npre;  // update rows; update entries (a prefix) that go to the parent's panel
     int32_t u_lds, pad;
     int64_t ea_off, inv_off, U_off;
+};
+
+// a wave front as the backward substitution reads it, in the order of wave_list
+struct BackRec {
+    int32_t m, p, rows_off, L_off, D_off, y_off;
 };
 
 struct DevPlan {
@@ -29,7 +34,7 @@ struct DevPlan {
     const int32_t* ea_dst;
     const int32_t* inv;
     const DevChild* childrec;
-    const int32_t* wave_list;
+    const BackRec* back;
     const int32_t* wave_hbeg;
     int32_t nwave_h;       // number of heights in the wave phase
     int32_t wave_slice;    // LDS elements per wave slice
