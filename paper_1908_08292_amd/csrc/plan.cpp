@@ -387,7 +387,7 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
         // condensation beside the Newton residual) and what they take in LDS: two
         // buffers of a 16-pivot block's rows beside the panel; in the backward
         // substitution the front's rows and one partial sum per wave
-        const int64_t rhs_cols = d * d + (d == 2 ? 1 : 0), block_rhs = 2 * 16 * rhs_cols;
+        const int64_t rhs_cols = d * d + (d == 2 ? 1 : 0), block_rhs = 2 * 16 * rhs_cols + 2;
         auto packed_panel = [](const FrontHost& X) { return (int64_t)X.p * X.m - (int64_t)X.p * (X.p - 1) / 2; };
         // targets of the original entries as offsets in the packed panel
         for (const FrontHost& F : P.fronts)
@@ -461,8 +461,8 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
         }
         const int64_t slices = kSolveWaves * P.wave_slice;
         P.ul_base = slices;
-        if (all_wave && slices + all_u <= kWaveElemsMax) {
-            int64_t at = 0;
+        if (all_wave && slices + all_u + 2 <= kWaveElemsMax) {
+            int64_t at = 2;  // (element 0 is a zero)
             for (FrontHost& F : P.fronts)
                 if (F.parent >= 0) {
                     F.u_lds = (int)at;
@@ -470,7 +470,7 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
                 }
             P.wave_elems = slices + at;
         } else {
-            const int64_t budget = kWaveElemsMax / kSolveWaves - P.wave_slice;
+            const int64_t budget = (kWaveElemsMax / kSolveWaves / 32) * 32 - P.wave_slice - 2;
             for (int s = 0; s < ns; ++s) {
                 const FrontHost& F = P.fronts[s];
                 fused[s] = F.wave;
@@ -485,7 +485,7 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
             for (int s = 0; s < ns; ++s)
                 ntask += fused[s] && (P.fronts[s].parent < 0 || !fused[P.fronts[s].parent]);
             if (ntask < kSolveWaves) std::fill(fused.begin(), fused.end(), 0);
-            std::vector<int64_t> at(ns, 0);
+            std::vector<int64_t> at(ns, 2);
             for (int s = 0; s < ns; ++s) {
                 FrontHost& F = P.fronts[s];
                 if (!fused[s] || F.parent < 0 || !fused[F.parent]) continue;
@@ -495,7 +495,7 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
                 at[root] += u_elems(F);
                 P.ul_stride = std::max(P.ul_stride, at[root]);
             }
-            P.ul_stride = (P.ul_stride + 31) / 32 * 32;
+            P.ul_stride = (std::max<int64_t>(P.ul_stride, 2) + 31) / 32 * 32;
             P.wave_elems = slices + kSolveWaves * P.ul_stride;
         }
         // tasks: the subtrees first (a contiguous range of the postorder each), then

@@ -1643,6 +1643,15 @@ __device__ inline void front_sync() {
     }
 }
 
+// masked store into a panel: FP64 under the lane mask; FP32 without a branch, masked
+// lanes to F[-1] (eight of them in a row measured 4 % of a solve faster in FP32, 4 %
+// slower in FP64, whose same-address stores cost more)
+template <typename T>
+__device__ inline void put(FEHMM_LDS T* F, bool ok, int at, T v) {
+    if constexpr (sizeof(T) == 4) F[ok ? at : -1] = v;
+    else if (ok) F[at] = v;
+}
+
 // Original entries of a panel from the element matrices (one gather level): U
 // strides of the list per pass, every index load first, then every value load
 // (clamped addresses, zeros selected), then the stores, so a pass costs two
@@ -1677,8 +1686,7 @@ __device__ inline void gather_original(const PanelCtx& pl, const FEHMM_GLB KT* k
             }
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (t0 + u * stride < a1) F[dst[u]] = v[u];
+        for (int u = 0; u < U; ++u) put(F, t0 + u * stride < a1, dst[u], (T)v[u]);
     }
 }
 // one pass of an extend-add in parts, so that its loads can be issued early
@@ -1700,31 +1708,19 @@ struct ExtendPass {
 #pragma unroll
         for (int u = 0; u < U; ++u) o[u] = F[e[u]];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (first + u * stride < nu) F[e[u]] = o[u] + v[u];
+        for (int u = 0; u < U; ++u) put(F, first + u * stride < nu, e[u], (T)(o[u] + v[u]));
     }
 };
 template <int U = 8, typename Src, typename T>
 __device__ inline void extend_add_packed(const FEHMM_GLB int32_t* ea, const Src* Uc, int nu, int first, int stride,
                                          FEHMM_LDS T* F) {
     for (int t0 = first; t0 < nu; t0 += U * stride) {
-        int e[U];
-        T v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int t = min(t0 + u * stride, nu - 1);
-            e[u] = ea[t];
-            v[u] = Uc[t];
-        }
         // the targets of a pass are distinct (a child adds to each parent entry
-        // once; clamped duplicates are read, never written): every target is read
-        // before any is written, one LDS round trip per pass
-        T o[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) o[u] = F[e[u]];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (t0 + u * stride < nu) F[e[u]] = o[u] + v[u];
+        // once): every target is read before any is written, one LDS round trip
+        ExtendPass<U, T> ep;
+        ep.index(ea, nu, t0, stride);
+        ep.value(Uc, nu, t0, stride);
+        ep.add(nu, t0, stride, F);
     }
 }
 
@@ -1820,7 +1816,7 @@ __device__ inline void panel_update(FEHMM_LDS T* F, int m, int p, int K, int kb,
                 const int r = T0 + 16 * (I + u) + l15;
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (cv[v] < p && r < m && r >= cv[v]) F[cb[v] + r] = o[u][v] - acc[u][v];
+                    put(F, cv[v] < p && r < m && r >= cv[v], cb[v] + r, (T)(o[u][v] - acc[u][v]));
             }
         }
     }
@@ -1845,10 +1841,14 @@ __device__ inline void schur_tiles(const PanelCtx& pl, int child_begin, int nch,
     const int lane = threadIdx.x & 63, l15 = lane & 15, lg = lane >> 4;
     const int mu = m - p, ns = (mu + 31) >> 5;
     const FEHMM_GLB T* Ug = (const FEHMM_GLB T*)pl.U;
+    const int blast = cpk(p - 1, m) - (p - 1);
     int t = 0;
     for (int J = 0; J < ns; ++J)
         for (int I = J; I < ns; ++I, ++t) {
             if ((t & (nw - 1)) != gw) continue;
+            // MFMA tiles (row, column) of the four: (0, 0) always, (0, 1) off the
+            // diagonal, (1, 0) and (1, 1) where the second row tile exists
+            const bool off = I > J, two = 32 * I + 16 < mu;
             int r[2], c[2][4];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -1856,44 +1856,65 @@ __device__ inline void schur_tiles(const PanelCtx& pl, int child_begin, int nch,
 #pragma unroll
                 for (int v = 0; v < 4; ++v) c[u][v] = 32 * J + 16 * u + M::row(lane, v);
             }
-            T val[2][2][2][4];  // [child][row tile][column tile][element]
+            // inv: child row | column offset cpk(row) - row above it, negative where
+            // the child has no such row (then the offsets sum to below zero, and
+            // element 0, a zero, is read); entries above the diagonal read some entry
+            // of the child and are not stored
             auto child_load = [&](const auto* inv, const ChildU<T>& ch, T (&x)[2][2][4]) {
-                int ir[2], ic[2][4];
+                constexpr int kNone = -(1 << 28);
+                const int base = ch.lds >= 0 ? ch.lds : ch.off;
+                int ro[2], co[2][4];
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    ir[u] = inv[p + min(r[u], mu - 1)];
+                    const int y = inv[p + min(r[u], mu - 1)];
+                    ro[u] = y < 0 ? kNone : base + (y & 0xffff);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) ic[u][v] = inv[p + min(c[u][v], mu - 1)];
+                    for (int v = 0; v < 4; ++v) {
+                        const int z = inv[p + min(c[u][v], mu - 1)];
+                        co[u][v] = z < 0 ? kNone : z >> 16;
+                    }
                 }
-                // inv: child row | column offset cpk(row) - row above it, negative
-                // where the child has no such row (entries above the diagonal read
-                // some entry of the child and are not stored)
-                if (ch.lds >= 0) {
-                    const FEHMM_LDS T* Uc = Ul + ch.lds;
+                auto get = [&](int u, int w) {
+                    if (ch.lds >= 0) {
 #pragma unroll
-                    for (int u = 0; u < 2; ++u)
+                        for (int v = 0; v < 4; ++v) x[u][w][v] = Ul[max(ro[u] + co[w][v], 0)];
+                    } else {
 #pragma unroll
-                        for (int w = 0; w < 2; ++w)
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                const bool ok = (ir[u] | ic[w][v]) >= 0;
-                                const T y = Uc[ok ? (ir[u] & 0xffff) + (ic[w][v] >> 16) : 0];
-                                x[u][w][v] = ok ? y : T(0);
-                            }
-                } else {
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int w = 0; w < 2; ++w)
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                const bool ok = (ir[u] | ic[w][v]) >= 0;
-                                x[u][w][v] = Ug[ok ? ch.off + (ir[u] & 0xffff) + (ic[w][v] >> 16) : 0];
-                            }
+                        for (int v = 0; v < 4; ++v) x[u][w][v] = Ug[max(ro[u] + co[w][v], 0)];
+                    }
+                };
+                get(0, 0);
+                if (off) get(0, 1);
+                if (two) {
+                    get(1, 0);
+                    get(1, 1);
                 }
             };
-            if (nch > 0) child_load(iv, ch0, val[0]);
-            if (nch > 1) child_load(iv + m, ch1, val[1]);
+            // the children's entries (the products are summed on their own: added to
+            // a running sum of both, FP32 factors lost half a digit)
+            T val[2][2][4] = {};  // [row tile][column tile][element]
+            if (nch > 0) child_load(iv, ch0, val);
+            if (nch > 1) {
+                T x[2][2][4] = {};
+                child_load(iv + m, ch1, x);
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int w = 0; w < 2; ++w)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) val[u][w][v] += x[u][w][v];
+            }
+            for (int q = 2; q < nch; ++q) {
+                const DevChild ch = load_const(pl.childrec + child_begin + q);
+                T x[2][2][4] = {};
+                child_load(pl.inv + ch.inv_off, ChildU<T>{ch.u_lds, (int)(ch.U_off * (8 / (int)sizeof(T)))}, x);
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int w = 0; w < 2; ++w)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) val[u][w][v] += x[u][w][v];
+            }
             typename M::V acc[2][2];
 #pragma unroll
             for (int u = 0; u < 2; ++u)
@@ -1905,14 +1926,24 @@ __device__ inline void schur_tiles(const PanelCtx& pl, int child_begin, int nch,
                 ra[u] = min(p + 32 * I + 16 * u + l15, m - 1);
                 rc[u] = min(p + 32 * J + 16 * u + l15, m - 1);
             }
-            // (columns past p: the last column's address, a zero pivot)
+            // eight columns per step, k = lg and lg + 4 in it: column k starts at
+            // base(k) = cpk(k, m) - k, base(k + 8) - base(k) = 8 m - 8 k - 36; past p
+            // the last column's address and a zero pivot
+            int bs[2], inc[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int k = lg + 4 * h;
+                bs[h] = cpkv(k, m) - k;
+                inc[h] = 8 * m - 8 * k - 36;
+            }
             T ob[2][2][2], oa[2][2][2], od[2][2];
             auto load = [&](int k0, int h) {
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
-                    const int k = k0 + 4 * s + lg, kc = min(k, p - 1);
-                    const int base = cpkv(kc, m) - kc;
-                    od[h][s] = F[base + kc] * (k < p ? T(1) : T(0));
+                    const int k = k0 + 4 * s + lg, base = min(bs[s], blast);
+                    bs[s] += inc[s];
+                    inc[s] -= 64;
+                    od[h][s] = F[base + min(k, p - 1)] * (k < p ? T(1) : T(0));
 #pragma unroll
                     for (int u = 0; u < 2; ++u) {
                         oa[h][s][u] = F[base + rc[u]];
@@ -1922,13 +1953,15 @@ __device__ inline void schur_tiles(const PanelCtx& pl, int child_begin, int nch,
             };
             auto mul = [&](int h) {
 #pragma unroll
-                for (int s = 0; s < 2; ++s)
-#pragma unroll
-                    for (int w = 0; w < 2; ++w) {
-                        const T av = oa[h][s][w] * od[h][s];
-#pragma unroll
-                        for (int u = 0; u < 2; ++u) acc[u][w] = M::mma(av, ob[h][s][u], acc[u][w]);
+                for (int s = 0; s < 2; ++s) {
+                    const T a0 = oa[h][s][0] * od[h][s], a1 = oa[h][s][1] * od[h][s];
+                    acc[0][0] = M::mma(a0, ob[h][s][0], acc[0][0]);
+                    if (off) acc[0][1] = M::mma(a1, ob[h][s][0], acc[0][1]);
+                    if (two) {
+                        acc[1][0] = M::mma(a0, ob[h][s][1], acc[1][0]);
+                        acc[1][1] = M::mma(a1, ob[h][s][1], acc[1][1]);
                     }
+                }
             };
             load(0, 0);
             for (int k0 = 0; k0 < p; k0 += 16) {
@@ -1939,24 +1972,6 @@ __device__ inline void schur_tiles(const PanelCtx& pl, int child_begin, int nch,
                     mul(1);
                 }
             }
-            if (nch > 0)
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int w = 0; w < 2; ++w)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            acc[u][w][v] -= nch > 1 ? val[0][u][w][v] + val[1][u][w][v] : val[0][u][w][v];
-            for (int q = 2; q < nch; ++q) {
-                const DevChild ch = load_const(pl.childrec + child_begin + q);
-                child_load(pl.inv + ch.inv_off, ChildU<T>{ch.u_lds, (int)(ch.U_off * (8 / (int)sizeof(T)))}, val[0]);
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int w = 0; w < 2; ++w)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[u][w][v] -= val[0][u][w][v];
-            }
 #pragma unroll
             for (int w = 0; w < 2; ++w)
 #pragma unroll
@@ -1964,7 +1979,7 @@ __device__ inline void schur_tiles(const PanelCtx& pl, int child_begin, int nch,
                     const int cb = cpkv(c[w][v], mu) - c[w][v];
 #pragma unroll
                     for (int u = 0; u < 2; ++u)
-                        if (r[u] < mu && r[u] >= c[w][v]) dst[cb + r[u]] = -acc[u][w][v];
+                        if (r[u] < mu && r[u] >= c[w][v]) dst[cb + r[u]] = val[u][w][v] - acc[u][w][v];
                 }
         }
 }
@@ -2090,10 +2105,9 @@ __device__ inline void front_lds(const PanelCtx& pl, const FEHMM_GLB KeType<D, N
             T piv = T(1);
             eliminate16<NRHS, T>(blk, row, yb, b, kb, i - K, piv);
             if (i >= K && i < K + kb) mypiv = piv;
-            const bool act = i >= K && i < m;
+            const int top = i < m ? i - K : -1;  // the row's last column in the block
 #pragma unroll
-            for (int cc = 0; cc < 16; ++cc)
-                if (act && cc < kb && K + cc <= i) F[cpk(K + cc, m) + i - K - cc] = row[cc];
+            for (int cc = 0; cc < 16; ++cc) put(F, cc <= top && cc < kb, cpk(K + cc, m) + i - K - cc, row[cc]);
             if (i >= K + 16 && i < K + 32)
 #pragma unroll
                 for (int q = 0; q < NRHS; ++q) ys[((par ^ 1) * NRHS + q) * 16 + i - K - 16] = b[q];
@@ -2125,8 +2139,8 @@ __device__ inline void front_lds(const PanelCtx& pl, const FEHMM_GLB KeType<D, N
                 for (int u = 0; u < 4; ++u) v[u] = F[cj + max(min(r0 + 4 * u + lg, m - 1), j)];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int r = r0 + 4 * u + lg;
-                    if (r < m && j0 + l15 < p) Lg[r * p + j] = v[u];
+                    const int r = min(r0 + 4 * u + lg, m - 1);  // (clamped lanes repeat a store)
+                    Lg[r * p + j] = v[u];
                 }
             }
         }
@@ -2136,8 +2150,7 @@ __device__ inline void front_lds(const PanelCtx& pl, const FEHMM_GLB KeType<D, N
 #pragma unroll
             for (int u = 0; u < 8; ++u) v[u] = F[min(t0 + u * GT, lp - 1)];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (t0 + u * GT < lp) Lg[t0 + u * GT] = v[u];
+            for (int u = 0; u < 8; ++u) Lg[min(t0 + u * GT, lp - 1)] = v[u];
         }
     }
     if (mu > 0) {
@@ -2168,12 +2181,14 @@ __device__ __noinline__ void factorize_lds(const RveCtx& c, Smem& sm, T* Fgen) {
     FEHMM_LDS int32_t* iv = (FEHMM_LDS int32_t*)sm.red;  // inverse row maps of two children of every front in flight
     static_assert(sizeof(Smem::red) >= 2 * NT * sizeof(int32_t), "inverse row maps");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    constexpr int YS = 2 * NRHS * 16;
+    constexpr int YS = 2 * NRHS * 16 + 2;  // (F[-1]: where masked stores go)
     // small subtrees, one per wave: a task is a contiguous range of fronts, the
     // update matrices inside it stay in the wave's LDS; tasks of a level are
     // independent
     FEHMM_LDS T* const Fw = F + wave * pl.wave_slice;
     FEHMM_LDS T* const Ul = F + pl.ul_base + wave * pl.ul_stride;
+    if (pl.ntask_lev > 0) Ul[0] = T(0);  // read for entries a child does not have
+    __syncthreads();
     for (int h = 0; h < pl.ntask_lev; ++h) {
         const int k1 = load_const(pl.task_beg + h + 1);
         for (int k = load_const(pl.task_beg + h) + wave; k < k1; k += NWAVE) {
@@ -2382,7 +2397,7 @@ __device__ inline void backsolve_front(const PanelCtx& pl, int s, FEHMM_LDS doub
 // 55.3 -> 52 ms (FP32 factors 46.9 -> 43.3).
 template <int NRHS, typename T>
 __device__ inline void backsolve_rows(const PanelCtx& pl, int k, int end, FEHMM_LDS double* xk, FEHMM_GLB double* x) {
-    constexpr int CH = 16;  // rows per chunk
+    constexpr int CH = NRHS == 1 ? 16 : 8;  // rows per chunk (registers)
     const int lane = threadIdx.x & 63, l = lane & 15, r = lane >> 4;
     BackRec f;
     {
