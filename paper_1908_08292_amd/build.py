@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "librve.so")
-SOURCES = ["plan.cpp", "rve_abi.cpp", "rve_solve.hip", "rve_static.hip", "fehmm.hip",
+SOURCES = ["plan.cpp", "rve_abi.cpp", "rve_solve.hip", "rve_solve_w8.hip", "rve_static.hip", "fehmm.hip",
            "surrogate.hip", "probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          # no packed FP32 add/mul/FMA in any kernel: the device pass honours

@@ -19,10 +19,17 @@
 #include "solver_dev.h"
 
 namespace fehmm {
+// the solver compiled with four-wave and with eight-wave workgroups
+namespace w4 {
 hipError_t launch_rve_solve(const SolveArgs& a, int nslots, size_t dyn_bytes, bool fp32, hipStream_t stream);
 hipError_t launch_rve_assembly(const SolveArgs& a, int nslots, hipStream_t stream);
 hipError_t prepare_rve_solve();
 int lds_static_bytes();
+}
+namespace w8 {
+hipError_t launch_rve_solve(const SolveArgs& a, int nslots, size_t dyn_bytes, bool fp32, hipStream_t stream);
+hipError_t prepare_rve_solve();
+}
 }
 
 using namespace fehmm;
@@ -179,7 +186,7 @@ int plan_device(PlanEntry* e) {
                                    8 * kSolveWaves * P.bs_slice, 8 * (int64_t)P.max_m * rhs_cols});
     }
     // (one thread per front row: m <= 256; the plan decides)
-    e->dev.lds_ok = (P.lds_path && e->lds_need[0] + lds_static_bytes() + 1024 <= kLdsBytesMax) ? 1 : 0;
+    e->dev.lds_ok = (P.lds_path && e->lds_need[0] + w4::lds_static_bytes() + 1024 <= kLdsBytesMax) ? 1 : 0;
     return RVE_OK;
 }
 
@@ -211,6 +218,7 @@ struct rve_batch_s {
     int nslots = 0;
     int64_t bs_slice = 0;           // FP64 scratch per wave of the backward substitution
     size_t dyn_bytes[2] = {0, 0};   // dynamic LDS with FP64 / FP32 factors
+    bool wide = false;              // every plan keeps its fronts in global memory: eight-wave workgroups
     SlotLayout lay{};
     std::vector<int64_t> state_off;
     // device
@@ -374,7 +382,8 @@ static void free_batch(rve_batch_s* b) {
 static int ensure_prepared() {
     static bool prepared = false;
     if (!prepared) {
-        hipError_t pe = prepare_rve_solve();
+        hipError_t pe = w4::prepare_rve_solve();
+        if (pe == hipSuccess) pe = w8::prepare_rve_solve();
         if (pe != hipSuccess) return fail(RVE_EHIP, std::string("rve kernels: ") + hipGetErrorString(pe));
         prepared = true;
     }
@@ -456,6 +465,12 @@ int rve_batch_create(const rve_mesh* meshes, int64_t B, rve_batch* out) {
                 b->dyn_bytes[k] = std::max<size_t>(b->dyn_bytes[k], (size_t)kTileLdsElems * 8);
         }
     }
+    // eight waves: 3D batches of global fronts (512 RVEs of 8^3 / 12^3 / 16^3 2.33 s
+    // with four waves, 1.45 with eight), and 2D ones while every RVE has a CU of its
+    // own (8 of 60 x 60: 127 and 108 ms); a full chip of their small fronts (at most
+    // 378 rows) is better off with two four-wave workgroups per CU (512 of 40 x 40:
+    // 84 and 100 ms)
+    b->wide = (d == 3 || B <= 256) && std::none_of(plans.begin(), plans.end(), [](const PlanEntry* p) { return p->dev.lds_ok != 0; });
     // (the backward substitution's slices are the largest of the batch's plans)
     for (int k = 0; k < 2; ++k) b->dyn_bytes[k] = std::max<size_t>(b->dyn_bytes[k], (size_t)(8 * kSolveWaves * b->bs_slice));
     auto rnd = [](int64_t x) { return (x + 31) / 32 * 32; };
@@ -590,7 +605,7 @@ static int solve_batch_impl(rve_batch b, const int32_t* subset, const int32_t* s
     // limit), the condensation factorization runs in FP64 and the direct Schur
     // form replaces the refined FP32 solves
     a.tan64 = 0;
-    if (fp32 && (int64_t)b->dyn_bytes[0] + lds_static_bytes() <= kLdsBytesMax / 2) {
+    if (fp32 && (int64_t)b->dyn_bytes[0] + w4::lds_static_bytes() <= kLdsBytesMax / 2) {
         a.tan64 = 1;
         dyn = std::max(dyn, b->dyn_bytes[0]);
     }
@@ -604,7 +619,8 @@ static int solve_batch_impl(rve_batch b, const int32_t* subset, const int32_t* s
     a.reuse_tan = (A != nullptr && !(o.flags & RVE_FLAG_DIRECT_TANGENT)) ? 1 : 0;
     a.ir_eta = 1e-2;
     a.ir_eta_tan = 0.0;
-    hipError_t e = launch_rve_solve(a, nslots, dyn, fp32, (hipStream_t)hip_stream);
+    hipError_t e = b->wide ? w8::launch_rve_solve(a, nslots, dyn, fp32, (hipStream_t)hip_stream)
+                           : w4::launch_rve_solve(a, nslots, dyn, fp32, (hipStream_t)hip_stream);
     if (e != hipSuccess) return fail(RVE_EHIP, std::string("rve_solve_batch launch: ") + hipGetErrorString(e));
     return RVE_OK;
 }
@@ -645,7 +661,7 @@ int rve_assemble_batch(rve_batch b, const double* F, const double* w_state, int3
     a.status = status;
     a.dim = b->d;
     a.atol = -1.0;
-    hipError_t e = launch_rve_assembly(a, b->nslots, (hipStream_t)hip_stream);
+    hipError_t e = w4::launch_rve_assembly(a, b->nslots, (hipStream_t)hip_stream);
     if (e != hipSuccess) return fail(RVE_EHIP, std::string("rve_assemble_batch launch: ") + hipGetErrorString(e));
     return RVE_OK;
 }

@@ -38,11 +38,22 @@
 #include "mesh_common.h"
 #include "solver_dev.h"
 
-namespace fehmm {
+// Waves per workgroup: four, or eight when compiled with FEHMM_NWAVE=8 into
+// namespace fehmm::w8 (batches whose plans all keep their fronts in global memory)
+#ifndef FEHMM_NWAVE
+#define FEHMM_NWAVE 4
+#define FEHMM_VARIANT w4
+#endif
 
-constexpr int NWAVE = kSolveWaves;
+namespace fehmm {
+namespace FEHMM_VARIANT {
+
+constexpr int NWAVE = FEHMM_NWAVE;
 constexpr int NT = 64 * NWAVE;
-static_assert(NT / 128 == kStepGroups && NWAVE == kStepFronts, "thread groups of a step");
+// plans with panels in LDS run four waves
+constexpr bool kLdsPlans = NWAVE == kSolveWaves;
+static_assert(NWAVE == 4 || NWAVE == 8, "workgroup size");
+static_assert(64 * kSolveWaves / 128 == kStepGroups && kSolveWaves == kStepFronts, "thread groups of a step");
 
 // Optional per-phase clock accounting (slot 0, thread 0), compiled in only
 // with -DFEHMM_PHASE_PROF=1; the default build records nothing.
@@ -1023,13 +1034,14 @@ __device__ inline void diag_block_wave(T* Ap, int ldA, T* Dd, const T* d0v, int 
 // global loads first, runs the MFMAs of the current slab while they are in
 // flight, and stages the next slab at its end.  Loads are unconditional at
 // clamped addresses; rows and columns past the block only reach outputs that
-// are never written, and columns past kdim are zeroed through dv.  Each wave
-// computes a 64 x TN/2 quarter of a tile as 4 x TN/32 MFMA tiles.  Every
+// are never written, and columns past kdim are zeroed through dv.  Four waves
+// compute a 64 x TN/2 quarter of a tile each, eight a 64 x TN/4 eighth.  Every
 // thread of the workgroup must call it; it ends with a barrier.
 static_assert(kTileLdsElems == 2 * kTileSlab * 2 * kTileStride, "tile update LDS size");
 template <typename T, int TN>
 struct TileRegs {
-    T a[8], b[TN / 16], d[4];
+    static constexpr int C = kTileSlab / NWAVE;  // slab columns a wave loads
+    T a[2 * C], b[(TN / 64) * C], d[C];
     int j0;  // first column of the slab
 };
 // global-address-space view of a workspace pointer: its loads count only on
@@ -1057,7 +1069,9 @@ __device__ __attribute__((noinline)) void tiles_update(const T* A, const T* dv, 
     static_assert(TN == 64 || TN == 128, "tile width");
     typedef Mfma16<T> M;
     constexpr int NB = TN / 64;   // B rows per loader thread and column
-    constexpr int WT = TN / 32;   // MFMA column tiles per wave
+    constexpr int C = kTileSlab / NWAVE;   // slab columns a wave loads
+    constexpr int WC = NWAVE / 2;          // waves across a tile's columns (two across its rows)
+    constexpr int WT = TN / 16 / WC;       // MFMA column tiles per wave
     A = uni(A);
     dv = uni(dv);
     lda = uni(lda);
@@ -1068,7 +1082,7 @@ __device__ __attribute__((noinline)) void tiles_update(const T* A, const T* dv, 
     nrows = uni(nrows);
     ncols = uni(ncols);  // (lds stays as passed: its LDS address space is inferred from the caller)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lr = tid & 63, lj = (tid >> 6) * 4;
+    const int lr = tid & 63, lj = (tid >> 6) * C;
     constexpr int BUF = kTileSlab * 2 * kTileStride;
     const auto* Ag = as_global(A);
     const auto* dg = as_global(dv);
@@ -1086,13 +1100,13 @@ __device__ __attribute__((noinline)) void tiles_update(const T* A, const T* dv, 
 #pragma unroll
         for (int h = 0; h < NB; ++h) rb[h] = min(lc.c0 + lr + 64 * h, ncols - 1);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < C; ++q) {
             const int j = min(j0 + lj + q, kdim - 1);
             const auto* Aj = Ag + (int64_t)j * lda;
             R.a[q] = Aj[ra0];
-            R.a[4 + q] = Aj[ra1];
+            R.a[C + q] = Aj[ra1];
 #pragma unroll
-            for (int h = 0; h < NB; ++h) R.b[4 * h + q] = Aj[rb[h]];
+            for (int h = 0; h < NB; ++h) R.b[C * h + q] = Aj[rb[h]];
             R.d[q] = dg[j];
         }
         // advance with selects only: a branch here would split the loop body
@@ -1110,12 +1124,12 @@ __device__ __attribute__((noinline)) void tiles_update(const T* A, const T* dv, 
         T* As = lds + buf * BUF;
         T* Bs = As + kTileSlab * kTileStride;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < C; ++q) {
             const T dq = R.j0 + lj + q < kdim ? R.d[q] : T(0);  // columns past kdim
             As[(lj + q) * kTileStride + lr] = R.a[q] * dq;
-            As[(lj + q) * kTileStride + lr + 64] = R.a[4 + q] * dq;
+            As[(lj + q) * kTileStride + lr + 64] = R.a[C + q] * dq;
 #pragma unroll
-            for (int h = 0; h < NB; ++h) Bs[(lj + q) * kTileStride + lr + 64 * h] = R.b[4 * h + q];
+            for (int h = 0; h < NB; ++h) Bs[(lj + q) * kTileStride + lr + 64 * h] = R.b[C * h + q];
         }
     };
     typename M::V acc[4][WT];
@@ -1123,7 +1137,7 @@ __device__ __attribute__((noinline)) void tiles_update(const T* A, const T* dv, 
     for (int u = 0; u < 4; ++u)
 #pragma unroll
         for (int w2 = 0; w2 < WT; ++w2) acc[u][w2] = M::zero();
-    const int wr = 64 * (wave >> 1), wc = (TN / 2) * (wave & 1);
+    const int wr = 64 * (wave / WC), wc = 16 * WT * (wave % WC);
     auto compute = [&](int buf) {
         const T* As = lds + buf * BUF;
         const T* Bs = As + kTileSlab * kTileStride;
@@ -1356,21 +1370,39 @@ __device__ __attribute__((noinline)) void factorize_glb(const RveCtx& c, Smem& s
                 // (c) rows below: L21 = A21 W (MFMA)
                 const int R0 = K + kb;
                 {
+                    // four row tiles in flight per wave: every operand is read before
+                    // the products (a tile's rows are overwritten by its own results
+                    // only)
                     const int nt = (m - R0 + 15) >> 4;
-                    for (int t = wave; t < nt; t += NWAVE) {
-                        const int ra = R0 + 16 * t + (lane & 15);
-                        typename M::V acc = M::zero();
+                    FEHMM_GLB T* Fg = glb(Fp);
+                    T wv[4];
 #pragma unroll
-                        for (int ks = 0; ks < 4; ++ks) {
-                            const int kk = 4 * ks + (lane >> 4);
-                            const T av = (kk < kb && ra < m) ? Fp[(int64_t)(K + kk) * m + ra] : T(0);
-                            acc = M::mma(av, W[kk * 16 + (lane & 15)], acc);
+                    for (int ks = 0; ks < 4; ++ks) wv[ks] = W[(4 * ks + (lane >> 4)) * 16 + (lane & 15)];
+                    for (int t0 = 4 * wave; t0 < nt; t0 += 4 * NWAVE) {
+                        T av[4][4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int ra = min(R0 + 16 * (t0 + u) + (lane & 15), m - 1);
+#pragma unroll
+                            for (int ks = 0; ks < 4; ++ks) {
+                                const int kk = 4 * ks + (lane >> 4);
+                                av[u][ks] = Fg[(int64_t)(K + min(kk, kb - 1)) * m + ra];
+                            }
                         }
-                        const int cc = lane & 15;
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int rr = R0 + 16 * t + M::row(lane, v);
-                            if (rr < m && cc < kb) Fp[(int64_t)(K + cc) * m + rr] = acc[v];
+                        for (int u = 0; u < 4; ++u) {
+                            // (transposed product: consecutive lanes hold consecutive
+                            // rows of a column)
+                            typename M::V acc = M::zero();
+#pragma unroll
+                            for (int ks = 0; ks < 4; ++ks)
+                                acc = M::mma(wv[ks], 4 * ks + (lane >> 4) < kb ? av[u][ks] : T(0), acc);
+                            const int rr = R0 + 16 * (t0 + u) + (lane & 15);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                const int cc = M::row(lane, v);
+                                if (rr < m && cc < kb) Fg[(int64_t)(K + cc) * m + rr] = acc[v];
+                            }
                         }
                     }
                 }
@@ -1475,42 +1507,94 @@ __device__ __attribute__((noinline)) void forward_glb(const RveCtx& c, Smem& sm,
 }
 
 // backward substitution L^T x = D^-1 y with global-memory factors; x
-// node-major [dof][NRHS].  Per front: the update rows' contribution (thread
-// per pivot), then 16-pivot blocks from the last: wave 0 solves the block
-// triangle with readlane broadcasts, all threads fold the block into the
-// earlier pivots.
+// node-major [dof][NRHS].  Per front: the update rows' contribution v = D^-1 y -
+// L21^T x_u on FP64 MFMA (16 pivots x 4 rows x up to 16 rhs columns), one 16-pivot
+// tile per wave, or with fewer tiles than waves the rows of a tile split over
+// several (partial sums in lds, added in a fixed order); then 16-pivot blocks from
+// the last: wave 0 solves the block triangle with readlane broadcasts, all threads
+// fold the block into the earlier pivots.  Bound by the one read of L: a thread per
+// pivot walking its column, four loads in flight, took 55 Mclk per sweep at 16^3.
 template <int D, int NRHS, typename T>
-__device__ __attribute__((noinline)) void backsolve_glb(const RveCtx& c, Smem& sm, double* xo) {
+__device__ __attribute__((noinline)) void backsolve_glb(const RveCtx& c, Smem& sm, double* xo, double* ldsgen) {
+    typedef Mfma16<double> M;
     const DevPlan& pl = *c.plan;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l15 = lane & 15, lg = lane >> 4;
     zero_pinned<D>(c, xo, NRHS);
     __syncthreads();
     double* const cL = uni(c.L);
+    FEHMM_LDS double* const pb = (FEHMM_LDS double*)ldsgen;  // [parts][16 tiles][NRHS] partial sums
     xo = uni(xo);
+    const FEHMM_GLB double* const xg = glb((const double*)xo);
     for (int s = uni(pl.nfront) - 1; s >= 0; --s) {
         const DevFront fr = pl.fronts[s];
-        const int m = uni(fr.m), p = uni(fr.p);
+        const int m = uni(fr.m), p = uni(fr.p), mu = m - p;
         const int32_t* rows = uni(pl.rows + fr.rows_off);
+        const FEHMM_GLB int32_t* rg = glb(rows);
         const T* Fp = reinterpret_cast<const T*>(cL + uni(fr.L_off));
+        const FEHMM_GLB T* Fg = glb(Fp);
         const T* Dg = reinterpret_cast<const T*>(cL + uni(fr.D_off));
         double* y = cL + uni(fr.y_off);
-        for (int j = tid; j < p; j += NT) {
-            const double rd = 1.0 / (double)Dg[j];
-            double v[NRHS];
+        const int ntile = (p + 15) >> 4, nks = (mu + 3) >> 2;
+        const int parts = mu > 0 ? max(1, NWAVE / ntile) : 1;
+        for (int unit = wave; unit < ntile * parts; unit += NWAVE) {
+            const int t = unit % ntile, part = unit / ntile;
+            const int j = min(16 * t + l15, p - 1);
+            const FEHMM_GLB T* col = Fg + (int64_t)j * m + p;
+            M::V acc[2] = {M::zero(), M::zero()};
+            // (the next eight steps' L and row numbers are requested with this
+            // step's solution values)
+            T a[8];
+            int ri[8];
+            auto load = [&](int k0, T (&av)[8], int (&rv)[8]) {
 #pragma unroll
-            for (int q = 0; q < NRHS; ++q) v[q] = y[(int64_t)q * p + j] * rd;
-            const T* cj = Fp + (int64_t)j * m;
-#pragma unroll 4
-            for (int i = p; i < m; ++i) {
-                const double l = (double)cj[i];
-                const double* xr = xo + (int64_t)rows[i] * NRHS;
+                for (int u = 0; u < 8; ++u) {
+                    const int i = min(4 * (k0 + u * parts) + lg, mu - 1);
+                    av[u] = col[i];
+                    rv[u] = rg[p + i] * NRHS + (NRHS == 1 ? 0 : min(l15, NRHS - 1));
+                }
+            };
+            if (mu > 0) load(part, a, ri);
+            for (int k0 = part; k0 < nks; k0 += 8 * parts) {
+                double b[8];
+                T an[8];
+                int rn[8];
 #pragma unroll
-                for (int q = 0; q < NRHS; ++q) v[q] -= l * xr[q];
+                for (int u = 0; u < 8; ++u) b[u] = xg[ri[u]];
+                load(k0 + 8 * parts, an, rn);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const bool ok = 4 * (k0 + u * parts) + lg < mu && l15 < NRHS;
+                    acc[u & 1] = M::mma((double)a[u], ok ? b[u] : 0.0, acc[u & 1]);
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    a[u] = an[u];
+                    ri[u] = rn[u];
+                }
             }
+            // element e of lane: pivot 16 t + row(lane, e), rhs column l15
+            if (l15 < NRHS)
 #pragma unroll
-            for (int q = 0; q < NRHS; ++q) y[(int64_t)q * p + j] = v[q];
+                for (int e = 0; e < 4; ++e) {
+                    const int jj = 16 * t + M::row(lane, e);
+                    if (jj < p) {
+                        const double sum = acc[0][e] + acc[1][e];
+                        if (parts > 1) pb[(part * 16 * ntile + jj) * NRHS + l15] = sum;
+                        else y[(int64_t)l15 * p + jj] = y[(int64_t)l15 * p + jj] / (double)Dg[jj] - sum;
+                    }
+                }
         }
         __syncthreads();
+        if (parts > 1) {
+            for (int t = tid; t < p * NRHS; t += NT) {
+                const int j = t % p, q = t / p;
+                double sum = 0.0;
+                for (int w = 0; w < parts; ++w) sum += pb[(w * 16 * ntile + j) * NRHS + q];
+                y[t] = y[t] / (double)Dg[j] - sum;
+            }
+            __syncthreads();
+        }
         const int nb = (p + 15) >> 4;
         for (int bk = nb - 1; bk >= 0; --bk) {
             const int K = 16 * bk, kb = min(16, p - K);
@@ -2804,8 +2888,38 @@ __device__ inline void rve_setup(const SolveArgs& a, int rve, double* base, RveC
     __syncthreads();
 }
 
+// factorization, backward and forward substitution of the RVE's plan: panels in LDS
+// or fronts in global memory (3D plans in LDS never carry d^2 + 1 columns)
+template <int D, int NRHS, typename T>
+__device__ inline void factorize(const RveCtx& c, Smem& sm, T* lds) {
+    if constexpr (kLdsPlans && (D == 2 || NRHS <= D * D))
+        if (c.plan->lds_ok) {
+            factorize_lds<D, NRHS, T>(c, sm, lds);
+            return;
+        }
+    factorize_glb<D, T>(c, sm, NRHS, lds);
+}
+template <int D, int NRHS, typename T>
+__device__ inline void backsolve(const RveCtx& c, Smem& sm, double* x, double* lds, int slice) {
+    if constexpr (kLdsPlans && (D == 2 || NRHS <= D * D))
+        if (c.plan->lds_ok) {
+            backsolve_lds<D, NRHS, T>(c, lds, x, slice);
+            return;
+        }
+    backsolve_glb<D, NRHS, T>(c, sm, x, lds);
+}
+template <int D, int NRHS, typename T>
+__device__ inline void forward(const RveCtx& c, Smem& sm, double* b, T* lds, int elems) {
+    if constexpr (kLdsPlans)
+        if (c.plan->lds_ok) {
+            forward_lds<D, NRHS, T>(c, sm, lds, b, elems);
+            return;
+        }
+    forward_glb<D, NRHS, T>(c, sm, b);
+}
+
 template <int D, typename T>
-__global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
+__global__ __launch_bounds__(NT, 2) void rve_solve_kernel(SolveArgs a) {
     __shared__ Smem sm;
     extern __shared__ double dynRaw[];
     T* dynF = reinterpret_cast<T*>(dynRaw);
@@ -2903,15 +3017,13 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                     node_gather<D>(c, c.re, D2, c.rhs, NSPEC, 1);
                     for (int t = threadIdx.x; t < ndof; t += NT) c.rhs[(int64_t)t * NSPEC] = -c.R[t];
                     __syncthreads();
-                    if (!c.plan->lds_ok) factorize_glb<D, T>(c, sm, NSPEC, dynF);
-                    else if constexpr (D == 2) factorize_lds<D, NSPEC, T>(c, sm, dynF);
+                    factorize<D, NSPEC, T>(c, sm, dynF);
                 }
             }
             if (!spec) {
                 for (int t = threadIdx.x; t < ndof; t += NT) c.rhs[t] = -c.R[t];
                 __syncthreads();
-                if (c.plan->lds_ok) factorize_lds<D, 1, T>(c, sm, dynF);
-                else factorize_glb<D, T>(c, sm, 1, dynF);
+                factorize<D, 1, T>(c, sm, dynF);
             }
             if (sm.flag) { status = 3; break; }
             PROF_RESET();
@@ -2920,16 +3032,13 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                     // every column in one backward sweep, into the rhs buffer
                     // ([dof][1 + d^2]): the Newton step, then X' = K'^-1 Y', which
                     // stays there for the condensation if the next state converges
-                    if (!c.plan->lds_ok) backsolve_glb<D, NSPEC, T>(c, sm, c.rhs);
-                    else if constexpr (D == 2)
-                        backsolve_lds<D, NSPEC, T>(c, dynRaw, c.rhs, a.bs_slice);
+                    backsolve<D, NSPEC, T>(c, sm, c.rhs, dynRaw, a.bs_slice);
                     for (int t = threadIdx.x; t < ndof; t += NT) c.x[t] = c.rhs[(int64_t)t * NSPEC];
                     __syncthreads();
                 }
             }
             if (!spec) {
-                if (c.plan->lds_ok) backsolve_lds<D, 1, T>(c, dynRaw, c.x, a.bs_slice);
-                else backsolve_glb<D, 1, T>(c, sm, c.x);
+                backsolve<D, 1, T>(c, sm, c.x, dynRaw, a.bs_slice);
             }
             PROF_MARK(PH_BACK);
             if constexpr (IR) {
@@ -2942,13 +3051,8 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                     __syncthreads();
                     const double rl2 = sqrt(free_norm2<D>(c, sm, ir1));
                     if (!(rl2 > a.ir_eta * rn)) break;
-                    if (c.plan->lds_ok) {
-                        forward_lds<D, 1, T>(c, sm, dynF, ir1, a.lds_elems);
-                        backsolve_lds<D, 1, T>(c, dynRaw, ir2, a.bs_slice);
-                    } else {
-                        forward_glb<D, 1, T>(c, sm, ir1);
-                        backsolve_glb<D, 1, T>(c, sm, ir2);
-                    }
+                    forward<D, 1, T>(c, sm, ir1, dynF, a.lds_elems);
+                    backsolve<D, 1, T>(c, sm, ir2, dynRaw, a.bs_slice);
                     for (int t = threadIdx.x; t < ndof; t += NT) c.x[t] += ir2[t];
                     __syncthreads();
                 }
@@ -3036,12 +3140,10 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                 }
                 if (stale)
                     ;
-                else if (!c.plan->lds_ok)
-                    factorize_glb<D, double>(c, sm, D2, dynRaw);
-                else if (IR && a.tan64)
-                    factorize_lds<D, D2, double>(c, sm, dynRaw);
+                else if (!c.plan->lds_ok || (IR && a.tan64))
+                    factorize<D, D2, double>(c, sm, dynRaw);
                 else
-                    factorize_lds<D, D2, T>(c, sm, dynF);
+                    factorize<D, D2, T>(c, sm, dynF);
                 if (sm.flag) {
                     status = 3;
                 } else if (!tan64) {
@@ -3050,7 +3152,7 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                     // (second-order) form
                     //   Abar = <A> - Y^T X - X^T r,  r = Y - K X,
                     // whose error is (X - X*)^T K (X - X*) (energy-norm error squared)
-                    if (!stale) backsolve_lds<D, D2, T>(c, dynRaw, X, a.bs_slice);
+                    if (!stale) backsolve<D, D2, T>(c, sm, X, dynRaw, a.bs_slice);
                     // refinement corrections: ir2 unless it holds Y
                     double* const corr = stale ? c.rhs : ir2;
                     const int max_ref = stale ? 2 : a.ir_max_tan;
@@ -3070,13 +3172,8 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
                             __syncthreads();
                             if (done) break;
                         }
-                        if (c.plan->lds_ok) {
-                            forward_lds<D, D2, T>(c, sm, dynF, ir1, a.lds_elems);
-                            backsolve_lds<D, D2, T>(c, dynRaw, corr, a.bs_slice);
-                        } else {
-                            forward_glb<D, D2, T>(c, sm, ir1);
-                            backsolve_glb<D, D2, T>(c, sm, corr);
-                        }
+                        forward<D, D2, T>(c, sm, ir1, dynF, a.lds_elems);
+                        backsolve<D, D2, T>(c, sm, corr, dynRaw, a.bs_slice);
                         for (int t = threadIdx.x; t < ndof * D2; t += NT) X[t] += corr[t];
                         __syncthreads();
                     }
@@ -3143,7 +3240,7 @@ __global__ __launch_bounds__(NT, 512 / NT) void rve_solve_kernel(SolveArgs a) {
 // (the assembly phase of a Newton iteration, timed on its own by
 // rve_assemble_batch).  status[r] = 2 where some J <= 0, else 0.
 template <int D>
-__global__ __launch_bounds__(NT, 512 / NT) void rve_assembly_kernel(SolveArgs a) {
+__global__ __launch_bounds__(NT, 2) void rve_assembly_kernel(SolveArgs a) {
     __shared__ Smem sm;
     double* base = a.ws + (int64_t)blockIdx.x * a.lay.stride;
     for (;;) {
@@ -3208,11 +3305,24 @@ hipError_t launch_rve_solve(const SolveArgs& a, int nslots, size_t dyn_bytes, bo
     return hipGetLastError();
 }
 
+}  // namespace FEHMM_VARIANT
 }  // namespace fehmm
 
 #if FEHMM_PHASE_PROF
+#if FEHMM_NWAVE == 4
+extern "C" int rve_debug_phase_clocks_w8(unsigned long long* out, int reset);
+extern "C" int rve_debug_phase_clocks_w4(unsigned long long* out, int reset);
 extern "C" int rve_debug_phase_clocks(unsigned long long* out, int reset) {
-    using namespace fehmm;
+    unsigned long long b[fehmm::w4::PH_N];
+    if (rve_debug_phase_clocks_w4(out, reset) || rve_debug_phase_clocks_w8(b, reset)) return -3;
+    for (int i = 0; i < fehmm::w4::PH_N; ++i) out[i] += b[i];
+    return 0;
+}
+extern "C" int rve_debug_phase_clocks_w4(unsigned long long* out, int reset) {
+#else
+extern "C" int rve_debug_phase_clocks_w8(unsigned long long* out, int reset) {
+#endif
+    using namespace fehmm::FEHMM_VARIANT;
     if (hipMemcpyFromSymbol(out, HIP_SYMBOL(g_phase), sizeof(unsigned long long) * PH_N) != hipSuccess) return -3;
     if (reset) {
         unsigned long long z[PH_N] = {0};
