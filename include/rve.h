@@ -285,7 +285,8 @@ int rve_plan_export(int32_t ndim, int32_t n, int64_t* sizes, int32_t* fronts, in
 
 /* Processing schedule of the (ndim, n) plan's LDS path, for tooling and tests
  * (host only).  *nsteps receives the number of workgroup-front steps (0 when
- * the fronts live in global memory); steps, if non-NULL, receives [nsteps][4]
+ * whole packed fronts exceed LDS, i.e. 2D from 36 x 36 on under periodic coupling,
+ * though up to 43 x 43 the solver still holds the fronts' panels there); steps, if non-NULL, receives [nsteps][4]
  * in processing order: the 1, 2 or 4 fronts processed side by side on equal
  * parts of the workgroup, -1 padded; wave, if non-NULL, receives one flag per
  * front (elimination order): 1 for the fronts eliminated one per wave before

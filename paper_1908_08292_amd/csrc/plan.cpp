@@ -368,13 +368,21 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
     P.L_size = Loff;
     P.U_stack = maxtop;
     P.U_scratch = scratch;
-    // LDS path: whole fronts fit the LDS buffer; then update matrices get static
-    // slots (any processing order) and small subtrees run wave-per-front
+    // LDS path: every panel fits LDS (2D up to 43 x 43 under periodic coupling); then
+    // update matrices get static slots (any processing order) and small subtrees run
+    // wave-per-front
     {
         const int64_t mm = P.max_m;
         P.lds_path = mm <= 256 && (mm * (mm + 1) / 2 + mm * d * d) * 8 <= kLdsFrontBytes;
+        // (3D fronts past lds_path are p-heavy and run on the global path's tiles; in 2D
+        // a panel in LDS is worth one workgroup per CU: 512 RVEs of 40 x 40 take 23 ms,
+        // on the global path 76)
+        int64_t panel = 0;
+        for (const FrontHost& F : P.fronts)
+            panel = std::max(panel, (int64_t)F.p * F.m - (int64_t)F.p * (F.p - 1) / 2 + 2 * 16 * (d * d + 1) + 2);
+        P.panel_path = P.lds_path || (d == 2 && mm <= 256 && panel * 8 <= kLdsFrontBytes);
     }
-    if (P.lds_path) {
+    if (P.panel_path) {
         int64_t off = 2;  // (element 0 stays zero: read in place of entries a child does not have)
         for (int s = 0; s < ns; ++s) {
             FrontHost& F = P.fronts[s];

@@ -86,7 +86,8 @@ struct PlanHost {
     int64_t wave_elems = 0;    // LDS elements of the wave phase (slices + update matrices)
     int64_t wg_elems = 0;      // LDS elements of the largest workgroup step (panels + block-row rhs)
     int64_t bs_slice = 0;      // FP64 scratch per wave of the backward substitution
-    bool lds_path = false;     // every front fits the LDS front buffer
+    bool panel_path = false;   // every front's panel fits LDS, with a thread per row (m <= 256)
+    bool lds_path = false;     // whole packed fronts would fit as well (what plan_schedule reports on)
     int64_t L_size = 0;        // doubles of L + D + y storage
     int64_t U_stack = 0;       // doubles of the update-matrix stack
     int64_t U_scratch = 0;     // doubles of the largest update matrix (+ rhs)
@@ -95,7 +96,8 @@ struct PlanHost {
     int64_t nnz_L = 0;
 };
 
-// LDS budget of the front buffer (packed front + its m x d^2 rhs rows)
+// LDS budget of a workgroup front: its panel with the rhs of the block rows, or
+// (lds_path) the packed front with its m x d^2 rhs rows
 constexpr int64_t kLdsFrontBytes = 148 * 1024;
 constexpr int kWaveFrontMaxM = 64;
 constexpr int kStepFronts = 4;  // fronts per workgroup-front step at most

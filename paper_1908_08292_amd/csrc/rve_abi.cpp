@@ -186,7 +186,7 @@ int plan_device(PlanEntry* e) {
                                    8 * kSolveWaves * P.bs_slice, 8 * (int64_t)P.max_m * rhs_cols});
     }
     // (one thread per front row: m <= 256; the plan decides)
-    e->dev.lds_ok = (P.lds_path && e->lds_need[0] + w4::lds_static_bytes() + 1024 <= kLdsBytesMax) ? 1 : 0;
+    e->dev.lds_ok = (P.panel_path && e->lds_need[0] + w4::lds_static_bytes() + 1024 <= kLdsBytesMax) ? 1 : 0;
     return RVE_OK;
 }
 
@@ -218,6 +218,7 @@ struct rve_batch_s {
     int nslots = 0;
     int64_t bs_slice = 0;           // FP64 scratch per wave of the backward substitution
     size_t dyn_bytes[2] = {0, 0};   // dynamic LDS with FP64 / FP32 factors
+    bool tall = false;              // some plan's panels fit LDS where its packed fronts would not
     bool wide = false;              // every plan keeps its fronts in global memory: eight-wave workgroups
     SlotLayout lay{};
     std::vector<int64_t> state_off;
@@ -458,6 +459,7 @@ int rve_batch_create(const rve_mesh* meshes, int64_t B, rve_batch* out) {
         if (p->dev.lds_ok) {
             for (int k = 0; k < 2; ++k) b->dyn_bytes[k] = std::max<size_t>(b->dyn_bytes[k], (size_t)p->lds_need[k]);
             b->bs_slice = std::max(b->bs_slice, p->host.bs_slice);
+            b->tall = b->tall || !p->host.lds_path;
         } else {
             // global fronts: staged tile slabs, FP64-sized in both kernels (the
             // condensation factorization of global-front plans is FP64)
@@ -605,7 +607,8 @@ static int solve_batch_impl(rve_batch b, const int32_t* subset, const int32_t* s
     // limit), the condensation factorization runs in FP64 and the direct Schur
     // form replaces the refined FP32 solves
     a.tan64 = 0;
-    if (fp32 && (int64_t)b->dyn_bytes[0] + w4::lds_static_bytes() <= kLdsBytesMax / 2) {
+    // (always where a packed FP64 front would not fit LDS)
+    if (fp32 && (b->tall || (int64_t)b->dyn_bytes[0] + w4::lds_static_bytes() <= kLdsBytesMax / 2)) {
         a.tan64 = 1;
         dyn = std::max(dyn, b->dyn_bytes[0]);
     }
@@ -815,7 +818,7 @@ int rve_autotune(rve_mesh m, const double* F, int64_t nF, const rve_opts* o, rve
             PlanParams pp;
             pp.leaf = leaf;
             pp.bc = m->bc;
-            lds = build_plan(d, n, pp).lds_path;
+            lds = build_plan(d, n, pp).panel_path;
         } catch (const std::exception& ex) {
             err = fail(RVE_EINVAL, std::string("rve_autotune: ") + ex.what());
             break;

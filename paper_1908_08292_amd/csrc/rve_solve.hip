@@ -2393,24 +2393,20 @@ __device__ inline void backsolve_front(const PanelCtx& pl, int s, FEHMM_LDS doub
     };
     if (mu > 0) a_load(0, gw);
     if (staged) {  // columns of the triangle, wave by wave, eight columns in flight
-        for (int jb = gw; jb < p; jb += 8 * nw) {
-            T c[8][2];
+        for (int jb = gw; jb < p; jb += 8 * nw)
+            for (int h = lane; h < p - jb; h += 64) {  // (every eighth column is no longer than its first)
+                T c[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int j = min(jb + u * nw, p - 1), cj = cpk(j, m) - j;
-                c[u][0] = Lg[cj + min(j + lane, p - 1)];
-                if (p > 64) c[u][1] = Lg[cj + min(j + lane + 64, p - 1)];
-            }
+                for (int u = 0; u < 8; ++u) {
+                    const int j = min(jb + u * nw, p - 1);
+                    c[u] = Lg[cpk(j, m) + min(h, p - 1 - j)];
+                }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int j = jb + u * nw;
-                if (j < p) {
-                    const int cj = cpk(j, p) - j;
-                    if (j + lane < p) tri[cj + j + lane] = c[u][0];
-                    if (p > 64 && j + lane + 64 < p) tri[cj + j + lane + 64] = c[u][1];
+                for (int u = 0; u < 8; ++u) {
+                    const int j = jb + u * nw;
+                    if (j + h < p) tri[cpk(j, p) + h] = c[u];
                 }
             }
-        }
     }
     if (gt < p)
 #pragma unroll

@@ -12,7 +12,7 @@ from paper_1908_08292_amd import api, rve, workloads
 
 pytestmark = pytest.mark.gpu
 
-SIZES = (2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 13, 15, 16, 17, 20, 23, 27, 31, 32)
+SIZES = (2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 13, 15, 16, 17, 20, 23, 27, 31, 32, 37, 43)
 
 
 @pytest.mark.parametrize("bc", [0, 1])
