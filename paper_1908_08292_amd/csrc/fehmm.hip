@@ -549,22 +549,32 @@ __global__ __launch_bounds__(kBandNT) void macro_band_solve_blocked(double* __re
 // in LDS for the whole factorization: diagonal d = I - J keeps its ntw - d tiles
 // of the window in a ring, tile (I, J) at slot base(d) + J mod (ntw - d), so the
 // row that enters when the window moves on takes exactly the slots of the
-// retired panel column.  Per panel (tile column kt), one workgroup of four
-// waves: wave 0 factors the diagonal tile (lane = row, readlane broadcasts) and
-// forms W = L11^-T D^-1; the tiles below become L = A W on MFMA (in place); the
-// factor goes out to K and Kt (band entries only); the trailing tiles take -L(I)
-// D L(J)^T on MFMA; the entering tile row, read from K while the panel is
-// processed (no earlier panel reaches it), is stored.  The matrix is read once
-// and the factor written once, and no global round trip sits on the panel
-// chain.  Rows and columns past n are padded with the identity.
+// retired panel column.  Per panel (tile column kt), one workgroup of eight
+// waves: wave 0 factors the diagonal tile and forms W = L11^-T D^-1; the tiles
+// below become L = A W on MFMA (in place); the trailing tiles take -L(I) D L(J)^T
+// on MFMA; the factor goes out to K and Kt (band entries only); the entering tile
+// row, read from K while the panel is processed (no earlier panel reaches it), is
+// stored.  The right-hand side goes along: z = D^-1 L^-1 (-R) panel by panel, so
+// that only the backward substitution is left.  The matrix is read once and the
+// factor written once, and no global round trip sits on the panel chain.  Rows
+// and columns past n are padded with the identity.
+// The kernel is compiled for each number of tile rows: the tiles and the loops over
+// them are constants, and nothing is done for tiles that the band does not have.
+// What bounds it is the chain of dependent panels: the diagonal tile's sixteen pivots,
+// then one tile of L and one trailing tile, about 2.8 us in all.  At 4802 unknowns and
+// bandwidth 101 (301 panels) the factorization took 1378 us with four waves, ten tile
+// rows for every band and the stores within the panel, 917 us without these, and with
+// the forward substitution within it 1078 us, of which eight waves leave 864 us; the
+// two substitutions took 553 us, the backward one takes 231.
 constexpr int kWinMax = 10;                                  // tile rows of the window (bw <= 144)
 constexpr int kWinSlots = kWinMax * (kWinMax + 1) / 2;       // window tiles
-constexpr int kWinWaves = 4;
+constexpr int kWinWaves = 8;
 constexpr int kWinNT = 64 * kWinWaves;
 constexpr int kWinStride = 17;                               // LDS row stride of a tile (doubles)
 constexpr int kWinTile = 16 * kWinStride;
+constexpr int kWinRing = 256;                                // right-hand side of the window (16 tile rows)
 inline size_t band_win_lds_bytes() {
-    return sizeof(double) * ((size_t)(kWinSlots + kWinMax) * kWinTile + 256 + 16) +
+    return sizeof(double) * ((size_t)(kWinSlots + kWinMax) * kWinTile + 256 + 16 + kWinRing + 16) +
            sizeof(int) * (2 * kWinMax * kWinMax);
 }
 inline bool band_win_fits(int bw) { return (bw + 15) / 16 + 1 <= kWinMax; }
@@ -592,69 +602,106 @@ __device__ inline double recip_nr64(double x) {
     return r;
 }
 
-// B. by one wave: LDL^T of the diagonal tile T of panel kt (lane = row, readlane
-// broadcasts), W = L11^-T D^-1 from the rows of L11^-1 into Wm, the pivots into
-// Dv, the tile's factor rows out to K and Kt
-__device__ __forceinline__ void win_diag(const double* T, double* Wm, double* Dv, int kt, int n, int bw,
-                                         double* __restrict__ K, double* __restrict__ Kt, int* __restrict__ flag,
-                                         int lane) {
-    const int ld = bw + 1;
-    const bool own = lane < 16;
-    double a[16];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) a[c] = (own && c <= lane) ? T[(lane & 15) * kWinStride + c] : 0.0;
-    double dpiv = 1.0;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const double piv = rdlane(a[j], j);
-        if (lane == j) {
-            dpiv = piv;
-            if (!(fabs(piv) > 0.0) || !isfinite(piv)) *flag = 1;
-        }
-        const double l = (own && lane > j) ? a[j] * recip_nr64(piv) : 0.0;
-        const double lp = l * piv;
-#pragma unroll
-        for (int cc = j + 1; cc < 16; ++cc) a[cc] -= lp * rdlane(l, cc);
-        if (lane > j) a[j] = l;
-    }
-    // row `lane` of L11^-1 (unit lower), by forward substitution
-    double li[16];
-#pragma unroll
-    for (int cc = 0; cc < 16; ++cc) li[cc] = (cc == lane) ? 1.0 : 0.0;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const double le = (own && lane > e) ? a[e] : 0.0;
-#pragma unroll
-        for (int cc = 0; cc <= e; ++cc) li[cc] -= le * rdlane(li[cc], e);
-    }
-    if (own) {
-        const double rd = recip_nr64(dpiv);
-#pragma unroll
-        for (int k = 0; k < 16; ++k) Wm[k * 16 + lane] = li[k] * rd;
-        Dv[lane] = dpiv;
-        const int r = 16 * kt + lane;
-        if (r < n) {
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                const int off = lane - c;
-                if (off >= 0 && off <= bw) {
-                    const double v = off == 0 ? dpiv : a[c];
-                    K[(int64_t)r * ld + off] = v;
-                    Kt[(int64_t)(16 * kt + c) * ld + off] = v;
-                }
-            }
-        }
+// f(0), f(1), .. f(N - 1) with the index as a constant
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void win_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        win_for<N, I + 1>(f);
     }
 }
 
-// C. the panel tiles below the diagonal owned by wave W (o = W + 1, W + 5, ...):
-// L = A W on MFMA, in place, L D to LDp, the factor out to K and Kt
-template <int W>
+// lane N of the caller's 16-lane row, in every lane of the row
+template <int N>
+__device__ __forceinline__ double win_bcast(double v) {
+    return __builtin_amdgcn_mov_dpp(v, 0x150 + N, 0xf, 0xf, true);
+}
+
+// B. by one wave: LDL^T of the diagonal tile T, in place, W = L11^-T D^-1 from the
+// rows of L11^-1 into Wm, the pivots into Dv.  Every 16-lane row of the wave holds
+// the whole tile (lane = row of it, row_newbcast broadcasts) and four of the 16
+// columns of L11^-1, so that the elimination is done four times over and the
+// inverse once: this wave's chain of pivots is what a panel waits for.
+__device__ __forceinline__ void win_diag(double* T, double* Wm, double* Dv, int* __restrict__ flag, int lane) {
+    const int row = lane & 15, g = lane >> 4;
+    double* Tr = T + row * kWinStride;
+    double a[16], li[4];  // li[q]: column 4 q + g of row `row` of L11^-1
+#pragma unroll
+    for (int c = 0; c < 16; ++c) a[c] = c <= row ? Tr[c] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) li[q] = 4 * q + g == row ? 1.0 : 0.0;
+    double dpiv = 1.0;
+    win_for<16>([&](auto J) {
+        constexpr int j = decltype(J)::value;
+        const double piv = win_bcast<j>(a[j]);
+        if (row == j) dpiv = piv;
+        const double l = row > j ? a[j] * recip_nr64(piv) : 0.0;
+        const double lp = l * piv;
+        win_for<16>([&](auto C) {
+            constexpr int cc = decltype(C)::value;
+            if constexpr (cc > j) a[cc] -= lp * win_bcast<cc>(l);
+        });
+        // L11^-1 (unit lower) by forward substitution; its row j ends at column j
+#pragma unroll
+        for (int q = 0; q <= j / 4; ++q) li[q] -= l * win_bcast<j>(li[q]);
+        if (row > j) a[j] = l;
+    });
+    if (!(fabs(dpiv) > 0.0) || !isfinite(dpiv)) *flag = 1;
+    const double rd = recip_nr64(dpiv);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) Wm[(4 * q + g) * 16 + row] = li[q] * rd;
+    if (g == 0) {
+        Dv[row] = dpiv;
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+            if (c <= row) Tr[c] = c == row ? dpiv : a[c];
+    }
+}
+
+// the panel's factor tiles (the diagonal one too) out to K and Kt, by waves 1, 2, ..:
+// 16 consecutive entries of a row of K, then of a row of Kt, per 16 lanes; and the
+// panel's z leaves the right-hand side, r(o) -= L(o) D z
+template <int W, int NTW>
+__device__ __forceinline__ void win_store(const double* Wn, const double* LDp, const int* slot, int rows_w, int kt,
+                                          int n, int bw, double* __restrict__ K, double* __restrict__ Kt, double* rw,
+                                          const double* zb, double* __restrict__ du, int lane) {
+    const int ld = bw + 1, x = lane & 15, y = lane >> 4;
+#pragma unroll
+    for (int o = W - 1; o < NTW; o += kWinWaves - 1)
+        if (o < rows_w) {
+            const double* T = Wn + slot[o * kWinMax] * kWinTile;
+            double kv[4], tv[4], u = 0.0;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if (o > 0) u += LDp[o * kWinTile + x * kWinStride + y + 4 * v] * zb[y + 4 * v];
+                kv[v] = T[(y + 4 * v) * kWinStride + x];
+                tv[v] = T[x * kWinStride + y + 4 * v];
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = 16 * (kt + o) + y + 4 * v, off = r - (16 * kt + x);
+                if (r < n && off >= 0 && off <= bw) K[(int64_t)r * ld + off] = kv[v];
+                const int rt = 16 * (kt + o) + x, gc = 16 * kt + y + 4 * v, offt = rt - gc;
+                if (rt < n && offt >= 0 && offt <= bw) Kt[(int64_t)gc * ld + offt] = tv[v];
+            }
+            if (o > 0) {
+                u += __shfl_xor(u, 16);
+                u += __shfl_xor(u, 32);
+                if (y == 0) rw[16 * ((kt + o) & 15) + x] -= u;
+            } else if (y == 0 && 16 * kt + x < n) {
+                du[16 * kt + x] = zb[x];
+            }
+        }
+}
+
+// C. the panel tiles below the diagonal owned by wave W (o = W + 1, W + 9):
+// L = A W on MFMA, in place, L D to LDp; the last wave also takes the panel's part of the
+// forward substitution, z = D^-1 L11^-1 r = W^T r
+template <int W, int NTW>
 __device__ __forceinline__ void win_panel(double* Wn, double* LDp, const double* Wm, const double* Dv,
-                                          const int* slot, int rows_w, int kt, int n, int bw,
-                                          double* __restrict__ K, double* __restrict__ Kt, int lane) {
-    constexpr int NO = (kWinMax - 1 - W + kWinWaves - 1) / kWinWaves;  // tiles of this wave
-    const int ld = bw + 1, c = lane & 15, gc = 16 * kt + c;
+                                          const int* slot, int rows_w, const double* r, double* zb, int lane) {
+    constexpr int NO = NTW - 1 > W ? (NTW - 1 - W + kWinWaves - 1) / kWinWaves : 0;  // tiles of this wave
+    const int c = lane & 15;
     double av[NO > 0 ? NO : 1][4];
     double* T[NO > 0 ? NO : 1];
     double wv[4];
@@ -668,6 +715,14 @@ __device__ __forceinline__ void win_panel(double* Wn, double* LDp, const double*
         for (int ks = 0; ks < 4; ++ks) av[q][ks] = T[q][c * kWinStride + 4 * ks + (lane >> 4)];
     }
     const double dc = Dv[c];
+    if constexpr (W == kWinWaves - 1) {
+        double z = 0.0;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) z += wv[ks] * r[4 * ks + (lane >> 4)];
+        z += __shfl_xor(z, 16);
+        z += __shfl_xor(z, 32);
+        if (lane < 16) zb[c] = z;
+    }
 #pragma unroll
     for (int q = 0; q < NO; ++q) {
         const int o = W + 1 + kWinWaves * q;
@@ -678,13 +733,9 @@ __device__ __forceinline__ void win_panel(double* Wn, double* LDp, const double*
             double* LDt = LDp + o * kWinTile;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int rr = (lane >> 4) + 4 * v, r = 16 * (kt + o) + rr, off = r - gc;
+                const int rr = (lane >> 4) + 4 * v;
                 T[q][rr * kWinStride + c] = t[v];
                 LDt[rr * kWinStride + c] = t[v] * dc;
-                if (r < n && off <= bw) {
-                    K[(int64_t)r * ld + off] = t[v];
-                    Kt[(int64_t)gc * ld + off] = t[v];
-                }
             }
         }
     }
@@ -692,16 +743,19 @@ __device__ __forceinline__ void win_panel(double* Wn, double* LDp, const double*
 
 // D. the trailing tiles owned by wave W: tile (kt + oi, kt + oj), 1 <= oj <= oi,
 // numbered t = (oi - 1) oi / 2 + oj - 1; wave 0 takes t = 0 (the next diagonal
-// tile, which it factors right after), waves 1 .. 3 the others in turn.  Every
+// tile, which it factors right after), the other waves the rest in turn.  Every
 // operand is read first, then the MFMAs run, then the tiles are stored.
 __device__ constexpr bool win_owns(int W, int t) { return W == 0 ? t == 0 : (t > 0 && (t - 1) % (kWinWaves - 1) == W - 1); }
 
-template <int W>
+template <int W, int NTW>
 __device__ __forceinline__ void win_trailing(double* Wn, const double* LDp, const int* slot, int rows_w, int lane) {
+    constexpr int NTT = (NTW - 1) * NTW / 2;
+    constexpr int NT = W == 0 ? 1 : (NTT - 1 - (W - 1) + kWinWaves - 2) / (kWinWaves - 1);
+    if constexpr (NT > 0) {
     const int c = lane & 15, kq = lane >> 4;
-    double aI[kWinMax][4], bJ[kWinMax][4];
+    double aI[NTW][4], bJ[NTW][4];
 #pragma unroll
-    for (int o = 1; o < (W == 0 ? 2 : kWinMax); ++o) {
+    for (int o = 1; o < (W == 0 ? 2 : NTW); ++o) {
         const double* LDt = LDp + min(o, rows_w - 1) * kWinTile;
         const double* Lt = Wn + slot[min(o, rows_w - 1) * kWinMax] * kWinTile;
 #pragma unroll
@@ -710,14 +764,12 @@ __device__ __forceinline__ void win_trailing(double* Wn, const double* LDp, cons
             bJ[o][ks] = Lt[c * kWinStride + 4 * ks + kq];
         }
     }
-    constexpr int NTT = (kWinMax - 1) * kWinMax / 2;
-    constexpr int NT = W == 0 ? 1 : (NTT - 1 - (W - 1) + kWinWaves - 2) / (kWinWaves - 1);
     band_dbl4 acc[NT];
     double* C[NT];
     {
         int q = 0;
 #pragma unroll
-        for (int oi = 1; oi < kWinMax; ++oi)
+        for (int oi = 1; oi < NTW; ++oi)
 #pragma unroll
             for (int oj = 1; oj <= oi; ++oj)
                 if (win_owns(W, (oi - 1) * oi / 2 + oj - 1)) {
@@ -730,7 +782,7 @@ __device__ __forceinline__ void win_trailing(double* Wn, const double* LDp, cons
     {
         int q = 0;
 #pragma unroll
-        for (int oi = 1; oi < kWinMax; ++oi)
+        for (int oi = 1; oi < NTW; ++oi)
 #pragma unroll
             for (int oj = 1; oj <= oi; ++oj)
                 if (win_owns(W, (oi - 1) * oi / 2 + oj - 1)) {
@@ -743,7 +795,7 @@ __device__ __forceinline__ void win_trailing(double* Wn, const double* LDp, cons
     {
         int q = 0;
 #pragma unroll
-        for (int oi = 1; oi < kWinMax; ++oi)
+        for (int oi = 1; oi < NTW; ++oi)
 #pragma unroll
             for (int oj = 1; oj <= oi; ++oj)
                 if (win_owns(W, (oi - 1) * oi / 2 + oj - 1)) {
@@ -754,10 +806,13 @@ __device__ __forceinline__ void win_trailing(double* Wn, const double* LDp, cons
                     ++q;
                 }
     }
+    }
 }
 
+template <int NTW>
 __global__ __launch_bounds__(kWinNT) void macro_band_factor_window(double* __restrict__ K, double* __restrict__ Kt,
-                                                                  int n, int bw, int* __restrict__ flag,
+                                                                  const double* __restrict__ R, int n, int bw,
+                                                                  double* __restrict__ du, int* __restrict__ flag,
                                                                   const int* __restrict__ done) {
     if (*done) return;
     extern __shared__ double win_lds[];
@@ -765,27 +820,33 @@ __global__ __launch_bounds__(kWinNT) void macro_band_factor_window(double* __res
     double* LDp = Wn + kWinSlots * kWinTile;     // the panel's L tiles with column c scaled by D[c]
     double* Wm = LDp + kWinMax * kWinTile;       // W[k * 16 + c]
     double* Dv = Wm + 256;                       // the panel's pivots
-    int* slots = reinterpret_cast<int*>(Dv + 16);  // two buffers of the panel's window-tile slots
-    const int ld = bw + 1, tid = threadIdx.x, lane = tid & 63;
+    double* rw = Dv + 16;                        // the window's right-hand side, row i at i mod kWinRing
+    double* zb = rw + kWinRing;                  // the panel's z = D^-1 L^-1 (-R)
+    int* slots = reinterpret_cast<int*>(zb + 16);  // two buffers of the panel's window-tile slots
+    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ntw = (bw + 15) / 16 + 1, nt = (n + 15) / 16;
-    const int pr = tid >> 4, pc = tid & 15;      // this thread's element of a staged tile
+    constexpr int ntw = NTW;
+    const int nt = (n + 15) / 16;
+    // this thread's element of a staged tile; each half of the workgroup takes every other tile
+    const int pr = (tid >> 4) & 15, pc = tid & 15, half = tid >> 8;
     for (int I = 0; I < min(ntw, nt); ++I)
-        for (int J = 0; J <= I; ++J)
+        for (int J = half; J <= I; J += 2)
             Wn[win_slot(I, J, ntw) * kWinTile + pr * kWinStride + pc] = band_at(K, n, bw, 16 * I + pr, 16 * J + pc);
+    if (tid < 16 * NTW) rw[tid] = tid < n ? -R[tid] : 0.0;
     // slots of panel kt's window tiles: slot[oi * kWinMax + oj] holds tile (kt +
     // oi, kt + oj); two buffers (a panel's E still reads its own while the next
     // table is written)
+    const int soi = tid / kWinMax, soj = tid - soi * kWinMax, sd = soi - soj;
+    const bool smine = tid < kWinMax * kWinMax && sd >= 0 && soi < ntw;
+    const int sm = smine ? ntw - sd : 1, sbase = sd * ntw - ((sd * (sd - 1)) >> 1);
+    int sres = soj % sm;  // (kt + soj) mod sm
     auto fill_slots = [&](int kt) {
-        int* slot = slots + (kt & 1) * kWinMax * kWinMax;
-        if (tid < kWinMax * kWinMax) {
-            const int oi = tid / kWinMax, oj = tid - oi * kWinMax;
-            if (oj <= oi && oi < ntw) slot[tid] = win_slot(kt + oi, kt + oj, ntw);
-        }
+        if (smine) slots[(kt & 1) * kWinMax * kWinMax + tid] = sbase + sres;
+        sres = sres + 1 == sm ? 0 : sres + 1;
     };
     fill_slots(0);
     __syncthreads();
-    if (wave == 0) win_diag(Wn + slots[0] * kWinTile, Wm, Dv, 0, n, bw, K, Kt, flag, lane);
+    if (wave == 0) win_diag(Wn + slots[0] * kWinTile, Wm, Dv, flag, lane);
     __syncthreads();
     // per panel kt (its diagonal tile already factored): C, then D with the next
     // panel's diagonal tile updated and factored by wave 0 while the other waves
@@ -797,50 +858,65 @@ __global__ __launch_bounds__(kWinNT) void macro_band_factor_window(double* __res
         // it takes the slots of the retired panel tiles (kt + d, kt)
         const int In = kt + ntw;
         const bool enter = In < nt;
-        double pf[kWinMax];
+        double pf[(NTW + 1) / 2];
 #pragma unroll
-        for (int d = 0; d < kWinMax; ++d) pf[d] = band_at(K, enter ? n : 0, bw, 16 * In + pr, 16 * (In - d) + pc);
+        for (int d = 0; d < (NTW + 1) / 2; ++d)
+            pf[d] = band_at(K, enter ? n : 0, bw, 16 * In + pr, 16 * (In - 2 * d - half) + pc);
+        const int ri = 16 * In + (tid & 15);
+        const double pr_rhs = enter && ri < n ? -R[ri] : 0.0;
         // C. the tiles below the diagonal: L = A W, in place
-        switch (wave) {
-            case 0: win_panel<0>(Wn, LDp, Wm, Dv, slot, rows_w, kt, n, bw, K, Kt, lane); break;
-            case 1: win_panel<1>(Wn, LDp, Wm, Dv, slot, rows_w, kt, n, bw, K, Kt, lane); break;
-            case 2: win_panel<2>(Wn, LDp, Wm, Dv, slot, rows_w, kt, n, bw, K, Kt, lane); break;
-            default: win_panel<3>(Wn, LDp, Wm, Dv, slot, rows_w, kt, n, bw, K, Kt, lane); break;
-        }
+        win_for<kWinWaves>([&](auto W) {
+            if (wave == decltype(W)::value)
+                win_panel<decltype(W)::value, NTW>(Wn, LDp, Wm, Dv, slot, rows_w, rw + 16 * (kt & 15), zb, lane);
+        });
         __syncthreads();
         // D. the trailing tiles; wave 0 then factors panel kt + 1's diagonal tile
         //    (Wm and Dv are free: C has read them)
-        switch (wave) {
-            case 0:
-                win_trailing<0>(Wn, LDp, slot, rows_w, lane);
-                if (kt + 1 < nt) {
-                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                    win_diag(Wn + slot[kWinMax + 1] * kWinTile, Wm, Dv, kt + 1, n, bw, K, Kt, flag, lane);
-                }
-                break;
-            case 1: win_trailing<1>(Wn, LDp, slot, rows_w, lane); break;
-            case 2: win_trailing<2>(Wn, LDp, slot, rows_w, lane); break;
-            default: win_trailing<3>(Wn, LDp, slot, rows_w, lane); break;
-        }
+        win_for<kWinWaves>([&](auto W) {
+            constexpr int w = decltype(W)::value;
+            if (wave != w) return;
+            win_trailing<w, NTW>(Wn, LDp, slot, rows_w, lane);
+            if constexpr (w > 0) {
+                win_store<w, NTW>(Wn, LDp, slot, rows_w, kt, n, bw, K, Kt, rw, zb, du, lane);
+            } else if (kt + 1 < nt) {
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                win_diag(Wn + slot[kWinMax + 1] * kWinTile, Wm, Dv, flag, lane);
+            }
+        });
         __syncthreads();
         // E. the entering tile row into the retired panel tiles' slots; the next
         //    panel's slot table
         if (enter) {
 #pragma unroll
-            for (int d = 0; d < kWinMax; ++d)
-                if (d < ntw) Wn[slot[d * kWinMax] * kWinTile + pr * kWinStride + pc] = pf[d];
+            for (int d = 0; d < (NTW + 1) / 2; ++d)
+                if (2 * d + half < NTW) Wn[slot[(2 * d + half) * kWinMax] * kWinTile + pr * kWinStride + pc] = pf[d];
+            if (tid < 16) rw[16 * (In & 15) + tid] = pr_rhs;
         }
         fill_slots(kt + 1);
         __syncthreads();
     }
 }
 
-// Both triangular solves of K du = -R on the band factor of
-// macro_band_factor_window (bw <= 144), one workgroup: forward L y = -R on K,
-// then x = D^-1 y - L^T x on Kt (row j of Kt holds column j of L), in blocks of
-// 64 rows.  Each block is staged in LDS while the previous one is solved
+// the factor kernel of a window of ntw tile rows
+inline decltype(&macro_band_factor_window<2>) band_factor_window(int ntw) {
+    switch (ntw) {
+        case 2: return macro_band_factor_window<2>;
+        case 3: return macro_band_factor_window<3>;
+        case 4: return macro_band_factor_window<4>;
+        case 5: return macro_band_factor_window<5>;
+        case 6: return macro_band_factor_window<6>;
+        case 7: return macro_band_factor_window<7>;
+        case 8: return macro_band_factor_window<8>;
+        case 9: return macro_band_factor_window<9>;
+        default: return macro_band_factor_window<kWinMax>;
+    }
+}
+
+// Backward substitution after macro_band_factor_window (bw <= 144), one workgroup:
+// x = z - L^T x on Kt (row j of Kt holds column j of L) with z in du, in blocks of
+// 64 rows from the last.  Each block is staged in LDS while the previous one is solved
 // (double buffer; the next block's rows are read into registers first).  The
-// contributions of earlier (forward) or later (backward) rows are dot products
+// contributions of later rows are dot products
 // over the LDS ring of solved values, split over the four waves; the block's
 // own 64 x 64 triangle is a sweep in wave 0 (lane = row, readlane broadcasts)
 // with every factor entry of the lane's row read before the sweep.
@@ -850,9 +926,7 @@ inline size_t band_solve_win_lds_bytes(int bw) {
     return sizeof(double) * (2 * (size_t)kSolveBlk * (bw + 1) + kRing + 4 * 64);
 }
 
-__global__ __launch_bounds__(kBandNT) void macro_band_solves_win(const double* __restrict__ K,
-                                                                const double* __restrict__ Kt,
-                                                                const double* __restrict__ R, int n, int bw,
+__global__ __launch_bounds__(kBandNT) void macro_band_backward_win(const double* __restrict__ Kt, int n, int bw,
                                                                 double* __restrict__ du,
                                                                 const int* __restrict__ done) {
     if (*done) return;
@@ -863,93 +937,67 @@ __global__ __launch_bounds__(kBandNT) void macro_band_solves_win(const double* _
     double* ring = sv_lds + 2 * bsz;
     double* red = ring + kRing;
     const int nb = (n + kSolveBlk - 1) / kSolveBlk;
-    double pre[kSolvePer];
-    for (int pass = 0; pass < 2; ++pass) {
-        const double* Src = pass == 0 ? K : Kt;
-        // the rows of block bi: forward in increasing, backward in decreasing order
-        auto row0 = [&](int bi) { return (pass == 0 ? bi : nb - 1 - bi) * kSolveBlk; };
-        auto fetch = [&](int bi) {
-            const int r0 = row0(bi), cnt = min(kSolveBlk, n - r0) * ld;
-            const double* src = Src + (int64_t)r0 * ld;
+    double pre[kSolvePer], zpre = 0.0;
+    auto row0 = [&](int bi) { return (nb - 1 - bi) * kSolveBlk; };
+    auto fetch = [&](int bi) {
+        const int r0 = row0(bi), cnt = min(kSolveBlk, n - r0) * ld;
+        const double* src = Kt + (int64_t)r0 * ld;
 #pragma unroll
-            for (int q = 0; q < kSolvePer; ++q) {
-                const int e = tid + kBandNT * q;
-                pre[q] = src[e < cnt ? e : 0];
-            }
-        };
-        auto stage = [&](int bi) {
-            const int r0 = row0(bi), cnt = min(kSolveBlk, n - r0) * ld;
-            double* dst = sv_lds + (bi & 1) * bsz;
-#pragma unroll
-            for (int q = 0; q < kSolvePer; ++q) {
-                const int e = tid + kBandNT * q;
-                if (e < cnt) dst[e] = pre[q];
-            }
-        };
-        fetch(0);
-        stage(0);
-        __syncthreads();
-        for (int bi = 0; bi < nb; ++bi) {
-            const double* Kb = sv_lds + (bi & 1) * bsz;
-            const int i0 = row0(bi), rows = min(kSolveBlk, n - i0), i = i0 + lane;
-            if (bi + 1 < nb) fetch(bi + 1);
-            // contributions of rows outside the block
-            double s0 = 0.0, s1 = 0.0;
-            if (lane < rows) {
-                if (pass == 0) {
-                    const int tmax = min(i, bw);  // t = i - j, j < i0
-                    int t = lane + 1 + wave;
-                    for (; t + 4 <= tmax; t += 8) {
-                        s0 += Kb[lane * ld + t] * ring[(i - t) & (kRing - 1)];
-                        s1 += Kb[lane * ld + t + 4] * ring[(i - t - 4) & (kRing - 1)];
-                    }
-                    if (t <= tmax) s0 += Kb[lane * ld + t] * ring[(i - t) & (kRing - 1)];
-                } else {
-                    const int tmax = min(n - 1 - i, bw);  // t = j - i, j >= i0 + 64
-                    int t = kSolveBlk - lane + wave;
-                    for (; t + 4 <= tmax; t += 8) {
-                        s0 += Kb[lane * ld + t] * ring[(i + t) & (kRing - 1)];
-                        s1 += Kb[lane * ld + t + 4] * ring[(i + t + 4) & (kRing - 1)];
-                    }
-                    if (t <= tmax) s0 += Kb[lane * ld + t] * ring[(i + t) & (kRing - 1)];
-                }
-            }
-            red[wave * 64 + lane] = s0 + s1;
-            __syncthreads();
-            if (wave == 0) {
-                double acc = 0.0;
-                if (lane < rows) {
-                    const double s4 = red[lane] + red[64 + lane] + red[128 + lane] + red[192 + lane];
-                    acc = pass == 0 ? -R[i] - s4 : du[i] / Kb[lane * ld] - s4;  // du[i]: stored by this lane
-                }
-                const int lr = min(lane, rows - 1);
-                if (pass == 0) {
-                    double l[kSolveBlk];
-#pragma unroll
-                    for (int k = 0; k < kSolveBlk; ++k) {
-                        const int off = lane - k;
-                        l[k] = ((off > 0) & (off <= bw)) ? Kb[lr * ld + (off > 0 && off <= bw ? off : 0)] : 0.0;
-                    }
-#pragma unroll
-                    for (int k = 0; k < kSolveBlk; ++k) acc -= l[k] * rdlane(acc, k);
-                } else {
-                    double l[kSolveBlk];
-#pragma unroll
-                    for (int k = 0; k < kSolveBlk; ++k) {
-                        const int off = k - lane;
-                        l[k] = ((off > 0) & (off <= bw)) ? Kb[lr * ld + (off > 0 && off <= bw ? off : 0)] : 0.0;
-                    }
-#pragma unroll
-                    for (int k = kSolveBlk - 1; k >= 0; --k) acc -= l[k] * rdlane(acc, k);
-                }
-                if (lane < rows) {
-                    ring[i & (kRing - 1)] = acc;
-                    du[i] = acc;
-                }
-            }
-            if (bi + 1 < nb) stage(bi + 1);
-            __syncthreads();
+        for (int q = 0; q < kSolvePer; ++q) {
+            const int e = tid + kBandNT * q;
+            pre[q] = src[e < cnt ? e : 0];
         }
+        zpre = du[min(r0 + lane, n - 1)];
+    };
+    auto stage = [&](int bi) {
+        const int r0 = row0(bi), cnt = min(kSolveBlk, n - r0) * ld;
+        double* dst = sv_lds + (bi & 1) * bsz;
+#pragma unroll
+        for (int q = 0; q < kSolvePer; ++q) {
+            const int e = tid + kBandNT * q;
+            if (e < cnt) dst[e] = pre[q];
+        }
+    };
+    fetch(0);
+    stage(0);
+    __syncthreads();
+    for (int bi = 0; bi < nb; ++bi) {
+        const double* Kb = sv_lds + (bi & 1) * bsz;
+        const int i0 = row0(bi), rows = min(kSolveBlk, n - i0), i = i0 + lane;
+        const double z = zpre;
+        if (bi + 1 < nb) fetch(bi + 1);
+        // contributions of the rows after the block
+        double s0 = 0.0, s1 = 0.0;
+        if (lane < rows) {
+            const int tmax = min(n - 1 - i, bw);  // t = j - i, j >= i0 + 64
+            int t = kSolveBlk - lane + wave;
+            for (; t + 4 <= tmax; t += 8) {
+                s0 += Kb[lane * ld + t] * ring[(i + t) & (kRing - 1)];
+                s1 += Kb[lane * ld + t + 4] * ring[(i + t + 4) & (kRing - 1)];
+            }
+            if (t <= tmax) s0 += Kb[lane * ld + t] * ring[(i + t) & (kRing - 1)];
+        }
+        red[wave * 64 + lane] = s0 + s1;
+        __syncthreads();
+        if (wave == 0) {
+            double acc = 0.0;
+            if (lane < rows) acc = z - (red[lane] + red[64 + lane] + red[128 + lane] + red[192 + lane]);
+            const int lr = min(lane, rows - 1);
+            double l[kSolveBlk];
+#pragma unroll
+            for (int k = 0; k < kSolveBlk; ++k) {
+                const int off = k - lane;
+                l[k] = ((off > 0) & (off <= bw)) ? Kb[lr * ld + (off > 0 && off <= bw ? off : 0)] : 0.0;
+            }
+#pragma unroll
+            for (int k = kSolveBlk - 1; k >= 0; --k) acc -= l[k] * rdlane(acc, k);
+            if (lane < rows) {
+                ring[i & (kRing - 1)] = acc;
+                du[i] = acc;
+            }
+        }
+        if (bi + 1 < nb) stage(bi + 1);
+        __syncthreads();
     }
 }
 
@@ -1050,10 +1098,11 @@ int fehmm_create(const fehmm_desc* d, fehmm* out) {
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         FH_HIP(hipFuncSetAttribute((const void*)macro_band_solve_blocked<4>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-        FH_HIP(hipFuncSetAttribute((const void*)macro_band_solves_win, hipFuncAttributeMaxDynamicSharedMemorySize,
+        FH_HIP(hipFuncSetAttribute((const void*)macro_band_backward_win, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)band_solve_win_lds_bytes(16 * kWinMax - 16)));
-        FH_HIP(hipFuncSetAttribute((const void*)macro_band_factor_window, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)band_win_lds_bytes()));
+        for (int ntw = 2; ntw <= kWinMax; ++ntw)
+            FH_HIP(hipFuncSetAttribute((const void*)band_factor_window(ntw), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)band_win_lds_bytes()));
         band_prepared = true;
     }
     auto h = std::make_unique<fehmm_s>();
@@ -1280,10 +1329,10 @@ static int enqueue_step(fehmm_s* h, int it_begin, int it_end, bool with_init) {
         const int slots = (kPanel + h->bw + 63) / 64;  // panel rows per lane
         const size_t lds = band_lds_bytes(h->bw);
         if (band_win_fits(h->bw)) {
-            hipLaunchKernelGGL(macro_band_factor_window, dim3(1), dim3(kWinNT), band_win_lds_bytes(), s, h->d_K,
-                               h->d_Kt, h->ndof, h->bw, &st->band_flag, done);
-            hipLaunchKernelGGL(macro_band_solves_win, dim3(1), dim3(kBandNT), band_solve_win_lds_bytes(h->bw), s,
-                               h->d_K, h->d_Kt, h->d_R, h->ndof, h->bw, h->d_du, done);
+            hipLaunchKernelGGL(band_factor_window((h->bw + 15) / 16 + 1), dim3(1), dim3(kWinNT), band_win_lds_bytes(), s, h->d_K,
+                               h->d_Kt, h->d_R, h->ndof, h->bw, h->d_du, &st->band_flag, done);
+            hipLaunchKernelGGL(macro_band_backward_win, dim3(1), dim3(kBandNT), band_solve_win_lds_bytes(h->bw), s,
+                               h->d_Kt, h->ndof, h->bw, h->d_du, done);
         } else if (slots <= 3)
             hipLaunchKernelGGL(macro_band_solve_blocked<3>, dim3(1), dim3(kBandNT), lds, s, h->d_K, h->d_Kt, h->d_R,
                                h->ndof, h->bw, h->d_du, &st->band_flag, done);
