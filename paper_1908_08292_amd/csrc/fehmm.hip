@@ -1,6 +1,6 @@
 // fehmm.hip -- two-scale FE-HMM driver (include/fehmm.h): macro Q1 mesh, device
 // gather of the quadrature-point deformation gradients, the batched RVE solves,
-// deterministic colour-ordered assembly of the banded macro system, and a
+// deterministic colour-ordered assembly of the banded macro system (one launch), and a
 // single-workgroup banded LDL^T solve; the macro Newton loop runs on the host
 // with one device-to-host norm per iteration.
 #include <hip/hip_runtime.h>
@@ -96,62 +96,45 @@ __global__ void macro_zero_ints(int* __restrict__ x, int64_t n, const int* __res
     if (t < n) x[t] = 0;
 }
 
-__global__ void macro_zero(double* __restrict__ x, int64_t n, const int* __restrict__ done) {
+// The assembled system, one thread per entry of the lower band K[i * (bw + 1) + k],
+// k = i - j >= 0, each written once: the up to four cells at a node (adj[4 node + colour]
+// = 4 cell + local node, -1 where there is none) are summed in the order of their
+// colours, so the result does not depend on the launch.  Dirichlet dofs get the
+// identity row and column and a zero residual (their increment is applied by
+// macro_update).  In the first macro iteration of a load step (dud non-null) the
+// prescribed increment moves the free dofs through the coupling block, R_f += K_fd dud.
+// Latency-bound.  Zeroing, four coloured scatters, that product and the Dirichlet rows
+// as seven or eight launches of at least 4.5 us took 64 us per iteration at 4802
+// unknowns and bandwidth 101 (122 us in the first of a step) and 32 us at 50 unknowns;
+// this one launch takes 11.4 and 6.9 us.
+__global__ void macro_assemble(const int* __restrict__ adj, const int* __restrict__ conn,
+                               const double* __restrict__ ke, const double* __restrict__ fe,
+                               const int* __restrict__ fixed, const double* __restrict__ dud, int ndof, int bw,
+                               double* __restrict__ K, double* __restrict__ R, const int* __restrict__ done) {
     if (*done) return;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) x[t] = 0.0;
-}
-
-// add the elements of one colour (no two share a node) into the lower band
-// K[i * (bw + 1) + (i - j)], i >= j, and into R
-__global__ void macro_scatter(const int* __restrict__ elist, int nel, const int* __restrict__ conn,
-                              const double* __restrict__ ke, const double* __restrict__ fe, int bw,
-                              double* __restrict__ K, double* __restrict__ R, const int* __restrict__ done) {
-    if (*done) return;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nel * 8) return;
-    const int e = elist[t >> 3], r = t & 7;
-    const int gi = 2 * conn[4 * e + (r >> 1)] + (r & 1);
-    R[gi] += fe[8 * e + r];
-    for (int c = 0; c < 8; ++c) {
-        const int gj = 2 * conn[4 * e + (c >> 1)] + (c & 1);
-        if (gj <= gi) K[(int64_t)gi * (bw + 1) + (gi - gj)] += ke[64 * e + 8 * r + c];
-    }
-}
-
-// first macro iteration of a load step: the prescribed increment moves the free
-// dofs through the coupling block, R_f += K_fd dud (K symmetric, lower band:
-// K(i, j) for j <= i sits in row i, for j > i as K(j, i) in row j)
-__global__ void macro_dirichlet_rhs(const double* __restrict__ K, const double* __restrict__ dud,
-                                    const int* __restrict__ fixed, int ndof, int bw, double* __restrict__ R,
-                                    const int* __restrict__ done) {
-    if (*done) return;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ndof || fixed[i]) return;
-    double acc = 0.0;
-    for (int k = 1; k <= bw; ++k) {
-        const int jl = i - k, ju = i + k;
-        if (jl >= 0) acc += K[(int64_t)i * (bw + 1) + k] * dud[jl];
-        if (ju < ndof) acc += K[(int64_t)ju * (bw + 1) + k] * dud[ju];
-    }
-    R[i] += acc;
-}
-
-// Dirichlet dofs: identity row/column, zero residual (their increment is
-// applied by macro_update)
-__global__ void macro_bc(const int* __restrict__ fixed, int ndof, int bw, double* __restrict__ K,
-                         double* __restrict__ R, const int* __restrict__ done) {
-    if (*done) return;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = (int)(t / (bw + 1)), k = (int)(t - (int64_t)i * (bw + 1)), j = i - k;
     if (i >= ndof) return;
-    for (int k = 1; k <= bw; ++k) {
-        const int j = i - k;
-        if (j >= 0 && (fixed[i] || fixed[j])) K[(int64_t)i * (bw + 1) + k] = 0.0;
+    double v = 0.0, f = 0.0, fd = 0.0;
+    if (j >= 0) {
+        const int b = j >> 1, cj = j & 1;
+        for (int q = 0; q < 4; ++q) {
+            const int s = adj[4 * (i >> 1) + q];
+            if (s < 0) continue;
+            const int e = s >> 2, r = 2 * (s & 3) + (i & 1);
+            const double* row = ke + 64 * (int64_t)e + 8 * r;
+            for (int lb = 0; lb < 4; ++lb)
+                if (conn[4 * e + lb] == b) v += row[2 * lb + cj];
+            if (k == 0) {
+                f += fe[8 * (int64_t)e + r];
+                if (dud)
+                    for (int c = 0; c < 8; ++c) fd += row[c] * dud[2 * conn[4 * e + (c >> 1)] + (c & 1)];
+            }
+        }
+        if (fixed[i] || fixed[j]) v = k == 0 ? 1.0 : 0.0;
+        if (k == 0) R[i] = fixed[i] ? 0.0 : f + fd;
     }
-    if (fixed[i]) {
-        K[(int64_t)i * (bw + 1)] = 1.0;
-        R[i] = 0.0;
-    }
+    K[t] = v;
 }
 
 // Device-side state of one load step.  The macro Newton's decisions are taken
@@ -1021,13 +1004,13 @@ struct fehmm_s {
     int nnode = 0, nelem = 0, ndof = 0, nqp = 0, bw = 0;
     std::vector<double> xy;
     std::vector<int> conn, fixed;
-    std::vector<std::vector<int>> colour;
+    std::vector<int> adj;  // the cells at each node, by colour
     MacroGeom geom{};
     rve_batch batch = nullptr;
     int64_t state_doubles = 0;
     hipStream_t stream = nullptr;
     // device
-    int *d_conn = nullptr, *d_fixed = nullptr, *d_col[4] = {nullptr, nullptr, nullptr, nullptr};
+    int *d_conn = nullptr, *d_fixed = nullptr, *d_adj = nullptr;
     int *d_status = nullptr, *d_iters = nullptr, *d_rightx = nullptr;
     StepState* d_state = nullptr;
     double *d_u = nullptr, *d_du = nullptr, *d_F = nullptr, *d_P = nullptr, *d_A = nullptr;
@@ -1055,8 +1038,7 @@ struct fehmm_s {
     } while (0)
 
 static void fehmm_free(fehmm_s* h) {
-    int* ip[] = {h->d_conn, h->d_fixed, h->d_col[0], h->d_col[1], h->d_col[2], h->d_col[3], h->d_status,
-                 h->d_iters, h->d_rightx};
+    int* ip[] = {h->d_conn, h->d_fixed, h->d_adj, h->d_status, h->d_iters, h->d_rightx};
     for (int* p : ip) (void)hipFree(p);
     (void)hipFree(h->d_state);
     if (h->gexec) (void)hipGraphExecDestroy(h->gexec);
@@ -1159,7 +1141,7 @@ int fehmm_create(const fehmm_desc* d, fehmm* out) {
                 h->xy[2 * id[j * (nx + 1) + i]] = i * hx;
                 h->xy[2 * id[j * (nx + 1) + i] + 1] = j * hy;
             }
-    h->colour.resize(4);
+    h->adj.assign(4 * (size_t)h->nnode, -1);
     for (int j = 0; j < ny; ++j)
         for (int i = 0; i < nx; ++i)
             if (keep[j * nx + i]) {
@@ -1168,7 +1150,7 @@ int fehmm_create(const fehmm_desc* d, fehmm* out) {
                 h->conn.push_back(id[j * (nx + 1) + i + 1]);
                 h->conn.push_back(id[(j + 1) * (nx + 1) + i + 1]);
                 h->conn.push_back(id[(j + 1) * (nx + 1) + i]);
-                h->colour[(i & 1) + 2 * (j & 1)].push_back(e);
+                for (int a = 0; a < 4; ++a) h->adj[4 * (size_t)h->conn[4 * e + a] + (i & 1) + 2 * (j & 1)] = 4 * e + a;
             }
     h->ndof = 2 * h->nnode;
     h->nqp = h->geom.npt * h->nelem;
@@ -1210,9 +1192,8 @@ int fehmm_create(const fehmm_desc* d, fehmm* out) {
         return RVE_OK;
     };
     fehmm_s* H = h.get();
-    if ((st = up(&H->d_conn, H->conn)) || (st = up(&H->d_fixed, H->fixed)) || (st = up(&H->d_col[0], H->colour[0])) ||
-        (st = up(&H->d_col[1], H->colour[1])) || (st = up(&H->d_col[2], H->colour[2])) ||
-        (st = up(&H->d_col[3], H->colour[3])) || (st = zal(&H->d_u, H->ndof)) || (st = zal(&H->d_du, H->ndof)) || (st = zal(&H->d_dud, H->ndof)) ||
+    if ((st = up(&H->d_conn, H->conn)) || (st = up(&H->d_fixed, H->fixed)) || (st = up(&H->d_adj, H->adj)) ||
+        (st = zal(&H->d_u, H->ndof)) || (st = zal(&H->d_du, H->ndof)) || (st = zal(&H->d_dud, H->ndof)) ||
         (st = up(&H->d_rightx, rightx)) || (st = zal(&H->d_F, 4 * (int64_t)H->nqp)) ||
         (st = zal(&H->d_P, 4 * (int64_t)H->nqp)) || (st = zal(&H->d_A, 16 * (int64_t)H->nqp)) ||
         (st = zal(&H->d_w, H->state_doubles)) || (st = zal(&H->d_ke, 64 * (int64_t)H->nelem)) ||
@@ -1310,19 +1291,9 @@ static int enqueue_step(fehmm_s* h, int it_begin, int it_end, bool with_init) {
         hipLaunchKernelGGL(macro_element, dim3(nblk(8 * (int64_t)h->nelem, 256)), dim3(256), 0, s, h->nelem,
                            h->d_P, h->d_A, h->geom, h->d_ke, h->d_fe, done);
         const int64_t nK = (int64_t)h->ndof * (h->bw + 1);
-        hipLaunchKernelGGL(macro_zero, dim3(nblk(nK, 256)), dim3(256), 0, s, h->d_K, nK, done);
-        hipLaunchKernelGGL(macro_zero, dim3(nblk(h->ndof, 256)), dim3(256), 0, s, h->d_R, (int64_t)h->ndof, done);
-        for (int c = 0; c < 4; ++c) {
-            const int nel = (int)h->colour[c].size();
-            if (nel == 0) continue;
-            hipLaunchKernelGGL(macro_scatter, dim3(nblk(8 * (int64_t)nel, 256)), dim3(256), 0, s, h->d_col[c], nel,
-                               h->d_conn, h->d_ke, h->d_fe, h->bw, h->d_K, h->d_R, done);
-        }
-        if (it == 0)
-            hipLaunchKernelGGL(macro_dirichlet_rhs, dim3(nblk(h->ndof, 256)), dim3(256), 0, s, h->d_K, h->d_dud,
-                               h->d_fixed, h->ndof, h->bw, h->d_R, done);
-        hipLaunchKernelGGL(macro_bc, dim3(nblk(h->ndof, 256)), dim3(256), 0, s, h->d_fixed, h->ndof, h->bw, h->d_K,
-                           h->d_R, done);
+        hipLaunchKernelGGL(macro_assemble, dim3(nblk(nK, 256)), dim3(256), 0, s, h->d_adj, h->d_conn, h->d_ke, h->d_fe,
+                           h->d_fixed, it == 0 ? (const double*)h->d_dud : (const double*)nullptr, h->ndof, h->bw,
+                           h->d_K, h->d_R, done);
         hipLaunchKernelGGL(macro_norm_step, dim3(1), dim3(256), 0, s, h->d_R, h->ndof, h->d_status, h->d_iters,
                            h->nqp, alt ? 1 : 0, h->surr ? (const int*)h->d_scnt : (const int*)nullptr, st, it, rtol,
                            d.max_macro_iter);
