@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kBandNT) void macro_band_solve_blocked(double* __re
 // retired panel column.  Per panel (tile column kt), one workgroup of eight
 // waves: wave 0 factors the diagonal tile and forms W = L11^-T D^-1; the tiles
 // below become L = A W on MFMA (in place); the trailing tiles take -L(I) D L(J)^T
-// on MFMA; the factor goes out to K and Kt (band entries only); the entering tile
+// on MFMA; the factor's columns go out to Kt (band entries only); the entering tile
 // row, read from K while the panel is processed (no earlier panel reaches it), is
 // stored.  The right-hand side goes along: z = D^-1 L^-1 (-R) panel by panel, so
 // that only the backward substitution is left.  The matrix is read once and the
@@ -641,29 +641,26 @@ __device__ __forceinline__ void win_diag(double* T, double* Wm, double* Dv, int*
     }
 }
 
-// the panel's factor tiles (the diagonal one too) out to K and Kt, by waves 1, 2, ..:
-// 16 consecutive entries of a row of K, then of a row of Kt, per 16 lanes; and the
-// panel's z leaves the right-hand side, r(o) -= L(o) D z
+// the panel's factor tiles (the diagonal one too) out to Kt, by waves 1, 2, ..: 16
+// consecutive entries of a row of Kt per 16 lanes; and the panel's z leaves the
+// right-hand side, r(o) -= L(o) D z
 template <int W, int NTW>
 __device__ __forceinline__ void win_store(const double* Wn, const double* LDp, const int* slot, int rows_w, int kt,
-                                          int n, int bw, double* __restrict__ K, double* __restrict__ Kt, double* rw,
-                                          const double* zb, double* __restrict__ du, int lane) {
+                                          int n, int bw, double* __restrict__ Kt, double* rw, const double* zb,
+                                          double* __restrict__ du, int lane) {
     const int ld = bw + 1, x = lane & 15, y = lane >> 4;
 #pragma unroll
     for (int o = W - 1; o < NTW; o += kWinWaves - 1)
         if (o < rows_w) {
             const double* T = Wn + slot[o * kWinMax] * kWinTile;
-            double kv[4], tv[4], u = 0.0;
+            double tv[4], u = 0.0;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 if (o > 0) u += LDp[o * kWinTile + x * kWinStride + y + 4 * v] * zb[y + 4 * v];
-                kv[v] = T[(y + 4 * v) * kWinStride + x];
                 tv[v] = T[x * kWinStride + y + 4 * v];
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int r = 16 * (kt + o) + y + 4 * v, off = r - (16 * kt + x);
-                if (r < n && off >= 0 && off <= bw) K[(int64_t)r * ld + off] = kv[v];
                 const int rt = 16 * (kt + o) + x, gc = 16 * kt + y + 4 * v, offt = rt - gc;
                 if (rt < n && offt >= 0 && offt <= bw) Kt[(int64_t)gc * ld + offt] = tv[v];
             }
@@ -793,7 +790,7 @@ __device__ __forceinline__ void win_trailing(double* Wn, const double* LDp, cons
 }
 
 template <int NTW>
-__global__ __launch_bounds__(kWinNT) void macro_band_factor_window(double* __restrict__ K, double* __restrict__ Kt,
+__global__ __launch_bounds__(kWinNT) void macro_band_factor_window(const double* __restrict__ K, double* __restrict__ Kt,
                                                                   const double* __restrict__ R, int n, int bw,
                                                                   double* __restrict__ du, int* __restrict__ flag,
                                                                   const int* __restrict__ done) {
@@ -860,7 +857,7 @@ __global__ __launch_bounds__(kWinNT) void macro_band_factor_window(double* __res
             if (wave != w) return;
             win_trailing<w, NTW>(Wn, LDp, slot, rows_w, lane);
             if constexpr (w > 0) {
-                win_store<w, NTW>(Wn, LDp, slot, rows_w, kt, n, bw, K, Kt, rw, zb, du, lane);
+                win_store<w, NTW>(Wn, LDp, slot, rows_w, kt, n, bw, Kt, rw, zb, du, lane);
             } else if (kt + 1 < nt) {
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 win_diag(Wn + slot[kWinMax + 1] * kWinTile, Wm, Dv, flag, lane);
@@ -1300,8 +1297,8 @@ static int enqueue_step(fehmm_s* h, int it_begin, int it_end, bool with_init) {
         const int slots = (kPanel + h->bw + 63) / 64;  // panel rows per lane
         const size_t lds = band_lds_bytes(h->bw);
         if (band_win_fits(h->bw)) {
-            hipLaunchKernelGGL(band_factor_window((h->bw + 15) / 16 + 1), dim3(1), dim3(kWinNT), band_win_lds_bytes(), s, h->d_K,
-                               h->d_Kt, h->d_R, h->ndof, h->bw, h->d_du, &st->band_flag, done);
+            hipLaunchKernelGGL(band_factor_window((h->bw + 15) / 16 + 1), dim3(1), dim3(kWinNT), band_win_lds_bytes(), s,
+                               h->d_K, h->d_Kt, h->d_R, h->ndof, h->bw, h->d_du, &st->band_flag, done);
             hipLaunchKernelGGL(macro_band_backward_win, dim3(1), dim3(kBandNT), band_solve_win_lds_bytes(h->bw), s,
                                h->d_Kt, h->ndof, h->bw, h->d_du, done);
         } else if (slots <= 3)
