@@ -104,7 +104,7 @@ __global__ void macro_zero_ints(int* __restrict__ x, int64_t n, const int* __res
 // macro_update).  In the first macro iteration of a load step (dud non-null) the
 // prescribed increment moves the free dofs through the coupling block, R_f += K_fd dud.
 // Latency-bound.  Zeroing, four coloured scatters, that product and the Dirichlet rows
-// as seven or eight launches of at least 4.5 us took 64 us per iteration at 4802
+// as seven or eight launches of at least 4.5 us took 64 us per iteration at 4312
 // unknowns and bandwidth 101 (122 us in the first of a step) and 32 us at 50 unknowns;
 // this one launch takes 11.4 and 6.9 us.
 __global__ void macro_assemble(const int* __restrict__ adj, const int* __restrict__ conn,
@@ -544,10 +544,10 @@ __global__ __launch_bounds__(kBandNT) void macro_band_solve_blocked(double* __re
 // The kernel is compiled for each number of tile rows: the tiles and the loops over
 // them are constants, and nothing is done for tiles that the band does not have.
 // What bounds it is the chain of dependent panels: the diagonal tile's sixteen pivots,
-// then one tile of L and one trailing tile, about 2.8 us in all.  At 4802 unknowns and
-// bandwidth 101 (301 panels) the factorization took 1378 us with four waves, ten tile
+// then one tile of L and one trailing tile, about 2.9 us in all.  At 4312 unknowns and
+// bandwidth 101 (270 panels) the factorization took 1378 us with four waves, ten tile
 // rows for every band and the stores within the panel, 917 us without these, and with
-// the forward substitution within it 1078 us, of which eight waves leave 864 us; the
+// the forward substitution within it 1078 us, of which eight waves leave 787 us; the
 // two substitutions took 553 us, the backward one takes 231.
 constexpr int kWinMax = 10;                                  // tile rows of the window (bw <= 144)
 constexpr int kWinSlots = kWinMax * (kWinMax + 1) / 2;       // window tiles
@@ -725,12 +725,27 @@ __device__ __forceinline__ void win_panel(double* Wn, double* LDp, const double*
 // numbered t = (oi - 1) oi / 2 + oj - 1; wave 0 takes t = 0 (the next diagonal
 // tile, which it factors right after), the other waves the rest in turn.  Every
 // operand is read first, then the MFMAs run, then the tiles are stored.
-__device__ constexpr bool win_owns(int W, int t) { return W == 0 ? t == 0 : (t > 0 && (t - 1) % (kWinWaves - 1) == W - 1); }
+// Wave 4 shares its SIMD with wave 0, whose pivots wait for its MFMAs.  Up to eight
+// tile rows, where the pivots are what a panel takes, it has no trailing tile (4312
+// unknowns, bandwidth 101: 854 -> 787 us); from nine on the tiles weigh as much and
+// it takes its share (5800 unknowns, bandwidth 117: 1253 us with, 1281 without; 7504 at
+// 133: 1670 and 1754).
+template <int NTW>
+__device__ constexpr bool win_owns(int W, int t) {
+    if (NTW > 8) return W == (t == 0 ? 0 : (t - 1) % (kWinWaves - 1) + 1);
+    const int turn = (t - 1) % (kWinWaves - 2);
+    return W == (t == 0 ? 0 : turn < kWinWaves / 2 - 1 ? turn + 1 : turn + 2);
+}
+template <int NTW>
+__device__ constexpr int win_owned(int W) {
+    int n = 0;
+    for (int t = 0; t < NTW * (NTW - 1) / 2; ++t) n += win_owns<NTW>(W, t) ? 1 : 0;
+    return n;
+}
 
 template <int W, int NTW>
 __device__ __forceinline__ void win_trailing(double* Wn, const double* LDp, const int* slot, int rows_w, int lane) {
-    constexpr int NTT = (NTW - 1) * NTW / 2;
-    constexpr int NT = W == 0 ? 1 : (NTT - 1 - (W - 1) + kWinWaves - 2) / (kWinWaves - 1);
+    constexpr int NT = win_owned<NTW>(W);
     if constexpr (NT > 0) {
     const int c = lane & 15, kq = lane >> 4;
     double aI[NTW][4], bJ[NTW][4];
@@ -752,7 +767,7 @@ __device__ __forceinline__ void win_trailing(double* Wn, const double* LDp, cons
         for (int oi = 1; oi < NTW; ++oi)
 #pragma unroll
             for (int oj = 1; oj <= oi; ++oj)
-                if (win_owns(W, (oi - 1) * oi / 2 + oj - 1)) {
+                if (win_owns<NTW>(W, (oi - 1) * oi / 2 + oj - 1)) {
                     C[q] = Wn + slot[min(oi, rows_w - 1) * kWinMax + min(oj, rows_w - 1)] * kWinTile;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) acc[q][v] = C[q][(kq + 4 * v) * kWinStride + c];
@@ -765,7 +780,7 @@ __device__ __forceinline__ void win_trailing(double* Wn, const double* LDp, cons
         for (int oi = 1; oi < NTW; ++oi)
 #pragma unroll
             for (int oj = 1; oj <= oi; ++oj)
-                if (win_owns(W, (oi - 1) * oi / 2 + oj - 1)) {
+                if (win_owns<NTW>(W, (oi - 1) * oi / 2 + oj - 1)) {
 #pragma unroll
                     for (int ks = 0; ks < 4; ++ks)
                         acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(aI[oi][ks], bJ[oj][ks], acc[q], 0, 0, 0);
@@ -778,7 +793,7 @@ __device__ __forceinline__ void win_trailing(double* Wn, const double* LDp, cons
         for (int oi = 1; oi < NTW; ++oi)
 #pragma unroll
             for (int oj = 1; oj <= oi; ++oj)
-                if (win_owns(W, (oi - 1) * oi / 2 + oj - 1)) {
+                if (win_owns<NTW>(W, (oi - 1) * oi / 2 + oj - 1)) {
                     if (oi < rows_w) {
 #pragma unroll
                         for (int v = 0; v < 4; ++v) C[q][(kq + 4 * v) * kWinStride + c] = acc[q][v];
