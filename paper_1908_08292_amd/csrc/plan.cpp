@@ -382,6 +382,7 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
             panel = std::max(panel, (int64_t)F.p * F.m - (int64_t)F.p * (F.p - 1) / 2 + 2 * 16 * (d * d + 1) + 2);
         P.panel_path = P.lds_path || (d == 2 && mm <= 256 && panel * 8 <= kLdsFrontBytes);
     }
+    P.wide_rhs = P.panel_path && !P.lds_path;
     if (P.panel_path) {
         int64_t off = 2;  // (element 0 stays zero: read in place of entries a child does not have)
         for (int s = 0; s < ns; ++s) {
@@ -395,7 +396,9 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
         // condensation beside the Newton residual) and what they take in LDS: two
         // buffers of a 16-pivot block's rows beside the panel; in the backward
         // substitution the front's rows and one partial sum per wave
-        const int64_t rhs_cols = d * d + (d == 2 ? 1 : 0), block_rhs = 2 * 16 * rhs_cols + 2;
+        // (wide_rhs: FP64 columns are two elements of FP32 factors, on even offsets)
+        const int64_t rhs_cols = d * d + (d == 2 ? 1 : 0), rw = P.wide_rhs ? 2 : 1;
+        const int64_t block_rhs = 2 * 16 * rhs_cols * rw + 1 + rw;
         auto packed_panel = [](const FrontHost& X) { return (int64_t)X.p * X.m - (int64_t)X.p * (X.p - 1) / 2; };
         // targets of the original entries as offsets in the packed panel
         for (const FrontHost& F : P.fronts)
@@ -457,7 +460,7 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
         // their separator from 16 x 16 on), as long as that leaves a task per wave.
         auto u_elems = [&](const FrontHost& X) {
             const int64_t mu = X.m - X.p;
-            return mu * (mu + 1) / 2 + mu * rhs_cols;
+            return (mu * (mu + 1) / 2 + rw - 1) / rw * rw + mu * rhs_cols * rw;
         };
         std::vector<int64_t> inner(ns, 0);  // LDS of a subtree's inner update matrices
         std::vector<char> fused(ns, 0);

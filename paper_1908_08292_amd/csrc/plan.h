@@ -87,6 +87,8 @@ struct PlanHost {
     int64_t wg_elems = 0;      // LDS elements of the largest workgroup step (panels + block-row rhs)
     int64_t bs_slice = 0;      // FP64 scratch per wave of the backward substitution
     bool panel_path = false;   // every front's panel fits LDS, with a thread per row (m <= 256)
+    bool wide_rhs = false;     // panel_path where whole packed fronts would not fit: with FP32 factors the
+                               // right-hand sides are FP64 (their LDS and update-matrix room is twice T's)
     bool lds_path = false;     // whole packed fronts would fit as well (what plan_schedule reports on)
     int64_t L_size = 0;        // doubles of L + D + y storage
     int64_t U_stack = 0;       // doubles of the update-matrix stack

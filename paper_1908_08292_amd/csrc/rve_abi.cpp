@@ -173,7 +173,8 @@ int plan_device(PlanEntry* e) {
                      e->d_asm_dst, e->d_asm_src, e->d_ea_dst, e->d_inv, e->d_childrec, e->d_back, e->d_wave_hbeg,
                      (int32_t)P.wave_hbeg.size() - 1, (int32_t)P.wave_slice, e->d_wg_steps,
                      (int32_t)(P.wg_steps.size() / kStepFronts), e->d_task, e->d_task_beg,
-                     std::max<int32_t>((int32_t)P.task_beg.size() - 1, 0), (int32_t)P.ul_base, (int32_t)P.ul_stride, 0};
+                     std::max<int32_t>((int32_t)P.task_beg.size() - 1, 0), (int32_t)P.ul_base, (int32_t)P.ul_stride,
+                     P.wide_rhs ? 1 : 0, 0};
     if (P.wave_hbeg.empty()) e->dev.nwave_h = 0;
     e->dev.bc = P.bc;
     // dynamic LDS of a plan whose panels live there: the wave phase's slices, the

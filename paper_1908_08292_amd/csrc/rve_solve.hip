@@ -1656,6 +1656,12 @@ __device__ __attribute__((noinline)) void backsolve_glb(const RveCtx& c, Smem& s
 //   4. after the last block the update matrix is formed tile by tile in MFMA
 //      accumulators over all p pivots, the children's entries (gathered through
 //      the inverse row maps) added, and written once, straight to the stack.
+// Storage type T (panels, update matrices) and arithmetic type C of the pivots and the
+// right-hand sides (block entries in registers, rhs rows of the blocks and of the
+// update matrices): equal, except for FP32 factors of plans whose packed fronts do not
+// fit LDS (DevPlan::wide_rhs), which keep C = double: with C = float their condensed
+// tangents are 2 to 4 times further from FP64's (43 x 43, stiffness ratio 50, RMS of 64
+// RVEs: 8.1e-10 against 2.4e-10), for 1 to 3 % of the time of a solve.
 // A panel needs 2 p / m of a packed front's LDS: two four-wave workgroups fit a
 // CU up to 32 x 32 in FP64 (81.4 KB each), where whole packed fronts (139 KB)
 // allowed one.  Small subtrees run the same code one front per wave first, then
@@ -1725,6 +1731,13 @@ __device__ inline void front_sync() {
     } else {
         __syncthreads();
     }
+}
+
+// elements of T before the rhs rows (of type C) of a packed update matrix of mu rows
+template <typename T, typename C>
+__device__ inline int rhs_at(int mu) {
+    const int e = cpk(mu, mu);
+    return sizeof(C) == sizeof(T) ? e : (e + 1) & ~1;
 }
 
 // masked store into a panel: FP64 under the lane mask; FP32 without a branch, masked
@@ -2076,9 +2089,9 @@ __device__ inline void schur_tiles(const PanelCtx& pl, int child_begin, int nch,
 // same sequence of barriers.  Every global load that needs no other is issued
 // first (rows, children's maps, original entries' sources, the first pass of the
 // children's panel entries): a front is about three memory round trips.
-template <int D, int NRHS, typename T, bool WAVE>
+template <int D, int NRHS, typename T, typename C, bool WAVE>
 __device__ inline void front_lds(const PanelCtx& pl, const FEHMM_GLB KeType<D, NRHS, T>* ke, const FEHMM_GLB double* rhs,
-                                 FEHMM_LDS int* flag, int s, FEHMM_LDS T* F, FEHMM_LDS T* ys, FEHMM_LDS int32_t* iv,
+                                 FEHMM_LDS int* flag, int s, FEHMM_LDS T* F, FEHMM_LDS C* ys, FEHMM_LDS int32_t* iv,
                                  FEHMM_LDS T* Ul, int gt, int GT, int gw, int nw) {
     constexpr int NEN = 1 << D;
     constexpr int per = 8 / (int)sizeof(T);
@@ -2112,16 +2125,21 @@ __device__ inline void front_lds(const PanelCtx& pl, const FEHMM_GLB KeType<D, N
         }
     for (int t = gt; t < lp; t += GT) F[t] = T(0);
     // rhs of the thread's row: its own entry and the children's
-    T b[NRHS], cr[2][NRHS];
+    C b[NRHS], cr[2][NRHS];
 #pragma unroll
-    for (int q = 0; q < NRHS; ++q) b[q] = i < p ? (T)rhs[ri * NRHS + q] : T(0);
+    for (int q = 0; q < NRHS; ++q) b[q] = i < p ? (C)rhs[ri * NRHS + q] : C(0);
+    // child rhs rows: column k of child row r of a child of mc rows at U
+    auto child_rhs = [&](const auto* U, int lds, int off, int mc, int r, int k) -> C {
+        const int at = rhs_at<T, C>(mc);
+        if (lds >= 0) return ((const FEHMM_LDS C*)(Ul + lds + at))[r + k * mc];
+        return ((const FEHMM_GLB C*)(U + off + at))[r + k * mc];
+    };
 #pragma unroll
     for (int q = 0; q < 2; ++q)
         if (q < nch) {
-            const int o = cpk(ch[q].mc, ch[q].mc) + (ivr[q] >= 0 ? (ivr[q] & 0xffff) : 0);
+            const int o = ivr[q] >= 0 ? (ivr[q] & 0xffff) : 0;
 #pragma unroll
-            for (int k = 0; k < NRHS; ++k)
-                cr[q][k] = cu[q].lds >= 0 ? Ul[cu[q].lds + o + k * ch[q].mc] : Ug[cu[q].off + o + k * ch[q].mc];
+            for (int k = 0; k < NRHS; ++k) cr[q][k] = child_rhs(Ug, cu[q].lds, cu[q].off, ch[q].mc, o, k);
             if (i < m) iv[q * m + i] = ivr[q];
         }
     front_sync<WAVE>();
@@ -2142,21 +2160,21 @@ __device__ inline void front_lds(const PanelCtx& pl, const FEHMM_GLB KeType<D, N
                 extend_add_packed(pl.ea_dst + ch[q].ea_off, Ug + cu[q].off, ch[q].npre, gt + 8 * GT, GT, F);
             }
 #pragma unroll
-            for (int k = 0; k < NRHS; ++k) b[k] += ivr[q] >= 0 ? cr[q][k] : T(0);
+            for (int k = 0; k < NRHS; ++k) b[k] += ivr[q] >= 0 ? cr[q][k] : C(0);
             front_sync<WAVE>();
         }
     for (int q = 2; q < nch; ++q) {
         const DevChild c2 = load_const(pl.childrec + fr.child_begin + q);
         const int v2 = (pl.inv + c2.inv_off)[ic];
-        const int o = cpk(c2.mc, c2.mc) + (v2 >= 0 ? (v2 & 0xffff) : 0);
+        const int o = v2 >= 0 ? (v2 & 0xffff) : 0;
         if (c2.u_lds >= 0)
             extend_add_packed(pl.ea_dst + c2.ea_off, (const FEHMM_LDS T*)Ul + c2.u_lds, c2.npre, gt, GT, F);
         else
             extend_add_packed(pl.ea_dst + c2.ea_off, Ug + (int)c2.U_off * per, c2.npre, gt, GT, F);
 #pragma unroll
         for (int k = 0; k < NRHS; ++k) {
-            const T v = c2.u_lds >= 0 ? Ul[c2.u_lds + o + k * c2.mc] : Ug[(int)c2.U_off * per + o + k * c2.mc];
-            b[k] += v2 >= 0 ? v : T(0);
+            const C v = child_rhs(Ug, c2.u_lds, (int)c2.U_off * per, c2.mc, o, k);
+            b[k] += v2 >= 0 ? v : C(0);
         }
         front_sync<WAVE>();
     }
@@ -2165,20 +2183,20 @@ __device__ inline void front_lds(const PanelCtx& pl, const FEHMM_GLB KeType<D, N
         for (int q = 0; q < NRHS; ++q) ys[q * 16 + i] = b[q];
     front_sync<WAVE>();
     PROF_MARK(PH_ASM);
-    T mypiv = T(1);
+    C mypiv = C(1);
     for (int K = 0; K < p; K += 16) {
         const int kb = min(16, p - K);
         const int par = (K >> 4) & 1;
         // waves that hold rows from K on
         const bool busy = WAVE || (64 * gw < m && 64 * gw + 63 >= K);
-        T blk[16], row[16], yb[NRHS];
+        C blk[16], row[16], yb[NRHS];
         if (busy) {
             const int rb = min(K + l15, m - 1);
 #pragma unroll
             for (int cc = 0; cc < 16; ++cc) {
                 const int col = min(K + cc, p - 1), base = cpk(col, m) - col;
-                blk[cc] = F[base + rb];
-                row[cc] = F[base + max(ic, K)];
+                blk[cc] = (C)F[base + rb];
+                row[cc] = (C)F[base + max(ic, K)];
             }
 #pragma unroll
             for (int q = 0; q < NRHS; ++q) yb[q] = ys[(par * NRHS + q) * 16 + l15];
@@ -2186,12 +2204,12 @@ __device__ inline void front_lds(const PanelCtx& pl, const FEHMM_GLB KeType<D, N
         // (the owners of the block rows overwrite what every wave reads here)
         front_sync<WAVE>();
         if (busy) {
-            T piv = T(1);
-            eliminate16<NRHS, T>(blk, row, yb, b, kb, i - K, piv);
+            C piv = C(1);
+            eliminate16<NRHS, C>(blk, row, yb, b, kb, i - K, piv);
             if (i >= K && i < K + kb) mypiv = piv;
             const int top = i < m ? i - K : -1;  // the row's last column in the block
 #pragma unroll
-            for (int cc = 0; cc < 16; ++cc) put(F, cc <= top && cc < kb, cpk(K + cc, m) + i - K - cc, row[cc]);
+            for (int cc = 0; cc < 16; ++cc) put(F, cc <= top && cc < kb, cpk(K + cc, m) + i - K - cc, (T)row[cc]);
             if (i >= K + 16 && i < K + 32)
 #pragma unroll
                 for (int q = 0; q < NRHS; ++q) ys[((par ^ 1) * NRHS + q) * 16 + i - K - 16] = b[q];
@@ -2238,14 +2256,16 @@ __device__ inline void front_lds(const PanelCtx& pl, const FEHMM_GLB KeType<D, N
         }
     }
     if (mu > 0) {
-        auto update_out = [&](auto dst) {
+        auto update_out = [&](auto dst, auto rdst) {
             if (i >= p && i < m)
 #pragma unroll
-                for (int q = 0; q < NRHS; ++q) dst[cpk(mu, mu) + q * mu + i - p] = b[q];
+                for (int q = 0; q < NRHS; ++q) rdst[q * mu + i - p] = b[q];
             schur_tiles<T>(pl, fr.child_begin, nch, F, Ul, iv, cu[0], cu[1], dst, m, p, gw, nw);
         };
-        if (WAVE && fr.u_lds >= 0) update_out(Ul + fr.u_lds);
-        else update_out((FEHMM_GLB T*)(pl.U + fr.U_off));
+        const int at = rhs_at<T, C>(mu);
+        FEHMM_GLB T* const Uo = (FEHMM_GLB T*)(pl.U + fr.U_off);
+        if (WAVE && fr.u_lds >= 0) update_out(Ul + fr.u_lds, (FEHMM_LDS C*)(Ul + fr.u_lds + at));
+        else update_out(Uo, (FEHMM_GLB C*)(Uo + at));
     }
     front_sync<WAVE>();
     PROF_MARK(PH_OUT);
@@ -2255,7 +2275,7 @@ struct Step {
     int32_t front[kStepFronts];
 };
 
-template <int D, int NRHS, typename T>
+template <int D, int NRHS, typename T, typename C>
 __device__ __noinline__ void factorize_lds(const RveCtx& c, Smem& sm, T* Fgen) {
     const PanelCtx pl = panel_ctx(c);
     const auto* ke = glb(ke_of<D, NRHS, T>(c));
@@ -2265,7 +2285,7 @@ __device__ __noinline__ void factorize_lds(const RveCtx& c, Smem& sm, T* Fgen) {
     FEHMM_LDS int32_t* iv = (FEHMM_LDS int32_t*)sm.red;  // inverse row maps of two children of every front in flight
     static_assert(sizeof(Smem::red) >= 2 * NT * sizeof(int32_t), "inverse row maps");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    constexpr int YS = 2 * NRHS * 16 + 2;  // (F[-1]: where masked stores go)
+    constexpr int YS = 2 * NRHS * 16 * (int)(sizeof(C) / sizeof(T)) + 2;  // (F[-1]: where masked stores go)
     // small subtrees, one per wave: a task is a contiguous range of fronts, the
     // update matrices inside it stay in the wave's LDS; tasks of a level are
     // independent
@@ -2278,7 +2298,8 @@ __device__ __noinline__ void factorize_lds(const RveCtx& c, Smem& sm, T* Fgen) {
         for (int k = load_const(pl.task_beg + h) + wave; k < k1; k += NWAVE) {
             const int s1 = load_const(pl.task + 2 * k + 1);
             for (int s = load_const(pl.task + 2 * k); s <= s1; ++s)
-                front_lds<D, NRHS, T, true>(pl, ke, rhs, flag, s, Fw + YS, Fw, iv + 128 * wave, Ul, tid & 63, 64, 0, 1);
+                front_lds<D, NRHS, T, C, true>(pl, ke, rhs, flag, s, Fw + YS, (FEHMM_LDS C*)Fw, iv + 128 * wave, Ul,
+                                               tid & 63, 64, 0, 1);
         }
         __syncthreads();
     }
@@ -2295,11 +2316,12 @@ __device__ __noinline__ void factorize_lds(const RveCtx& c, Smem& sm, T* Fgen) {
             const DevFront f = load_const(pl.fronts + e.front[j]);
             need = max(need, cpk(f.p, f.m));
         }
+        if constexpr (sizeof(C) != sizeof(T)) need = (need + 1) & ~1;
         FEHMM_LDS T* const base = F + g * (need + YS);
         for (int r = 0; r < nf / G; ++r) {
             const int s = load_const(pl.wg_steps + kStepFronts * st + r * G + g);
-            front_lds<D, NRHS, T, false>(pl, ke, rhs, flag, s, base + YS, base, iv + 2 * GT * g, (FEHMM_LDS T*)nullptr,
-                                         tid - g * GT, GT, wave - g * NW, NW);
+            front_lds<D, NRHS, T, C, false>(pl, ke, rhs, flag, s, base + YS, (FEHMM_LDS C*)base, iv + 2 * GT * g,
+                                            (FEHMM_LDS T*)nullptr, tid - g * GT, GT, wave - g * NW, NW);
         }
     }
 }
@@ -2890,7 +2912,14 @@ template <int D, int NRHS, typename T>
 __device__ inline void factorize(const RveCtx& c, Smem& sm, T* lds) {
     if constexpr (kLdsPlans && (D == 2 || NRHS <= D * D))
         if (c.plan->lds_ok) {
-            factorize_lds<D, NRHS, T>(c, sm, lds);
+            // (FP32 factors of these plans condense from a factorization in FP64, tan64:
+            // no d^2 columns in FP32)
+            if constexpr (D == 2 && NRHS != D * D && sizeof(T) == 4)
+                if (c.plan->wide_rhs) {
+                    factorize_lds<D, NRHS, T, double>(c, sm, lds);
+                    return;
+                }
+            factorize_lds<D, NRHS, T, T>(c, sm, lds);
             return;
         }
     factorize_glb<D, T>(c, sm, NRHS, lds);

@@ -44,6 +44,7 @@ struct DevPlan {
     const int32_t* task_beg;  // [ntask_lev + 1] tasks of each level
     int32_t ntask_lev;
     int32_t ul_base, ul_stride;  // LDS update matrices: first element of wave 0's, elements from wave to wave
+    int32_t wide_rhs;         // panels in LDS, FP32 factors: pivots and right-hand sides in FP64 all the same
     int32_t bc;               // micro boundary conditions: 0 periodic, 1 linear displacements
 };
 
