@@ -136,6 +136,16 @@ int rve_batch_create(const rve_mesh* meshes, int64_t B, rve_batch* out);
 int rve_batch_destroy(rve_batch b);
 int rve_batch_state_offsets(rve_batch b, int64_t* host_off /* [B+1] */);
 
+/* How rve_solve_batch runs b with factors of `precision` (host only, for tooling and
+ * tests): *nlaunch receives the number of launches (1; 2 where RVEs whose panels take
+ * more than half of a CU's LDS, 2D from 33 x 33 on, run before many others), info, if
+ * non-NULL, receives [nlaunch][4]: the RVEs a launch solves, those of them whose
+ * front panels live in LDS (the others' fronts: in global memory), its threads per
+ * workgroup (512 where every front of the batch is in global memory, in 2D up to 256
+ * RVEs; one mesh with panels in LDS, such as 3D up to 4^3, keeps 256 for all of it) and its LDS bytes
+ * per workgroup.  Errors: RVE_EINVAL. */
+int rve_batch_launches(rve_batch b, int32_t precision, int32_t* nlaunch, int64_t* info);
+
 #define RVE_PREC_FP64 0
 /* FP32: the Newton element tangents are stored in FP32 and factored in FP32 (MFMA
  * trailing updates); the Newton residual, its norm, the det F guard and the

@@ -40,6 +40,8 @@ namespace {
 // slots that follow stay 256-byte aligned)
 constexpr size_t kExtCounterBytes = 256;
 
+constexpr int kNumCu = 256;
+
 thread_local std::string g_err;
 
 int fail(int code, const std::string& msg) {
@@ -174,7 +176,7 @@ int plan_device(PlanEntry* e) {
                      (int32_t)P.wave_hbeg.size() - 1, (int32_t)P.wave_slice, e->d_wg_steps,
                      (int32_t)(P.wg_steps.size() / kStepFronts), e->d_task, e->d_task_beg,
                      std::max<int32_t>((int32_t)P.task_beg.size() - 1, 0), (int32_t)P.ul_base, (int32_t)P.ul_stride,
-                     P.wide_rhs ? 1 : 0, 0};
+                     P.wide_rhs ? 1 : 0, 0, 0};
     if (P.wave_hbeg.empty()) e->dev.nwave_h = 0;
     e->dev.bc = P.bc;
     // dynamic LDS of a plan whose panels live there: the wave phase's slices, the
@@ -213,14 +215,22 @@ struct rve_mesh_s {
     bool alive = true;
 };
 
-struct rve_batch_s {
-    int d = 0;
-    int64_t B = 0;
-    int nslots = 0;
+// RVEs of a batch that one launch solves: the queue entries first .. first + count - 1
+struct LaunchClass {
+    int64_t first = 0, count = 0;
+    int64_t panel_rves = 0;         // those whose panels live in LDS
     int64_t bs_slice = 0;           // FP64 scratch per wave of the backward substitution
     size_t dyn_bytes[2] = {0, 0};   // dynamic LDS with FP64 / FP32 factors
     bool tall = false;              // some plan's panels fit LDS where its packed fronts would not
     bool wide = false;              // every plan keeps its fronts in global memory: eight-wave workgroups
+};
+
+struct rve_batch_s {
+    int d = 0;
+    int64_t B = 0;
+    int nslots = 0;
+    LaunchClass all;                // every RVE in one launch
+    std::vector<LaunchClass> cls;   // or the launches to split it into, in this order
     SlotLayout lay{};
     std::vector<int64_t> state_off;
     // device
@@ -441,9 +451,6 @@ int rve_batch_create(const rve_mesh* meshes, int64_t B, rve_batch* out) {
         b->state_off[r + 1] = b->state_off[r] + (int64_t)d * m->plan->host.nnode;
         cost[r] = m->plan->host.factor_flops;
     }
-    std::vector<int32_t> order(B);
-    for (int64_t r = 0; r < B; ++r) order[r] = (int32_t)r;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return cost[x] > cost[y]; });
     // workspace layout: max over the distinct plans
     int64_t nn = 0, ne = 0, Lsz = 0, Ust = 0, Usc = 0;
     const int nen = 1 << d, nd = nen * d, d2 = d * d;
@@ -456,26 +463,82 @@ int rve_batch_create(const rve_mesh* meshes, int64_t B, rve_batch* out) {
         Ust = std::max(Ust, p->host.U_stack);
         Usc = std::max(Usc, p->host.U_scratch);
     }
-    for (PlanEntry* p : plans) {
-        if (p->dev.lds_ok) {
-            for (int k = 0; k < 2; ++k) b->dyn_bytes[k] = std::max<size_t>(b->dyn_bytes[k], (size_t)p->lds_need[k]);
-            b->bs_slice = std::max(b->bs_slice, p->host.bs_slice);
-            b->tall = b->tall || !p->host.lds_path;
+    // Launches.  A launch's workgroups all get the dynamic LDS of its most demanding
+    // plan, and one that leaves room for a single workgroup per CU (2D panels from
+    // 33 x 33 on) halves the waves of every other RVE in the launch.  A launch of their
+    // own for the RVEs of such plans, before the others', leaves CUs idle while they
+    // run, as much as they fall short of one on every CU, and is worth it where the
+    // others are 2.4 times that work (flops of one factorization each): 14288 RVEs of
+    // 16 x 16 with one of 40 x 40 (ratio 3.0) take 56.2 ms in one launch and 43.9 in two,
+    // 2048 of 32 x 32 with one (3.6) 35.9 and 33.8; 1024 of 32 x 32 with 64 (2.4) 21.6
+    // and 22.5, 3000 of 24 x 24 with one of 43 x 43 (2.0) 30.0 and 30.4, 3000 of 16 x 16
+    // with one of 40 x 40 (0.6) 12.3 and 16.7; with 256 of 40 x 40 none idles (1024 of
+    // 32 x 32: 27.8 and 22.7).  And where more of the others than CUs have fronts in global
+    // memory, which are as fast two to a CU as alone: 512 of 48 x 48 with 8 of 40 x 40
+    // 169 and 122 ms.
+    auto alone = [](const PlanEntry* p) {
+        return p->dev.lds_ok && p->lds_need[0] + w4::lds_static_bytes() > kLdsBytesMax / 2;
+    };
+    double large = 0, large_max = 0, others = 0;
+    int64_t others_global = 0;
+    for (int64_t r = 0; r < B; ++r) {
+        const PlanEntry* p = meshes[r]->plan;
+        if (alone(p)) {
+            large += cost[r];
+            large_max = std::max(large_max, cost[r]);
         } else {
-            // global fronts: staged tile slabs, FP64-sized in both kernels (the
-            // condensation factorization of global-front plans is FP64)
-            for (int k = 0; k < 2; ++k)
-                b->dyn_bytes[k] = std::max<size_t>(b->dyn_bytes[k], (size_t)kTileLdsElems * 8);
+            others += cost[r];
+            others_global += p->dev.lds_ok ? 0 : 1;
         }
     }
-    // eight waves: 3D batches of global fronts (512 RVEs of 8^3 / 12^3 / 16^3 2.33 s
-    // with four waves, 1.45 with eight), and 2D ones while every RVE has a CU of its
-    // own (8 of 60 x 60: 127 and 108 ms); a full chip of their small fronts (at most
-    // 378 rows) is better off with two four-wave workgroups per CU (512 of 40 x 40:
-    // 84 and 100 ms)
-    b->wide = (d == 3 || B <= 256) && std::none_of(plans.begin(), plans.end(), [](const PlanEntry* p) { return p->dev.lds_ok != 0; });
-    // (the backward substitution's slices are the largest of the batch's plans)
-    for (int k = 0; k < 2; ++k) b->dyn_bytes[k] = std::max<size_t>(b->dyn_bytes[k], (size_t)(8 * kSolveWaves * b->bs_slice));
+    const bool split =
+        large > 0 && others > 0 && (others > 2.4 * (kNumCu * large_max - large) || others_global > kNumCu);
+    std::vector<int32_t> plan_cls(plans.size(), 0);
+    for (size_t q = 0; q < plans.size(); ++q) plan_cls[q] = split && !alone(plans[q]) ? 1 : 0;
+    std::vector<int32_t> order(B);
+    for (int64_t r = 0; r < B; ++r) order[r] = (int32_t)r;
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+        const int32_t cx = plan_cls[rve_plan[x]], cy = plan_cls[rve_plan[y]];
+        return cx != cy ? cx < cy : cost[x] > cost[y];
+    });
+    auto launch_of = [&](int only) {  // of the RVEs of one class, or (-1) of all
+        LaunchClass c;
+        for (int64_t r = 0; r < B; ++r) {
+            if (only >= 0 && plan_cls[rve_plan[r]] != only) {
+                c.first += plan_cls[rve_plan[r]] < only ? 1 : 0;
+                continue;
+            }
+            c.count++;
+            c.panel_rves += meshes[r]->plan->dev.lds_ok ? 1 : 0;
+        }
+        for (size_t q = 0; q < plans.size(); ++q) {
+            const PlanEntry* p = plans[q];
+            if (only >= 0 && plan_cls[q] != only) continue;
+            if (p->dev.lds_ok) {
+                for (int k = 0; k < 2; ++k) c.dyn_bytes[k] = std::max<size_t>(c.dyn_bytes[k], (size_t)p->lds_need[k]);
+                c.bs_slice = std::max(c.bs_slice, p->host.bs_slice);
+                c.tall = c.tall || !p->host.lds_path;
+            } else {
+                // global fronts: staged tile slabs, FP64-sized in both kernels (the
+                // condensation factorization of global-front plans is FP64)
+                for (int k = 0; k < 2; ++k)
+                    c.dyn_bytes[k] = std::max<size_t>(c.dyn_bytes[k], (size_t)kTileLdsElems * 8);
+            }
+        }
+        // eight waves: 3D batches of global fronts (512 RVEs of 8^3 / 12^3 / 16^3 2.33 s
+        // with four waves, 1.45 with eight), and 2D ones while every RVE has a CU of its
+        // own (8 of 60 x 60: 127 and 108 ms); a full chip of their small fronts (at most
+        // 378 rows) is better off with two four-wave workgroups per CU (512 of 40 x 40:
+        // 84 and 100 ms)
+        // (parts of a batch run as the whole would: results do not depend on the split)
+        c.wide = only < 0 && (d == 3 || c.count <= kNumCu) && c.panel_rves == 0;
+        // (the backward substitution's slices are the largest of the launch's plans)
+        for (int k = 0; k < 2; ++k)
+            c.dyn_bytes[k] = std::max<size_t>(c.dyn_bytes[k], (size_t)(8 * kSolveWaves * c.bs_slice));
+        return c;
+    };
+    b->all = launch_of(-1);
+    if (split) b->cls = {launch_of(0), launch_of(1)};
     auto rnd = [](int64_t x) { return (x + 31) / 32 * 32; };
     SlotLayout& L = b->lay;
     int64_t o = 0;
@@ -502,7 +565,10 @@ int rve_batch_create(const rve_mesh* meshes, int64_t B, rve_batch* out) {
     if (nslots < 1) return fail(RVE_ENOMEM, "rve_batch_create: not enough device memory for one workspace slot");
     b->nslots = (int)nslots;
     std::vector<DevPlan> dplans;
-    for (PlanEntry* p : plans) dplans.push_back(p->dev);
+    for (size_t q = 0; q < plans.size(); ++q) {
+        dplans.push_back(plans[q]->dev);
+        dplans.back().cls = plan_cls[q];
+    }
     int st;
     if ((st = upload(dplans, &b->d_plans)) || (st = upload(rve_plan, &b->d_rve_plan)) ||
         (st = upload(rve_phase, &b->d_rve_phase)) || (st = upload(phase_pool, &b->d_phase_pool)) ||
@@ -533,6 +599,40 @@ int rve_batch_destroy(rve_batch b) {
 int rve_batch_state_offsets(rve_batch b, int64_t* host_off) {
     if (!b || !b->alive || !host_off) return fail(RVE_EINVAL, "rve_batch_state_offsets: invalid argument");
     std::memcpy(host_off, b->state_off.data(), sizeof(int64_t) * (b->B + 1));
+    return RVE_OK;
+}
+
+// dynamic LDS of a launch; FP32 factors: 1 where FP64 panels keep two workgroups per CU
+// (the register limit), so that the condensation factorization runs in FP64 and the
+// direct Schur form replaces the refined FP32 solves (always where a packed FP64 front
+// would not fit LDS)
+static int class_lds(const LaunchClass& c, bool fp32, size_t* dyn) {
+    *dyn = c.dyn_bytes[fp32 ? 1 : 0];
+    if (!fp32 || !(c.tall || (int64_t)c.dyn_bytes[0] + w4::lds_static_bytes() <= kLdsBytesMax / 2)) return 0;
+    *dyn = std::max(*dyn, c.dyn_bytes[0]);
+    return 1;
+}
+
+// launches of a batch over nslots workgroups (with no more of them than CUs none shares
+// its CU: one launch)
+static int num_launches(const rve_batch_s* b, int nslots) {
+    return nslots > kNumCu && !b->cls.empty() ? (int)b->cls.size() : 1;
+}
+
+int rve_batch_launches(rve_batch b, int32_t precision, int32_t* nlaunch, int64_t* info) {
+    if (!b || !b->alive || !nlaunch) return fail(RVE_EINVAL, "rve_batch_launches: invalid argument");
+    if (precision != RVE_PREC_FP64 && precision != RVE_PREC_FP32_IR)
+        return fail(RVE_EINVAL, "rve_batch_launches: unknown precision");
+    *nlaunch = num_launches(b, b->nslots);
+    for (int q = 0; info && q < *nlaunch; ++q) {
+        const LaunchClass& c = *nlaunch > 1 ? b->cls[q] : b->all;
+        size_t dyn = 0;
+        (void)class_lds(c, precision == RVE_PREC_FP32_IR, &dyn);
+        info[4 * q] = c.count;
+        info[4 * q + 1] = c.panel_rves;
+        info[4 * q + 2] = c.wide ? 512 : 256;
+        info[4 * q + 3] = (int64_t)dyn + w4::lds_static_bytes();
+    }
     return RVE_OK;
 }
 
@@ -580,8 +680,6 @@ static int solve_batch_impl(rve_batch b, const int32_t* subset, const int32_t* s
     a.lame_pool = b->d_lame_pool;
     a.state_off = b->d_state_off;
     a.rve_atol = b->d_atol;
-    a.order = subset ? subset : b->d_order;
-    a.count_dev = subset ? subset_count : nullptr;
     a.skip = skip;
     a.B = b->B;
     a.ws = ws;
@@ -600,19 +698,6 @@ static int solve_batch_impl(rve_batch b, const int32_t* subset, const int32_t* s
     a.want_A = A != nullptr;
     a.dim = b->d;
     a.flags = o.flags;
-    const int k = fp32 ? 1 : 0;
-    a.bs_slice = (int32_t)b->bs_slice;
-    size_t dyn = b->dyn_bytes[k];
-    a.lds_elems = (int32_t)(dyn / (fp32 ? 4 : 8));
-    // FP32 factors: where FP64 panels keep two workgroups per CU (the register
-    // limit), the condensation factorization runs in FP64 and the direct Schur
-    // form replaces the refined FP32 solves
-    a.tan64 = 0;
-    // (always where a packed FP64 front would not fit LDS)
-    if (fp32 && (b->tall || (int64_t)b->dyn_bytes[0] + w4::lds_static_bytes() <= kLdsBytesMax / 2)) {
-        a.tan64 = 1;
-        dyn = std::max(dyn, b->dyn_bytes[0]);
-    }
     // FP32 factors: a Newton step is refined only when ||b - K64 x|| > 1e-2 ||b||
     // (inexact Newton; convergence is judged on the FP64 residual); the tangent
     // takes the second-order (stationary) form straight from the FP32 solve: its
@@ -623,9 +708,23 @@ static int solve_batch_impl(rve_batch b, const int32_t* subset, const int32_t* s
     a.reuse_tan = (A != nullptr && !(o.flags & RVE_FLAG_DIRECT_TANGENT)) ? 1 : 0;
     a.ir_eta = 1e-2;
     a.ir_eta_tan = 0.0;
-    hipError_t e = b->wide ? w8::launch_rve_solve(a, nslots, dyn, fp32, (hipStream_t)hip_stream)
-                           : w4::launch_rve_solve(a, nslots, dyn, fp32, (hipStream_t)hip_stream);
-    if (e != hipSuccess) return fail(RVE_EHIP, std::string("rve_solve_batch launch: ") + hipGetErrorString(e));
+    const int nlaunch = num_launches(b, nslots);
+    for (int q = 0; q < nlaunch; ++q) {
+        const LaunchClass& c = nlaunch > 1 ? b->cls[q] : b->all;
+        // a subset list is in the caller's order: each launch takes its class's RVEs from it
+        a.order = subset ? subset : b->d_order + c.first;
+        a.nq = subset ? b->B : c.count;
+        a.count_dev = subset ? subset_count : nullptr;
+        a.cls = subset && nlaunch > 1 ? q : -1;
+        a.bs_slice = (int32_t)c.bs_slice;
+        size_t dyn = 0;
+        a.tan64 = class_lds(c, fp32, &dyn);
+        a.lds_elems = (int32_t)(c.dyn_bytes[fp32 ? 1 : 0] / (fp32 ? 4 : 8));
+        const int ns = (int)std::min<int64_t>(nslots, c.count);
+        hipError_t e = c.wide ? w8::launch_rve_solve(a, ns, dyn, fp32, (hipStream_t)hip_stream)
+                              : w4::launch_rve_solve(a, ns, dyn, fp32, (hipStream_t)hip_stream);
+        if (e != hipSuccess) return fail(RVE_EHIP, std::string("rve_solve_batch launch: ") + hipGetErrorString(e));
+    }
     return RVE_OK;
 }
 
@@ -657,6 +756,8 @@ int rve_assemble_batch(rve_batch b, const double* F, const double* w_state, int3
     a.rve_atol = b->d_atol;
     a.order = b->d_order;
     a.B = b->B;
+    a.nq = b->B;
+    a.cls = -1;
     a.ws = b->d_ws;
     a.lay = b->lay;
     a.counter = b->d_counter;

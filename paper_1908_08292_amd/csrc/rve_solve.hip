@@ -2954,17 +2954,16 @@ __global__ __launch_bounds__(NT, 2) void rve_solve_kernel(SolveArgs a) {
     double* base = a.ws + slot * a.lay.stride;
     for (;;) {
         if (threadIdx.x == 0) {
-            // queue length: the whole batch, or a device-side count of a subset
-            // list (entries outside [0, B) are skipped)
-            const unsigned int nq =
-                a.count_dev ? (unsigned int)min((int64_t)max(*a.count_dev, 0), a.B) : (unsigned int)a.B;
+            // queue length: the launch's share of the batch, or a device-side count of
+            // a subset list (entries outside [0, B) or of another launch are skipped)
+            const unsigned int nq = (unsigned int)(a.count_dev ? min((int64_t)max(*a.count_dev, 0), a.B) : a.nq);
             int r = -1;
             for (;;) {
                 if (a.skip && *a.skip) break;
                 const unsigned int idx = atomicAdd(a.counter, 1u);
                 if (idx >= nq) break;
                 const int cand = a.order[idx];
-                if (cand >= 0 && (int64_t)cand < a.B) {
+                if (cand >= 0 && (int64_t)cand < a.B && (a.cls < 0 || a.plans[a.rve_plan[cand]].cls == a.cls)) {
                     r = cand;
                     break;
                 }

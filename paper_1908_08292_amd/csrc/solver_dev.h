@@ -45,6 +45,7 @@ struct DevPlan {
     int32_t ntask_lev;
     int32_t ul_base, ul_stride;  // LDS update matrices: first element of wave 0's, elements from wave to wave
     int32_t wide_rhs;         // panels in LDS, FP32 factors: pivots and right-hand sides in FP64 all the same
+    int32_t cls;              // launch of the batch that solves the plan's RVEs (set per batch)
     int32_t bc;               // micro boundary conditions: 0 periodic, 1 linear displacements
 };
 
@@ -67,6 +68,8 @@ struct SolveArgs {
     const int32_t* count_dev;    // length of a subset list (device), or null for the whole batch
     const int* skip;             // device flag: when set, the launch solves nothing (graph-captured steps)
     int64_t B;
+    int64_t nq;                  // queue entries (without a subset list)
+    int32_t cls;                 // >= 0: only the RVEs of plans with this cls
     double* ws;
     SlotLayout lay;
     unsigned int* counter;

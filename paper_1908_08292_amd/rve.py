@@ -79,6 +79,7 @@ def lib():
         L.rve_plan_info.argtypes = [i32, i32, C.POINTER(dp), C.POINTER(i64), C.POINTER(i32), C.POINTER(i32)]
         L.rve_plan_export.argtypes = [i32, i32, vp, vp, vp, vp, vp, vp, vp]
         L.rve_plan_schedule.argtypes = [i32, i32, vp, vp, vp]
+        L.rve_batch_launches.argtypes = [vp, i32, vp, vp]
         L.rve_strerror.argtypes = [C.c_int]
         L.rve_strerror.restype = C.c_char_p
         L.rve_last_error.argtypes = [C.c_char_p, C.c_size_t]
@@ -256,6 +257,15 @@ class Batch:
         off = np.zeros(self.B + 1, np.int64)
         check(lib().rve_batch_state_offsets(self.h, _ptr(off)), "rve_batch_state_offsets")
         self.state_offsets = off
+
+    def launches(self, precision=PREC_FP64):
+        """rve_batch_launches: one row per launch, (RVEs, of these with panels in LDS,
+        threads per workgroup, LDS bytes per workgroup)."""
+        n = C.c_int32()
+        check(lib().rve_batch_launches(self.h, int(precision), C.byref(n), None), "rve_batch_launches")
+        out = np.zeros((n.value, 4), np.int64)
+        check(lib().rve_batch_launches(self.h, int(precision), C.byref(n), _ptr(out)), "rve_batch_launches")
+        return out
 
     def _check(self, t, numel, dtype, name):
         import torch
