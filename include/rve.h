@@ -258,8 +258,8 @@ typedef struct {
     int32_t leaf;        /* 0: default (16 nodes in 2D, 27 in 3D) */
     int32_t wave_max_m;  /* 0 .. 64; 64 is the default */
     int32_t slots;       /* 0: default (min(B, 1024)) */
-    int32_t threads;     /* 0, 256 or 512: accepted; the library picks the workgroup size itself (four
-                            waves for plans with panels in LDS, eight for batches of global fronts) */
+    int32_t threads;     /* 0, 256 or 512: accepted, without effect: the library picks the workgroup size
+                            itself (rve_batch_launches).  rve_autotune returns that of the tuning batch. */
     double ms;           /* measured time of the tuning batch (rve_autotune), else 0 */
 } rve_tuning;
 

@@ -929,7 +929,7 @@ int rve_autotune(rve_mesh m, const double* F, int64_t nF, const rve_opts* o, rve
             if (!lds && wave != kWaveFrontMaxM) continue;
             for (size_t c = 0; c < slots.size() && !err; ++c) {
                 const int sl = slots[c];
-                rve_tuning cand{leaf, wave, sl, kSolveWaves * 64, 0.0};
+                rve_tuning cand{leaf, wave, sl, 0, 0.0};
                 if ((err = rve_tuning_set(d, n, &cand))) break;
                 rve_mesh_desc md{};
                 md.ndim = d;
@@ -958,10 +958,11 @@ int rve_autotune(rve_mesh m, const double* F, int64_t nF, const rve_opts* o, rve
                     (void)hipEventElapsedTime(&t, e0, e1);
                     if (rep == 1) ms_best = t;
                 }
+                const int threads = cb->all.wide ? 512 : 256;
                 rve_batch_destroy(cb);
                 rve_mesh_destroy(cm);
                 if (err) break;
-                if (ms_best < win.ms) win = rve_tuning{leaf, wave, sl, kSolveWaves * 64, (double)ms_best};
+                if (ms_best < win.ms) win = rve_tuning{leaf, wave, sl, threads, (double)ms_best};
             }
             if (err) break;
         }

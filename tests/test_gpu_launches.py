@@ -105,3 +105,20 @@ def test_split_batch_gives_what_its_parts_give(prec):
         assert torch.equal(got.view(-1, w)[hit], want.view(-1, w)[hit])
         assert bool((got.view(-1, w)[~hit] == rest).all())
     _done(batch, meshes)
+
+
+@pytest.mark.parametrize("d,n,threads", [(2, 6, 256), (2, 44, 512), (3, 4, 256), (3, 5, 512)])
+def test_autotune_returns_the_workgroup_size_that_ran(d, n, threads):
+    import torch
+    F = workloads.draw_F(np.random.default_rng(9), 4, d, 0.05)
+    mesh = rve.Mesh(d, n, rve.two_phase_lame(8.0), radius=0.27)
+    print(f"case autotune {d}d n={n}", flush=True)
+    try:
+        t = rve.autotune(mesh, torch.tensor(F.reshape(-1), device="cuda"))
+        assert t["threads"] == threads
+        batch = rve.Batch([mesh] * 4)
+        assert batch.launches()[:, 2].tolist() == [threads]
+        batch.destroy()
+    finally:
+        rve.tuning_reset(d, n)
+        mesh.destroy()
