@@ -293,14 +293,14 @@ int rve_plan_info(int32_t ndim, int32_t n, double* factor_flops, int64_t* nnz_L,
 int rve_plan_export(int32_t ndim, int32_t n, int64_t* sizes, int32_t* fronts, int32_t* rows, int32_t* relind,
                     int32_t* children, int32_t* kpair, int32_t* kcontrib);
 
-/* Processing schedule of the (ndim, n) plan's LDS path, for tooling and tests
- * (host only).  *nsteps receives the number of workgroup-front steps (0 when
- * whole packed fronts exceed LDS, i.e. 2D from 36 x 36 on under periodic coupling,
- * though up to 43 x 43 the solver still holds the fronts' panels there); steps, if non-NULL, receives [nsteps][4]
- * in processing order: the 1, 2 or 4 fronts processed side by side on equal
- * parts of the workgroup, -1 padded; wave, if non-NULL, receives one flag per
- * front (elimination order): 1 for the fronts eliminated one per wave before
- * the workgroup fronts. */
+/* Processing schedule of the (ndim, n) plan under periodic coupling, for tooling and
+ * tests (host only).  *nsteps receives the number of workgroup-front steps; 0 where
+ * whole packed fronts exceed LDS, 2D from 33 x 33 and 3D from 5^3 on (2D up to 43 x 43
+ * the solver still runs such steps, of the fronts' panels: rve_batch_launches tells
+ * where the panels live).  steps, if non-NULL, receives [nsteps][4] in processing
+ * order: the 1, 2 or 4 fronts processed side by side on equal parts of the workgroup,
+ * -1 padded; wave, if non-NULL, receives one flag per front (elimination order): 1 for
+ * the fronts eliminated one per wave before the workgroup fronts. */
 int rve_plan_schedule(int32_t ndim, int32_t n, int64_t* nsteps, int32_t* steps, int32_t* wave);
 
 /* ---- the assembly phase alone ------------------------------------------------

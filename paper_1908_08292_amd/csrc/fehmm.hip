@@ -544,11 +544,12 @@ __global__ __launch_bounds__(kBandNT) void macro_band_solve_blocked(double* __re
 // The kernel is compiled for each number of tile rows: the tiles and the loops over
 // them are constants, and nothing is done for tiles that the band does not have.
 // What bounds it is the chain of dependent panels: the diagonal tile's sixteen pivots,
-// then one tile of L and one trailing tile, about 2.9 us in all.  At 4312 unknowns and
-// bandwidth 101 (270 panels) the factorization took 1378 us with four waves, ten tile
-// rows for every band and the stores within the panel, 917 us without these, and with
-// the forward substitution within it 1078 us, of which eight waves leave 787 us; the
-// two substitutions took 553 us, the backward one takes 231.
+// then one tile of L and one trailing tile, about 3.9 us in all.  At 4312 unknowns and
+// bandwidth 101 (270 panels) the factorization took 1835 us with four waves, ten tile
+// rows for every band and the stores within the panel, 1222 us without these, and with
+// the forward substitution within it 1436 us, of which eight waves leave 1150 us and
+// win_owns 1047; the two substitutions took 736 us, the backward one takes 307.
+// (Launches that do work: those after convergence return in 5 us.)
 constexpr int kWinMax = 10;                                  // tile rows of the window (bw <= 144)
 constexpr int kWinSlots = kWinMax * (kWinMax + 1) / 2;       // window tiles
 constexpr int kWinWaves = 8;
@@ -726,10 +727,12 @@ __device__ __forceinline__ void win_panel(double* Wn, double* LDp, const double*
 // tile, which it factors right after), the other waves the rest in turn.  Every
 // operand is read first, then the MFMAs run, then the tiles are stored.
 // Wave 4 shares its SIMD with wave 0, whose pivots wait for its MFMAs.  Up to eight
-// tile rows, where the pivots are what a panel takes, it has no trailing tile (4312
-// unknowns, bandwidth 101: 854 -> 787 us); from nine on the tiles weigh as much and
-// it takes its share (5800 unknowns, bandwidth 117: 1253 us with, 1281 without; 7504 at
-// 133: 1670 and 1754).
+// tile rows, where the pivots are what a panel takes, it has no trailing tile (plates of
+// 48 to 60 elements in length, factorizations with its share and without: two and three
+// tile rows equal, four 563 and 550 us, five 821 and 768, six 1108 and 1032, seven 1419 and
+// 1307, eight 1476 and 1350); from nine on the tiles weigh as much and it takes its
+// share (nine, 5800 unknowns and bandwidth 117: 1669 us with, 1707 without; ten, 7504 at
+// 133: 2225 and 2337).
 template <int NTW>
 __device__ constexpr bool win_owns(int W, int t) {
     if (NTW > 8) return W == (t == 0 ? 0 : (t - 1) % (kWinWaves - 1) + 1);

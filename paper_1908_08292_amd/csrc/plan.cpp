@@ -457,7 +457,10 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
         // keeps all of them, shared by the waves, where they fit.  Otherwise every
         // maximal subtree whose panels and inner update matrices fit a quarter of
         // the budget becomes one task of one wave (three fronts of two leaves and
-        // their separator from 16 x 16 on), as long as that leaves a task per wave.
+        // their separator), as long as that leaves a task per wave.  The budget is
+        // what the largest wave panel of the plan leaves: with the default leaf under
+        // periodic coupling that is enough at 16 x 16 and 32 x 32 and at no other size
+        // from 9 x 9 to 43 x 43.
         auto u_elems = [&](const FrontHost& X) {
             const int64_t mu = X.m - X.p;
             return (mu * (mu + 1) / 2 + rw - 1) / rw * rw + mu * rhs_cols * rw;
@@ -533,13 +536,12 @@ PlanHost build_plan(int d, int n, const PlanParams& prm) {
         // workgroup fronts by height (children first).  Fronts of one height are
         // independent; with equal p and child counts they pass the same barriers,
         // so up to kStepFronts of them can share a step (each on a group of at
-        // least 128 threads, one per front row: m <= 128) when together they fit
-        // the front region: the packed fronts with their rhs rows and diagonals,
-        // and in the backward substitution the staged panels with their FP64
-        // scratch (d^2 m + 3 p doubles, i.e. twice as many FP32 elements).
-        // (rhs rows: d^2 + 1 columns in 2D, where the last Newton factorization
-        // and its backward substitution carry the condensation's columns beside
-        // the residual; then the original diagonal)
+        // least 128 threads, one per front row: m <= 128).  What the kernel needs is
+        // kStepGroups panels with their block rows (wg_elems) and the backward
+        // substitution's scratch (bs_slice), both sized below from the steps.  The
+        // groups are formed by a stricter bound, that the packed fronts with their
+        // right-hand sides, and their panels with FP64 scratch, fit beside each other
+        // where the plan's largest packed front would.
         const int64_t rr = d * d + (d == 2 ? 2 : 1);
         const int64_t mm = P.max_m, region = mm * (mm + 1) / 2 + mm * rr;
         auto fneed = [&](const FrontHost& X) { return (int64_t)X.m * (X.m + 1) / 2 + (int64_t)X.m * rr; };

@@ -111,7 +111,7 @@ int upload(const std::vector<T>& v, T** out) {
 
 void free_plan_dev(PlanEntry& e) {
     (void)hipFree(e.d_fronts); (void)hipFree(e.d_rows); (void)hipFree(e.d_relind);
-    (void)hipFree(e.d_children); 
+    (void)hipFree(e.d_children);
     (void)hipFree(e.d_asm_dst); (void)hipFree(e.d_inv); (void)hipFree(e.d_childrec); (void)hipFree(e.d_task); (void)hipFree(e.d_task_beg);
     (void)hipFree(e.d_asm_src); (void)hipFree(e.d_ea_dst);
     (void)hipFree(e.d_back); (void)hipFree(e.d_wave_hbeg); (void)hipFree(e.d_wg_steps);
@@ -171,7 +171,7 @@ int plan_device(PlanEntry* e) {
         return st;
     }
     e->dev = DevPlan{P.d, P.n, P.nnode, P.nelem, (int32_t)P.fronts.size(), 0,
-                     e->d_fronts, e->d_rows, e->d_relind, e->d_children, 
+                     e->d_fronts, e->d_rows, e->d_relind, e->d_children,
                      e->d_asm_dst, e->d_asm_src, e->d_ea_dst, e->d_inv, e->d_childrec, e->d_back, e->d_wave_hbeg,
                      (int32_t)P.wave_hbeg.size() - 1, (int32_t)P.wave_slice, e->d_wg_steps,
                      (int32_t)(P.wg_steps.size() / kStepFronts), e->d_task, e->d_task_beg,
@@ -527,9 +527,9 @@ int rve_batch_create(const rve_mesh* meshes, int64_t B, rve_batch* out) {
         }
         // eight waves: 3D batches of global fronts (512 RVEs of 8^3 / 12^3 / 16^3 2.33 s
         // with four waves, 1.45 with eight), and 2D ones while every RVE has a CU of its
-        // own (8 of 60 x 60: 127 and 108 ms); a full chip of their small fronts (at most
-        // 378 rows) is better off with two four-wave workgroups per CU (512 of 40 x 40:
-        // 84 and 100 ms)
+        // own (256 of 48 x 48: 96.1 ms with four, 87.8 with eight; 8 of 60 x 60 119.0 and
+        // 111.7); more of their small fronts (at most 378 rows) are better off with two
+        // four-wave workgroups per CU (300 of 48 x 48: 106 and 134 ms, 512: 114 and 152)
         // (parts of a batch run as the whole would: results do not depend on the split)
         c.wide = only < 0 && (d == 3 || c.count <= kNumCu) && c.panel_rves == 0;
         // (the backward substitution's slices are the largest of the launch's plans)
@@ -914,7 +914,7 @@ int rve_autotune(rve_mesh m, const double* F, int64_t nF, const rve_opts* o, rve
     rve_tuning win{0, kWaveFrontMaxM, 0, 0, 1e300};
     int err = RVE_OK;
     for (int leaf : leaves) {
-        // the wave limit matters only where whole fronts fit LDS
+        // the wave limit matters only where panels live in LDS
         bool lds = false;
         try {
             PlanParams pp;

@@ -1,7 +1,8 @@
 // rve_solve.hip -- persistent batched periodic-RVE solver for gfx950.
 //
-// One workgroup (256 threads, four wave64) owns one workspace slot and pulls RVE
-// ids from a device queue until the batch is exhausted.  Per RVE it runs the
+// One workgroup (four wave64; eight in the second compilation, for batches that keep
+// every front in global memory) owns one workspace slot and pulls RVE ids from a
+// device queue until the batch is exhausted.  Per RVE it runs the
 // micro Newton iteration of Sec. 3.3 (residual, tangent, linear solve, update;
 // the PBC form in which G^T dLambda = 0), then the post-convergence outputs:
 // Pbar = <P> (eq. Average-of-P-and-F) and the tangent transfer of Sec. 3.2 for
@@ -19,8 +20,8 @@
 //     Y_(a,i),(kL)  = sum_gp (mu d_ik dN_a,L + c1 g_a,k Fi_Li + c2 g_a,i Fi_Lk) w|J|
 // which equal int B^T S and int B^T C B + S_hat 1 of the paper's eqs. (DG^h,
 // G_IK, S_IK) written with P and A = dP/dF.  The two other laws of the paper's
-// micro-convergence comparisons (Sec. 6) take a generic path with P and A
-// evaluated at the Gauss point (law_PA): St. Venant-Kirchhoff, P = F S with
+// micro-convergence comparisons (Sec. 6) share one closed form of A with it
+// (PointState): St. Venant-Kirchhoff, P = F S with
 // S = lambda tr(E) 1 + 2 mu E, A_iJkL = d_ik S_JL + lambda F_iJ F_kL +
 // mu (F_iL F_kJ + (F F^T)_ik d_JL); and the fully linear case, P = sigma(eps),
 // eps = sym(F - 1), A the constant elasticity tensor.
@@ -84,10 +85,9 @@ struct Smem {
     double dN[8 * 8 * 3];    // [gp][a][k]
     double Fbar[9];
     double outv[96];
-    double wJ, r0, rnorm, atol, alpha;
+    double wJ, atol;
     int flag;
     int rve;
-    int stop;
 };
 
 __device__ inline double wave_sum(double v) {
@@ -861,11 +861,10 @@ __device__ inline const KeType<D, NRHS, T>* ke_of(const RveCtx& c) {
     return reinterpret_cast<const KeType<D, NRHS, T>*>(c.ke);
 }
 
-// ---------------------------------------------------------------- LDS fronts
-// A front that fits in LDS is held there whole as a packed lower triangle,
-// column-major: entry (i, j), i >= j, at cpk(j, m) + i - j.  The first p columns
-// are the L panel and the trailing columns are exactly the packed update matrix,
-// so both leave the front with one contiguous copy each.
+// ---------------------------------------------------------------- packed fronts
+// A front's lower triangle is packed column-major: entry (i, j), i >= j, at
+// cpk(j, m) + i - j.  The first p columns are the L panel, the only part that LDS
+// holds; the trailing columns are exactly the packed update matrix.
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
@@ -3111,8 +3110,8 @@ __global__ __launch_bounds__(NT, 2) void rve_solve_kernel(SolveArgs a) {
             // (still in the rhs buffer, columns 1..d^2): used where the last
             // factorized residual was within 1e-4 of the initial one, so the
             // stationary form's error (second order in that step) stays far
-            // below the tangent's tolerance; in 2D the element pass adds it to
-            // the average tangent itself (mode 4)
+            // below the tangent's tolerance; in 2D element_average<D, true> sums
+            // the condensed tangent itself
             const bool stale = Aout && spec && !capped && rprev <= 1e-4 * r0;
             const bool stale2 = stale && D == 2;
             constexpr int NA = D2 * (D2 + 1) / 2;  // lower triangle of a symmetric d^2 x d^2
@@ -3259,6 +3258,7 @@ __global__ __launch_bounds__(NT, 2) void rve_solve_kernel(SolveArgs a) {
     }
 }
 
+#if FEHMM_NWAVE == 4
 // The Newton residual and the element tangents of every RVE at its stored (or
 // zero) fluctuation, alone: one element pass and the node gather of R per RVE
 // (the assembly phase of a Newton iteration, timed on its own by
@@ -3289,11 +3289,12 @@ __global__ __launch_bounds__(NT, 2) void rve_assembly_kernel(SolveArgs a) {
     }
 }
 
+int lds_static_bytes() { return (int)sizeof(Smem); }
+#endif
+
 __global__ void reset_counter_kernel(unsigned int* counter) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0u;
 }
-
-int lds_static_bytes() { return (int)sizeof(Smem); }
 
 // dynamic LDS limits are raised once per process, outside any stream capture
 hipError_t prepare_rve_solve() {
@@ -3307,6 +3308,7 @@ hipError_t prepare_rve_solve() {
     return hipSuccess;
 }
 
+#if FEHMM_NWAVE == 4
 hipError_t launch_rve_assembly(const SolveArgs& a, int nslots, hipStream_t stream) {
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, stream, a.counter);
     if (a.dim == 2)
@@ -3315,6 +3317,7 @@ hipError_t launch_rve_assembly(const SolveArgs& a, int nslots, hipStream_t strea
         hipLaunchKernelGGL((rve_assembly_kernel<3>), dim3(nslots), dim3(NT), 0, stream, a);
     return hipGetLastError();
 }
+#endif
 
 hipError_t launch_rve_solve(const SolveArgs& a, int nslots, size_t dyn_bytes, bool fp32, hipStream_t stream) {
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, stream, a.counter);

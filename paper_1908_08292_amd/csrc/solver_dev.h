@@ -24,7 +24,7 @@ struct BackRec {
 };
 
 struct DevPlan {
-    int32_t d, n, nnode, nelem, nfront, lds_ok;  // lds_ok: every front fits the LDS front buffer
+    int32_t d, n, nnode, nelem, nfront, lds_ok;  // lds_ok: every front's panel fits LDS
     const DevFront* fronts;
     const int32_t* rows;
     const int32_t* relind;
@@ -92,7 +92,7 @@ struct SolveArgs {
     double ir_eta_tan;           // same for the d^2 tangent columns (Frobenius)
 };
 
-// LDS available to the front buffer (packed front + m x d^2 rhs rows)
+// LDS of a CU
 constexpr int kLdsBytesMax = 160 * 1024;
 
 // tiles of the global-front updates: kTileM rows x (64 or 128) columns per
