@@ -476,41 +476,37 @@ int rve_batch_create(const rve_mesh* meshes, int64_t B, rve_batch* out) {
     // 32 x 32: 27.8 and 22.7).  And where more of the others than CUs have fronts in global
     // memory, which are as fast two to a CU as alone: 512 of 48 x 48 with 8 of 40 x 40
     // 169 and 122 ms.
-    auto alone = [](const PlanEntry* p) {
-        return p->dev.lds_ok && p->lds_need[0] + w4::lds_static_bytes() > kLdsBytesMax / 2;
-    };
+    std::vector<char> is_large(plans.size());
+    for (size_t q = 0; q < plans.size(); ++q)
+        is_large[q] = plans[q]->dev.lds_ok && plans[q]->lds_need[0] + w4::lds_static_bytes() > kLdsBytesMax / 2;
     double large = 0, large_max = 0, others = 0;
-    int64_t others_global = 0;
+    int64_t n_large = 0, others_global = 0;
     for (int64_t r = 0; r < B; ++r) {
-        const PlanEntry* p = meshes[r]->plan;
-        if (alone(p)) {
+        if (is_large[rve_plan[r]]) {
             large += cost[r];
             large_max = std::max(large_max, cost[r]);
+            n_large++;
         } else {
             others += cost[r];
-            others_global += p->dev.lds_ok ? 0 : 1;
+            others_global += plans[rve_plan[r]]->dev.lds_ok ? 0 : 1;
         }
     }
     const bool split =
         large > 0 && others > 0 && (others > 2.4 * (kNumCu * large_max - large) || others_global > kNumCu);
     std::vector<int32_t> plan_cls(plans.size(), 0);
-    for (size_t q = 0; q < plans.size(); ++q) plan_cls[q] = split && !alone(plans[q]) ? 1 : 0;
+    for (size_t q = 0; q < plans.size(); ++q) plan_cls[q] = split && !is_large[q] ? 1 : 0;
     std::vector<int32_t> order(B);
     for (int64_t r = 0; r < B; ++r) order[r] = (int32_t)r;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-        const int32_t cx = plan_cls[rve_plan[x]], cy = plan_cls[rve_plan[y]];
-        return cx != cy ? cx < cy : cost[x] > cost[y];
-    });
+    if (plans.size() > 1)
+        std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+            const int32_t cx = plan_cls[rve_plan[x]], cy = plan_cls[rve_plan[y]];
+            return cx != cy ? cx < cy : cost[x] > cost[y];
+        });
     auto launch_of = [&](int only) {  // of the RVEs of one class, or (-1) of all
         LaunchClass c;
-        for (int64_t r = 0; r < B; ++r) {
-            if (only >= 0 && plan_cls[rve_plan[r]] != only) {
-                c.first += plan_cls[rve_plan[r]] < only ? 1 : 0;
-                continue;
-            }
-            c.count++;
-            c.panel_rves += meshes[r]->plan->dev.lds_ok ? 1 : 0;
-        }
+        c.first = only == 1 ? n_large : 0;
+        c.count = only < 0 ? B : only == 0 ? n_large : B - n_large;
+        c.panel_rves = c.count - (only == 0 ? 0 : others_global);
         for (size_t q = 0; q < plans.size(); ++q) {
             const PlanEntry* p = plans[q];
             if (only >= 0 && plan_cls[q] != only) continue;
